@@ -135,20 +135,24 @@ SEQUENTIAL_NOTE = ("sequential per worker (each read depends on every earlier on
                    "workgroup per worker whose waves split the chains: bound by instruction "
                    "issue and latency on the chain, not by HBM; frac is the HBM fraction for "
                    "reference")
+POLICY_NOTE = ("one workgroup per worker scans its chains chunk by chunk: bound by the random "
+               "gathers of the sizes and by instruction issue, not by HBM bandwidth; frac is the "
+               "HBM fraction for reference")
 
 
 def _kernel_short_name(full):
     """'ns::(anonymous namespace)::plan_hist<true>(args...)' -> 'plan_hist';
-    the policy kernels keep their policy: 'ps_sim<1>(...)' -> 'ps_sim_naive',
-    'ps_staged<2>(...)' -> 'ps_sim_staging' (the names the library launches them by), and
+    the policy kernels keep their policy: 'ps_sim<1, 512>(...)' -> 'ps_sim_naive' (the
+    name the library launches it by), and
     the staging schedule's 8-byte-size unpartition its launch name 'st_unpart8'."""
     import re
     m = re.findall(r"(\w+)(?:<([^>()]*)>)?\(", full)
     if not m:
         return full
     name, targ = m[-1]
-    if name in ("ps_sim", "ps_staged") and targ.strip().isdigit() and int(targ) < len(POLICY_NAMES):
-        return f"ps_sim_{POLICY_NAMES[int(targ)]}"
+    policy = targ.split(",")[0].strip()
+    if name == "ps_sim" and policy.isdigit() and int(policy) < len(POLICY_NAMES):
+        return f"ps_sim_{POLICY_NAMES[int(policy)]}"
     if name == "st_unpart" and targ.strip() == "true":  # the 8-byte-size form, launched as such
         return "st_unpart8"
     return name
@@ -482,7 +486,7 @@ def time_policies(nopfs, torch, wl, w, job, M, M_w, R, tier, sizes, steps, warmu
         J = model.J
         out[name]["slowest_worker_s"] = round(float(f.max()), 3)
         out[name]["mean_worker_s"] = round(float(f.mean()), 3)
-        out[name]["roofline"]["note"] = SEQUENTIAL_NOTE
+        out[name]["roofline"]["note"] = POLICY_NOTE
         out[name]["fetch_s"] = {"pfs": round(float(tot[0]), 1),
                                 "remote": round(float(tot[1:1 + J].sum()), 1),
                                 "own": round(float(tot[1 + J:].sum()), 1)}

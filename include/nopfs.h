@@ -335,8 +335,8 @@ int nopfs_buffer_sim(const nopfs_job* job, const int32_t* R, const int32_t* next
  *              t(0) = Q(0) / p0, t(f) = max(Q(f) / p0, t(f-1) + u(f-1)).
  *            With fill all 0 (an unlimited buffer), NOPFS is
  *            nopfs_fetch_model's t (avail = the summed read times / p0).
- * The evaluation is sequential per worker, in this order, with IEEE double
- * operations: results do not depend on the launch.
+ * Results are those of the evaluation read by read, in this order, with IEEE
+ * double operations; they do not depend on the launch.
  *   R:      int32 [N][M_max], nopfs_access_streams' output for this job.
  *   sizes:  int64 [F] sample sizes in bytes.
  *   src:    int16 [N][M_max], nopfs_fetch_model's sources (NOPFS only; may
@@ -351,7 +351,7 @@ int nopfs_buffer_sim(const nopfs_job* job, const int32_t* R, const int32_t* next
  *   io:     double [N][1 + 2J], output: fetch time summed by source class,
  *           0 the PFS, 1 + j another worker's tier j, 1 + J + j the own tier
  *           j (all 0 for PERFECT).
- * One wave per worker replays its stream. No scratch. Errors: EINVAL (also
+ * No scratch. Errors: EINVAL (also
  * a policy outside 0..3, or a missing src or fill the policy needs), ERANGE
  * (J > 32), EDEVICE. */
 int nopfs_policy_sim(const nopfs_job* job, const int32_t* R, const int64_t* sizes,

@@ -163,11 +163,13 @@ __device__ inline uint32_t wave_inclusive_scan(uint32_t v) {
 }
 
 // One DPP move of a 64-bit value (both halves with the same control); lanes
-// with no source, or in rows outside RowMask, receive 0.
+// with no source, or in rows outside RowMask, receive 0 (with all rows taking
+// part the instruction itself gives 0, so the result needs no clearing first).
 template <int Ctrl, int RowMask>
 __device__ __forceinline__ uint64_t dpp_move64(uint64_t v) {
-  const uint32_t lo = __builtin_amdgcn_update_dpp(0u, uint32_t(v), Ctrl, RowMask, 0xf, false);
-  const uint32_t hi = __builtin_amdgcn_update_dpp(0u, uint32_t(v >> 32), Ctrl, RowMask, 0xf, false);
+  constexpr bool kZero = RowMask == 0xf;
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0u, uint32_t(v), Ctrl, RowMask, 0xf, kZero);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0u, uint32_t(v >> 32), Ctrl, RowMask, 0xf, kZero);
   return (uint64_t(hi) << 32) | lo;
 }
 

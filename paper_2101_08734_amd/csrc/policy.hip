@@ -19,42 +19,71 @@
 //                    t(0) = Q(0) / p0, t(f) = max(Q(f) / p0, t(f-1) + u(f-1)).
 // finish = t(last) + u(last); io sums fetch times by source class.
 //
-// The recurrence is sequential within a worker (a read may wait for the
-// consumption of any earlier read), so each worker is one workgroup on one
-// CU, and the arithmetic is the same IEEE operations in the same order as
-// the definition: results are bit-identical to a read-by-read evaluation.
-// (The maxima are taken with fmax: every operand is finite and non-negative
-// and never -0, where fmax and "the larger of the two" agree bit for bit.)
-// Reads go in batches of 64, one per lane: the per-read terms (u, fetch,
-// read) are lane-parallel, the chains step through the batch with lane reads
-// (full batches unrolled, so later steps' operands are formed while earlier
-// steps finish). The fetch-time sums by class depend on no t and run in a
-// wave of their own.
+// The results are those of the definition evaluated read by read with IEEE
+// doubles, bit for bit, but the chains are not stepped read by read: they are
+// scanned. While the running value x of a chain stays inside one binade
+// [2^E, 2^(E+1)), its values are consecutive integers (their bit patterns),
+// and adding a >= 0 with rounding adds an integer that depends on a and E
+// alone, round(a / ulp), unless a / ulp is exactly halfway between two
+// integers (then the parity of x decides). It is read off a single addition:
+// bits(2^E + a) - bits(2^E). A maximum with w is a maximum of bit patterns,
+// and rounding is monotone, so each read of a chain is a link
+//   x -> max(x + add, floor)    on 64-bit integers
+// (Q: add from read(f), floor = bits(p0 t(fill(f) - 1)) + add; with y(f) =
+// t(f) + u(f): add from u(f), floor = bits(Q(f) / p0) + add, t(f) the larger
+// of y(f-1) and Q(f) / p0), and links compose into links of the same form: a
+// prefix scan gives every value. The scan is exact up to the first read that
+// leaves the binade, falls halfway, has an operand that is not a plain
+// non-negative number, or waits for a read whose t is not known yet. Up to
+// there the values are kept, that read is stepped with ordinary additions
+// and maxima, and the scan resumes behind it. A row of M reads has about
+// log2(M) binades, and halfway cases are rare (a / ulp has tens of fractional
+// bits), so few scans are cut short.
 //
-//   ps_sim    -- Perfect and Naive: one wave for the t chain (Naive: a
-//                second for the PFS sum). Ids two batches ahead, sizes one.
-//   ps_staged -- StagingBuffer and NoPFS: a Q wave, a T wave and a sums wave.
-//                In iteration k the Q wave forms batch k's terms and its Q
-//                chain (waits p0 t(g) from an LDS ring of the last 8,192
-//                positions, older ones loaded from global memory a batch
-//                ahead), while the T wave runs batch k - 1's t chain from the
-//                Q values left in LDS (one division Q / p0 across the lanes).
-//                A batch waiting on batch k - 1 gets its Q chain after the
-//                iteration's first barrier; one waiting inside itself is
-//                stepped read by read, Q and t, by the T wave in the next
-//                iteration. The sums wave gives each class a lane.
+//   ps_sim -- one workgroup per worker (512 threads; 256 where workers
+//             outnumber the compute units), chunks of four reads per thread:
+//             per-read terms (ids, sources and windows loaded two chunks
+//             ahead, sizes and far waits one), the Q scan and the y scan (one
+//             barrier each) and one barrier that finds the first read, if
+//             any, at which the scan stops. The t of this chunk and the one
+//             before stay in LDS for the waits. Where scans would stop early
+//             (windows of less than 512 reads, the first reads of a row), one
+//             wave takes the chunk in scans of 64 reads without barriers, and
+//             steps reads one by one where even those stop within 8. The
+//             fetch-time sums by class are sums of the same kind (no maxima,
+//             only the final value needed): integer totals per chunk, and a
+//             chunk in which a class leaves its binade is added up in order
+//             by one wave.
+//
+// Stepping read by read took 37 ns a read (NoPFS, a chain of dependent
+// additions per worker); ImageNet-22k (2.2M reads per worker): Perfect 36,
+// Naive 56, StagingBuffer 63, NoPFS 82 ms, now NoPFS 13.0. ImageNet-1k on 256
+// workers: 7.4 / 11.3 / 12.8 / 16.7 ms, now 1.4 / 1.7 / 2.4 / 2.8. Bounds: the
+// random 8-byte gathers of the sizes (NoPFS at ImageNet-22k without them:
+// 8.1 ms) and, below that, instruction issue (1,250 vector instructions per
+// wave and chunk on two waves per SIMD). 1,024 threads of two reads each:
+// 15.3 ms (the scans' cross-lane steps double).
 
+#include <cmath>
 #include <new>
+#include <type_traits>
 
 #include "common.hpp"
 
 namespace nopfs {
 namespace {
 
-constexpr int kPsRingLog = 13;
-constexpr int64_t kPsRing = int64_t(1) << kPsRingLog;  // positions of t kept in LDS
+// Threads per worker: 512 where every worker has a compute unit of its own
+// (up to 256 workers), 256 where workers outnumber them, so that two
+// workgroups fit a compute unit's LDS.
+constexpr int kPsFew = 512, kPsMany = 256;
+constexpr int64_t kPsUnits = 256;                     // compute units
+constexpr int kPsPer = 4;                             // reads per thread and chunk
+constexpr int kPsMinStep = 512;   // scans shorter than this, twice in a chunk: one wave goes on
+constexpr int kPsMinWave = 8;     // wave scans shorter than this: read by read
 constexpr int kPsMaxJ = 32;
 constexpr int kPsClasses = 1 + 2 * kPsMaxJ;           // PFS, remote j, own j
+constexpr int kPsCopies = 16;                         // partial sums per class in LDS
 
 enum : int32_t { kPerfect = 0, kNaive = 1, kStaging = 2, kNoPFS = 3 };
 
@@ -68,19 +97,23 @@ struct PsRates {
   double thr[kPsClasses];  // by class: 0 the PFS, 1 + j remote tier j, 1 + J + j own tier j
   double wthr;             // min(beta, w0 / p0)
   double c, p0;
+  double rthr[kPsClasses], rwthr, rc, rp0;  // their reciprocals
   int32_t J;
+  int32_t rcp;             // quotients may be formed from the reciprocals
 };
 
 __device__ __forceinline__ int64_t ps_row_len(const PsShape& r, int64_t i) {
   return r.E * epoch_len(r.F, r.N, r.B, r.drop_last, i);
 }
 
+__device__ __forceinline__ uint64_t bits_of(double v) { return __builtin_bit_cast(uint64_t, v); }
+__device__ __forceinline__ double double_of(uint64_t b) { return __builtin_bit_cast(double, b); }
+
 __device__ __forceinline__ double rl_d(double v, int lane) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = __builtin_amdgcn_readlane(uint32_t(b), lane);
-  const uint32_t hi = __builtin_amdgcn_readlane(uint32_t(b >> 32), lane);
-  return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
+  return double_of(read_lane64(bits_of(v), lane));
 }
+
+__device__ __forceinline__ uint64_t max_u64(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
 // class of a source code (0 the PFS, 128 + j remote, 256 + j own); any
 // other code, and every code outside NoPFS, reads from the PFS
@@ -91,408 +124,675 @@ __device__ __forceinline__ int ps_class(int32_t policy, int32_t code, int32_t J)
   return 0;
 }
 
-// Perfect and Naive. Naive takes a second wave per worker for its PFS
-// fetch-time sum: it depends on no t, so its sequential chain (stream order)
-// runs beside the t chain instead of inside it.
-template <int32_t kPolicy>
-constexpr int ps_threads() {
-  return kPolicy == kPerfect ? 64 : 128;
+// a / b from y = 1 / b, rounded as the division is: a first quotient, one
+// correction (within an ulp of a / b), and the correction with the exact
+// remainder, which gives the rounded quotient when y is within half an ulp
+// of 1 / b (Markstein, "Computation of elementary functions on the IBM RISC
+// System/6000 processor", 1990). Five operations instead of a division's
+// twelve. Valid away from overflow and underflow of any of the terms, which
+// rcp_ok and the range of binade_of keep it from.
+__device__ __forceinline__ double div_rcp(double a, double b, double y) {
+  const double q0 = a * y;
+  const double q1 = __builtin_fma(__builtin_fma(-b, q0, a), y, q0);
+  return __builtin_fma(__builtin_fma(-b, q1, a), y, q1);
 }
 
-template <int32_t kPolicy>
-__global__ void __launch_bounds__(ps_threads<kPolicy>())
+// b's quotients may be formed from y = 1 / b: y is closer to 1 / b than half
+// an ulp of any number of its binade can be, and b is far from the ends of
+// the exponent range.
+bool rcp_ok(double b, double y) {
+  return b > 0x1p-300 && b < 0x1p300 && std::fabs(std::fma(-b, y, 1.0)) < 0x1p-53;
+}
+
+// The binade of a chain's value: bit patterns of its first value and of the
+// next binade's, and half its ulp. base = top = 0 (nothing can be added) when
+// the value is zero, below 2^-500 or above 2^500, negative or no number.
+struct Binade {
+  uint64_t base, top;
+  double half_ulp;
+};
+
+__device__ __forceinline__ Binade binade_of(double x) {
+  const uint32_t ex = uint32_t(bits_of(x) >> 52);  // sign and exponent
+  const bool ok = ex >= 1023u - 500u && ex <= 1023u + 500u;
+  Binade b;
+  b.base = ok ? uint64_t(ex) << 52 : 0ull;
+  b.top = ok ? uint64_t(ex + 1u) << 52 : 0ull;
+  b.half_ulp = double_of(uint64_t(ok ? ex - 53u : 0u) << 52);
+  return b;
+}
+
+// The integer that adding a adds inside the binade; *stop is set (and the
+// result 0) when a is not below 2^E, not a plain non-negative number, or
+// halfway between two multiples of the ulp. 2^E + a < 2^(E+1) rounds to a
+// multiple of the ulp with ties to even; its difference to 2^E and the
+// rounding error a - difference are exact.
+__device__ __forceinline__ uint64_t units(double a, const Binade& b, bool* stop) {
+#pragma clang fp contract(off)
+  const double base = double_of(b.base);
+  const double z = base + a;
+  const double err = a - (z - base);
+  const bool bad = bits_of(a) >= b.base || __builtin_fabs(err) == b.half_ulp;
+  *stop = *stop || bad;
+  return bad ? 0ull : bits_of(z) - b.base;
+}
+
+// x -> max(x + add, floor). {0, 0} leaves every x as it is; where only sums
+// are scanned (kMax false) floor stays 0.
+struct Link {
+  uint64_t add, floor;
+};
+
+template <bool kMax>
+__device__ __forceinline__ Link then(const Link& a, const Link& b) {
+  return Link{a.add + b.add, kMax ? max_u64(a.floor + b.add, b.floor) : 0ull};
+}
+template <bool kMax>
+__device__ __forceinline__ uint64_t apply(uint64_t x, const Link& l) {
+  return kMax ? max_u64(x + l.add, l.floor) : x + l.add;
+}
+
+// One step of a lane scan: the link of the DPP source lane goes before this
+// lane's (no source: {0, 0}; floor then becomes at least add, which is below
+// x + add for every x the links are applied to).
+template <bool kMax, int Ctrl, int RowMask>
+__device__ __forceinline__ void link_step(Link& v) {
+  const Link p{dpp_move64<Ctrl, RowMask>(v.add), kMax ? dpp_move64<Ctrl, RowMask>(v.floor) : 0ull};
+  v = then<kMax>(p, v);
+}
+template <bool kMax>
+__device__ __forceinline__ Link wave_link_scan(Link v) {  // inclusive, all lanes active
+  link_step<kMax, 0x111, 0xf>(v);  // row_shr:1
+  link_step<kMax, 0x112, 0xf>(v);  // row_shr:2
+  link_step<kMax, 0x114, 0xf>(v);  // row_shr:4
+  link_step<kMax, 0x118, 0xf>(v);  // row_shr:8
+  link_step<kMax, 0x142, 0xa>(v);  // row_bcast:15, rows 1 and 3
+  link_step<kMax, 0x143, 0xc>(v);  // row_bcast:31, rows 2 and 3
+  return v;
+}
+template <bool kMax>
+__device__ __forceinline__ Link wave_link_shift(const Link& v) {  // the lane below's, {0, 0} in lane 0
+  return Link{dpp_move64<0x138, 0xf>(v.add), kMax ? dpp_move64<0x138, 0xf>(v.floor) : 0ull};
+}
+
+// The chain's value before this wave's reads and after the whole chunk's,
+// from the waves' links in LDS (every wave computes both).
+template <bool kMax, int kWaves>
+__device__ __forceinline__ void block_links(const Link* tot, int wave, int lane, uint64_t x,
+                                            uint64_t* before, uint64_t* after) {
+  static_assert(kWaves == 4 || kWaves == 8, "lanes 0 to 7 of a row of 16");
+  Link v = tot[lane & (kWaves - 1)];
+  link_step<kMax, 0x111, 0xf>(v);
+  link_step<kMax, 0x112, 0xf>(v);
+  if (kWaves == 8) link_step<kMax, 0x114, 0xf>(v);
+  auto lane_link = [&](int l) {
+    return Link{read_lane64(v.add, l), kMax ? read_lane64(v.floor, l) : 0ull};
+  };
+  *before = wave > 0 ? apply<kMax>(x, lane_link(wave - 1)) : x;
+  *after = apply<kMax>(x, lane_link(kWaves - 1));
+}
+
+template <int32_t kPolicy, int kPsThreads>
+__global__ void __launch_bounds__(kPsThreads)
 ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ sizes,
        const int16_t* __restrict__ src, const int32_t* __restrict__ fill, PsRates rt,
        double* __restrict__ t, double* __restrict__ finish, double* __restrict__ io) {
 #pragma clang fp contract(off)
-  static_assert(kPolicy == kPerfect || kPolicy == kNaive, "the staging policies: ps_staged");
-  __shared__ double thr[kPsClasses];
+  constexpr bool kStaged = kPolicy == kStaging || kPolicy == kNoPFS;
+  constexpr bool kIo = kPolicy != kPerfect;
+  constexpr int kPsWaves = kPsThreads / 64;
+  constexpr int kPsChunk = kPsThreads * kPsPer;
+  constexpr int kRing = kStaged ? 2 * kPsChunk : kPsChunk;
+  constexpr int kCls = kPolicy == kNoPFS ? kPsClasses : 1;
+  __shared__ double ring[kRing];                   // t of position f at [f % kRing]
+  __shared__ double st_u[kPsChunk];                // a chunk's terms, where one wave needs them all
+  __shared__ double st_rd[kIo ? kPsChunk : 1];
+  __shared__ double st_w[kStaged ? kPsChunk : 1];
+  __shared__ int32_t st_g[kStaged ? kPsChunk : 1];
+  __shared__ double st_f[kIo ? kPsChunk : 1];      // a chunk's fetch times and classes
+  __shared__ uint8_t st_c[kPolicy == kNoPFS ? kPsChunk : 1];
+  __shared__ uint64_t io_x[kCls];                  // bits of each class's sum
+  __shared__ uint64_t io_acc[kCls * kPsCopies];    // this chunk's units, in partial sums
+  __shared__ uint32_t io_bad[kCls];                // a read of this chunk the units do not cover
+  __shared__ uint32_t s_io_slow;
+  __shared__ double thr[kPsClasses], rthr[kPsClasses];
+  __shared__ Link s_q[kPsWaves], s_y[kPsWaves];
+  __shared__ uint32_t s_stop[kPsWaves];
+  __shared__ double s_Q, s_Y;
+  __shared__ int32_t s_pos;
+  __shared__ uint32_t s_near[2];  // of chunks (even, odd): reads wait for reads of the chunk
   const int64_t i = blockIdx.x;
-  const int lane = threadIdx.x & 63;
-  const int64_t Mi = ps_row_len(r, i);
-  const int64_t M = r.M_max;
-  const int32_t* Rr = R + i * M;
-  double* tr = t + i * M;
-  for (int c = threadIdx.x; c < kPsClasses; c += ps_threads<kPolicy>()) thr[c] = rt.thr[c];
-  __syncthreads();
-  if (kPolicy != kPerfect && threadIdx.x >= 64) {
-    // the second wave: the PFS fetch time (class 0), reads in stream order
-    // (ids one batch ahead, sizes when they arrive)
-    double a0 = 0.0, a1 = 0.0;  // class lane, class 64 + lane
-    auto ids = [&](int64_t f0, int32_t& k, int32_t& code) {
-      const int64_t f = f0 + lane;
-      const int64_t fc = f < Mi ? f : 0;  // unconditional (Mi >= 1 inside the loop)
-      k = Rr[fc];
-      code = 0;
-      if (f >= Mi) k = -1;
-    };
-    int32_t kN = -1, cN = 0;
-    if (Mi > 0) ids(0, kN, cN);
-    for (int64_t f0 = 0; f0 < Mi; f0 += 64) {
-      const int32_t k = kN, code = cN;
-      if (f0 + 64 < Mi) ids(f0 + 64, kN, cN);
-      const double s = double((k >= 0 && k < r.F) ? sizes[k] : int64_t(0));
-      const int cls = ps_class(kPolicy, code, rt.J);
-      const double fetch = s / thr[cls];
-      const int nb = Mi - f0 < 64 ? int(Mi - f0) : 64;
-      if (nb == 64) {
-        // one class (the PFS) and a full batch: straight-line adds
-        double a = rl_d(a0, 0);
-#pragma unroll
-        for (int q = 0; q < 64; ++q) a = a + rl_d(fetch, q);
-        a0 = lane == 0 ? a : a0;
-        continue;
-      }
-      uint64_t rem = nb == 64 ? ~uint64_t(0) : (uint64_t(1) << nb) - 1;
-      while (rem) {
-        const int c = __builtin_amdgcn_readlane(cls, __builtin_ctzll(rem));
-        const uint64_t m = __ballot(cls == c) & rem;
-        rem &= ~m;
-        double a = c < 64 ? rl_d(a0, c) : rl_d(a1, c - 64);
-        for (uint64_t mm = m; mm; mm &= mm - 1) a = a + rl_d(fetch, __builtin_ctzll(mm));
-        if (c < 64) {
-          a0 = lane == c ? a : a0;
-        } else {
-          a1 = lane == c - 64 ? a : a1;
-        }
-      }
-    }
-    const int K = 1 + 2 * rt.J;
-    double* ior = io + i * K;
-    if (lane < K) ior[lane] = a0;
-    if (64 + lane < K) ior[64 + lane] = a1;
-    return;
-  }
-
-  // per-lane raw inputs of a batch: the id (only a load here, so nothing
-  // waits for it until it is used)
-  auto load_ids = [&](int64_t f0, int32_t& k, int32_t& code, int32_t& fl) {
-    const int64_t f = f0 + lane;
-    k = -1;
-    code = 0;
-    fl = 0;
-    if (f < Mi) k = Rr[f];
-  };
-  auto size_of = [&](int32_t k) -> int64_t {
-    return (k >= 0 && k < r.F) ? sizes[k] : int64_t(0);
-  };
-
-  double tprev = 0.0, uprev = 0.0;
-
-  // pipeline: ids two batches ahead, sizes one
-  int32_t kA, cA, fA, kB, cB, fB;
-  load_ids(0, kB, cB, fB);
-  int64_t sB = size_of(kB);
-  load_ids(64, kA, cA, fA);
-  for (int64_t f0 = 0; f0 < Mi; f0 += 64) {
-    // this batch's inputs
-    const double s = double(sB);
-    const int cls = ps_class(kPolicy, cB, rt.J);
-    // per-read terms, lane-parallel, in the definition's expressions
-    const double u = s / rt.c;
-    const double fetch = s / thr[cls];
-    const double rd = fetch + s / rt.wthr;
-    // the next batch's sizes, the one after's ids
-    sB = size_of(kA);
-    cB = cA;
-    fB = fA;
-    load_ids(f0 + 128, kA, cA, fA);
-
-    const int nb = Mi - f0 < 64 ? int(Mi - f0) : 64;
-    double tb = -1.0;  // lane q: t of read f0 + q
-    // one read's step
-    auto step = [&](int q) {
-      const int64_t f = f0 + q;
-      const double uq = rl_d(u, q);
-      const double rq = rl_d(rd, q);
-      double tf;
-      if (kPolicy == kPerfect) {
-        tf = f == 0 ? 0.0 : tprev + uprev;
-      } else {
-        tf = f == 0 ? rq : (tprev + uprev) + rq;
-      }
-      tb = lane == q ? tf : tb;
-      tprev = tf;
-      uprev = uq;
-    };
-    if (nb == 64) {
-      // a full batch: straight-line steps, so the terms of later steps can
-      // be formed while earlier ones finish
-#pragma unroll
-      for (int q = 0; q < 64; ++q) step(q);
-    } else {
-      for (int q = 0; q < nb; ++q) step(q);
-    }
-    const int64_t f = f0 + lane;
-    if (f < Mi) tr[f] = tb;
-  }
-  for (int64_t f = Mi + lane; f < M; f += 64) tr[f] = -1.0;
-  if (kPolicy == kPerfect) {  // no fetches (the other policies' second wave writes io)
-    const int K = 1 + 2 * rt.J;
-    double* ior = io + i * K;
-    if (lane < K) ior[lane] = 0.0;
-    if (64 + lane < K) ior[64 + lane] = 0.0;
-  }
-  if (lane == 0) finish[i] = Mi > 0 ? tprev + uprev : 0.0;
-}
-
-// The staging policies with the Q and t chains in two waves of the worker's
-// workgroup (and the fetch-time sums in a third). Iteration k: the Q wave
-// forms batch k's per-read terms and, when every lookback of the batch is
-// already known, its Q chain; the T wave runs batch k - 1's t chain from the
-// Q values the Q wave left in LDS. Waits of batch k on batch k - 1 are known
-// only once the T wave has finished it, so such a batch's Q chain runs after
-// the iteration's first barrier; a batch with a lookback inside itself is
-// stepped read by read (Q and t) by the T wave in the next iteration. Every
-// wave passes the same two barriers per iteration, and the operations are
-// those of the single-wave evaluation, in the same order.
-struct PsSlot {
-  double Qb[64];   // Q(f0 + q)
-  double u[64];    // compute time of read f0 + q
-  double rd[64];   // its staging time
-  double W[64];    // its wait p0 t(g), lookbacks before the batch (stepped batches)
-  int32_t gq[64];  // its lookback g - f0 (lookbacks inside the batch)
-  uint64_t inb;    // lanes whose lookback is inside the batch
-  int32_t near;    // the T wave steps the batch read by read
-};
-
-template <int32_t kPolicy>
-__global__ void __launch_bounds__(192)
-ps_staged(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ sizes,
-          const int16_t* __restrict__ src, const int32_t* __restrict__ fill, PsRates rt,
-          double* __restrict__ t, double* __restrict__ finish, double* __restrict__ io) {
-#pragma clang fp contract(off)
-  __shared__ double ring[kPsRing];
-  __shared__ double thr[kPsClasses];
-  __shared__ PsSlot slot[2];
-  __shared__ double s_Qend;  // Q after the last batch the T wave stepped
-  const int64_t i = blockIdx.x;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t Mi = ps_row_len(r, i);
   const int64_t M = r.M_max;
   const int32_t* Rr = R + i * M;
   const int16_t* Sr = kPolicy == kNoPFS ? src + i * M : nullptr;
-  const int32_t* Fr = fill + i * M;
+  const int32_t* Fr = kStaged ? fill + i * M : nullptr;
   double* tr = t + i * M;
-  for (int c = threadIdx.x; c < kPsClasses; c += 192) thr[c] = rt.thr[c];
-  if (threadIdx.x == 0) s_Qend = 0.0;
+  const int K = 1 + 2 * rt.J;
+  for (int c = tid; c < kPsClasses; c += kPsThreads) {
+    thr[c] = rt.thr[c];
+    rthr[c] = rt.rthr[c];
+  }
+  if (kIo) {
+    for (int c = tid; c < kCls; c += kPsThreads) {
+      io_x[c] = 0;
+      io_bad[c] = 0;
+    }
+    for (int c = tid; c < kCls * kPsCopies; c += kPsThreads) io_acc[c] = 0;
+  }
+  if (tid == 0) {
+    s_io_slow = 0;
+    s_near[0] = s_near[1] = 0;
+  }
   __syncthreads();
-  const int64_t nbat = (Mi + 63) / 64;
 
-  // -- Q wave: inputs two batches ahead (ids), one ahead (sizes, far lookbacks)
-  auto load_ids = [&](int64_t f0, int32_t& k, int32_t& code, int32_t& fl) {
-    const int64_t f = f0 + lane;
-    k = -1;
-    code = 0;
-    fl = 0;
-    if (f < Mi) {
-      k = Rr[f];
-      if (kPolicy == kNoPFS) code = Sr[f];
-      fl = Fr[f];
+  // a thread's four consecutive entries of a row in the chunk at f0 (`none`
+  // past the row's reads)
+  auto load4 = [&](const auto* row, int64_t f0, int32_t v[kPsPer], int32_t none) {
+    const int64_t f = f0 + kPsPer * tid;
+    if (f0 + kPsChunk <= Mi) {
+      std::remove_cv_t<std::remove_reference_t<decltype(*row)>> w[kPsPer];
+      __builtin_memcpy(w, row + f, sizeof(w));
+#pragma unroll
+      for (int j = 0; j < kPsPer; ++j) v[j] = w[j];
+    } else {
+#pragma unroll
+      for (int j = 0; j < kPsPer; ++j) {
+        const int32_t w = row[f + j < Mi ? f + j : 0];
+        v[j] = f + j < Mi ? w : none;
+      }
     }
   };
-  auto look = [&](int64_t f0, int32_t fl) -> int64_t {
-    const int64_t f = f0 + lane;
+  auto gather = [&](const int32_t k[kPsPer], int64_t s[kPsPer]) {
+#pragma unroll
+    for (int j = 0; j < kPsPer; ++j) {
+      const bool in = k[j] >= 0 && k[j] < r.F;
+      const int64_t v = sizes[in ? k[j] : 0];
+      s[j] = in ? v : 0;
+    }
+  };
+  // position whose consumption read f waits for, from its window (-1: none)
+  auto look = [&](int64_t f, int32_t fl) -> int64_t {
     int64_t g = int64_t(fl) - 1;
     if (g > f - 1) g = f - 1;
-    if (g < -1 || f >= Mi) g = -1;
-    return g;
+    return g < -1 ? -1 : g;
   };
-  auto size_of = [&](int32_t k) -> int64_t {
-    return (k >= 0 && k < r.F) ? sizes[k] : int64_t(0);
+  // t of the waits that have left the ring by the chunk at f0
+  auto far_waits = [&](int64_t f0, const int32_t fl[kPsPer], double w[kPsPer]) {
+#pragma unroll
+    for (int j = 0; j < kPsPer; ++j) {
+      const int64_t f = f0 + kPsPer * tid + j;
+      const int64_t g = f < Mi ? look(f, fl[j]) : -1;
+      w[j] = tr[g >= 0 && g < f0 - kRing ? g : 0];  // unconditional; used for such g only
+    }
   };
-  auto far_wait = [&](int64_t f0, int64_t g) -> double {
-    return (g >= 0 && g < f0 - kPsRing) ? tr[g] : 0.0;
-  };
-  double Q = 0.0;
-  int32_t kA = -1, cA = 0, fA = 0, kB = -1, cB = 0, fB = 0;
-  int64_t sB = 0;
-  double farB = 0.0;
-  if (wave == 0) {
-    load_ids(0, kB, cB, fB);
-    sB = size_of(kB);
-    load_ids(64, kA, cA, fA);
-  }
-  // -- T wave
-  double tprev = 0.0, uprev = 0.0;
-  // -- io wave: fetch time by class, ids and sources one batch ahead
-  double a0 = 0.0, a1 = 0.0;
-  const int K = 1 + 2 * rt.J;  // source classes
-  int32_t kN = -1, cN = 0;
-  auto io_ids = [&](int64_t f0, int32_t& k, int32_t& code) {
-    const int64_t f = f0 + lane;
-    const int64_t fc = f < Mi ? f : 0;
-    k = Rr[fc];
-    code = kPolicy == kNoPFS ? int32_t(Sr[fc]) : 0;
-    if (f >= Mi) k = -1;
-  };
-  if (wave == 2 && Mi > 0) io_ids(0, kN, cN);
 
-  for (int64_t k = 0; k <= nbat; ++k) {
-    const int64_t f0 = k * 64;
-    // Q wave registers kept across the iteration's first barrier
-    double rd = 0.0, far = 0.0;
-    int64_t g = -1;
-    bool q_done = false;
-    // ------------------------------------------------------------ phase 1
-    if (wave == 0 && k < nbat) {
-      const double s = double(sB);
-      const int cls = ps_class(kPolicy, cB, rt.J);
-      g = look(f0, fB);
-      far = farB;
-      const double u = s / rt.c;
-      const double fetch = s / thr[cls];
-      rd = fetch + s / rt.wthr;
-      sB = size_of(kA);
-      cB = cA;
-      fB = fA;
-      farB = far_wait(f0 + 64, look(f0 + 64, fA));
-      load_ids(f0 + 128, kA, cA, fA);
-      PsSlot& sl = slot[k & 1];
-      sl.u[lane] = u;
-      sl.rd[lane] = rd;
-      const bool prev_near = k > 0 && slot[(k - 1) & 1].near != 0;
-      // every lookback in a batch the T wave has finished (k - 2 or before)
-      if (!prev_near && __ballot(g >= f0 - 64) == 0) {
-        const double tg = g >= 0 ? (g >= f0 - kPsRing ? ring[g & (kPsRing - 1)] : far) : 0.0;
-        const double W = g >= 0 ? rt.p0 * tg : 0.0;
-        const int nb = Mi - f0 < 64 ? int(Mi - f0) : 64;
-        double Qb = 0.0;
-        if (nb == 64) {
+  // marks the chunk at f0 when one of its reads waits for another (bit 0),
+  // and when one of its first reads does (bit 1)
+  auto mark_near = [&](int64_t f0, const int32_t fl[kPsPer]) {
+    bool near = false;
 #pragma unroll
-          for (int q = 0; q < 64; ++q) {
-            Q = __builtin_fmax(Q, rl_d(W, q));
-            Q = Q + rl_d(rd, q);
-            Qb = lane == q ? Q : Qb;
-          }
+    for (int j = 0; j < kPsPer; ++j) {
+      const int64_t f = f0 + kPsPer * tid + j;
+      near = near || (f < Mi && look(f, fl[j]) >= f0);
+    }
+    if (near) atomicOr(&s_near[(f0 / kPsChunk) & 1], kPsPer * tid < kPsMinStep ? 3u : 1u);
+  };
+  // each class's sum after the chunk from the chunk's units, or a mark that
+  // the chunk's reads have to be added up in order (one wave)
+  auto io_check = [&]() -> bool {
+    bool any = false;
+    for (int c = lane; c < kCls; c += 64) {
+      uint64_t sum = 0;
+#pragma unroll
+      for (int q = 0; q < kPsCopies; ++q) {
+        sum += io_acc[c * kPsCopies + q];
+        io_acc[c * kPsCopies + q] = 0;
+      }
+      const uint64_t x = io_x[c];
+      const bool slow = io_bad[c] != 0u || (sum != 0u && x + sum >= binade_of(double_of(x)).top);
+      if (slow) io_bad[c] = 1;
+      else io_x[c] = x + sum;
+      any = any || slow;
+    }
+    return __ballot(any) != 0u;
+  };
+  // the marked classes' fetch times of the chunk (st_f, st_c), in stream
+  // order (one wave): 64 at a time where the sum stays inside its binade
+  auto io_ordered = [&](int n) {
+    for (int c = 0; c < kCls; ++c) {
+      if (io_bad[c] == 0u) continue;
+      double x = double_of(io_x[c]);
+      for (int b = 0; b < n; b += 64) {
+        const int at = b + lane;
+        const double v = st_f[at];
+        const bool on = at < n && (kPolicy != kNoPFS || st_c[at] == c);
+        const uint64_t m = __ballot(on);
+        if (m == 0) continue;
+        const Binade bx = binade_of(x);
+        bool stop = false;
+        const uint64_t d = units(v, bx, &stop);
+        const uint64_t sum = read_lane64(wave_inclusive_scan64(on ? d : 0ull), 63);
+        if (__ballot(on && stop) == 0 && bits_of(x) + sum < bx.top) {
+          x = double_of(bits_of(x) + sum);
         } else {
+          for (uint64_t mm = m; mm; mm &= mm - 1) x = x + rl_d(v, __builtin_ctzll(mm));
+        }
+      }
+      if (lane == 0) {
+        io_x[c] = bits_of(x);
+        io_bad[c] = 0;
+      }
+    }
+  };
+
+  double Q = 0.0, Y = 0.0;  // Q and y = t + u after the last read
+  int32_t kA[kPsPer], cA[kPsPer] = {}, fA[kPsPer] = {}, cB[kPsPer] = {}, fB[kPsPer] = {};
+  int64_t sB[kPsPer];
+  double wB[kPsPer] = {};
+  if (Mi > 0) {
+    load4(Rr, 0, kA, -1);
+    if (kPolicy == kNoPFS) load4(Sr, 0, cB, 0);
+    if (kStaged) load4(Fr, 0, fB, 0);
+    gather(kA, sB);
+    load4(Rr, kPsChunk, kA, -1);
+    if (kPolicy == kNoPFS) load4(Sr, kPsChunk, cA, 0);
+    if (kStaged) load4(Fr, kPsChunk, fA, 0);
+    if (kStaged) {
+      mark_near(0, fB);
+      __syncthreads();
+    }
+  }
+  const int i0 = kPsPer * tid;
+  for (int64_t f0 = 0; f0 < Mi; f0 += kPsChunk) {
+    const int n = Mi - f0 < kPsChunk ? int(Mi - f0) : kPsChunk;
+    // per-read terms, in the definition's expressions
+    double u[kPsPer], fetch[kPsPer], rd[kPsPer], W[kPsPer];
+    int cls[kPsPer];
+    int32_t g[kPsPer];  // the position waited for, from the chunk's start (negative: before it)
+#pragma unroll
+    for (int j = 0; j < kPsPer; ++j) {
+      const double s = double(sB[j]);
+      cls[j] = ps_class(kPolicy, cB[j], rt.J);
+      if (rt.rcp) {
+        u[j] = div_rcp(s, rt.c, rt.rc);
+        fetch[j] = kIo ? div_rcp(s, thr[cls[j]], rthr[cls[j]]) : 0.0;
+        rd[j] = kIo ? fetch[j] + div_rcp(s, rt.wthr, rt.rwthr) : 0.0;
+      } else {
+        u[j] = s / rt.c;
+        fetch[j] = kIo ? s / thr[cls[j]] : 0.0;
+        rd[j] = kIo ? fetch[j] + s / rt.wthr : 0.0;
+      }
+      W[j] = 0.0;
+      g[j] = -1;
+      if (kStaged) {
+        const int64_t gp = i0 + j < n ? look(f0 + i0 + j, fB[j]) : -1;
+        g[j] = int32_t(gp - f0);
+        const double near = ring[gp & (kRing - 1)];
+        const double tg = gp >= f0 - kRing ? near : wB[j];
+        W[j] = gp >= 0 && gp < f0 ? rt.p0 * tg : 0.0;
+      }
+    }
+    // the next chunk's sizes and far waits, the one after's ids
+    gather(kA, sB);
+    if (kStaged) far_waits(f0 + kPsChunk, fA, wB);
+#pragma unroll
+    for (int j = 0; j < kPsPer; ++j) {
+      cB[j] = cA[j];
+      fB[j] = fA[j];
+    }
+    load4(Rr, f0 + 2 * kPsChunk, kA, -1);
+    if (kPolicy == kNoPFS) load4(Sr, f0 + 2 * kPsChunk, cA, 0);
+    if (kStaged) load4(Fr, f0 + 2 * kPsChunk, fA, 0);
+    const uint32_t near = kStaged ? uint32_t(__builtin_amdgcn_readfirstlane(int(s_near[(f0 / kPsChunk) & 1]))) : 0u;
+    if (kStaged) mark_near(f0 + kPsChunk, fB);
+
+    // fetch-time sums: this chunk's units by class
+    if (kIo) {
+      uint64_t sum = 0;
+      uint32_t bad = 0;
+#pragma unroll
+      for (int j = 0; j < kPsPer; ++j) {
+        bool stop = false;
+        uint64_t d = units(fetch[j], binade_of(double_of(io_x[cls[j]])), &stop);
+        if (i0 + j >= n) d = 0;
+        bad |= stop && i0 + j < n ? 1u << j : 0u;
+        if (kPolicy == kNoPFS)
+          atomicAdd(reinterpret_cast<unsigned long long*>(&io_acc[cls[j] * kPsCopies + (lane & (kPsCopies - 1))]),
+                    (unsigned long long)(d));
+        else
+          sum += d;
+      }
+      if (bad) {
+#pragma unroll
+        for (int j = 0; j < kPsPer; ++j)
+          if ((bad >> j) & 1u) io_bad[cls[j]] = 1;
+      }
+      if (kPolicy != kNoPFS) {
+        sum = wave_inclusive_scan64(sum);
+        if (lane == 63) io_acc[wave] = sum;
+      }
+    }
+
+    // the chunk's terms to LDS, for a wave that takes reads of all threads
+    auto stage = [&]() {
+#pragma unroll
+      for (int j = 0; j < kPsPer; ++j) {
+        st_u[i0 + j] = u[j];
+        if (kIo) st_rd[i0 + j] = rd[j];
+        if (kStaged) {
+          st_w[i0 + j] = W[j];
+          st_g[i0 + j] = g[j];
+        }
+      }
+    };
+    // the chunk's reads from pos on by one wave
+    auto wave_chain = [&](int pos) {
+      int p = pos;
+      while (p < n) {
+        auto load = [&](double* uu, double* rr, double* ww, int32_t* gg) {
+          const int x = p + lane < n ? p + lane : n - 1;
+          *uu = st_u[x];
+          *rr = kIo ? st_rd[x] : 0.0;
+          *ww = kStaged ? st_w[x] : 0.0;
+          *gg = kStaged ? st_g[x] : -1;
+          if (kStaged && *gg >= 0 && *gg < p) *ww = rt.p0 * ring[(f0 + *gg) & (kRing - 1)];
+        };
+        double ul, rl, wl;
+        int32_t gl;
+        load(&ul, &rl, &wl, &gl);
+        const bool on = p + lane < n;
+        const Binade wq = binade_of(Q), wy = binade_of(Y);
+        bool stop = false, unknown = false;
+        Link l{0, 0}, ex;
+        uint64_t qx = 0, c = 0;
+        if (kStaged) {
+          unknown = gl >= p;
+          stop = unknown || bits_of(wl) >= wq.top;
+          const uint64_t d = units(rl, wq, &stop);
+          if (on) l = Link{d, bits_of(wl) + d};
+          l = wave_link_scan<true>(l);
+          qx = apply<true>(bits_of(Q), l);
+          stop = stop || qx >= wq.top;
+          c = bits_of(rt.rcp ? div_rcp(double_of(qx), rt.p0, rt.rp0) : double_of(qx) / rt.p0);
+          stop = stop || c >= wy.top;
+        }
+        uint64_t d = units(ul, wy, &stop);
+        if (kPolicy == kNaive) {
+          c = units(rl, wy, &stop);
+          d += c;
+        }
+        l = on ? Link{d, kStaged ? c + d : 0ull} : Link{0, 0};
+        l = wave_link_scan<kStaged>(l);
+        ex = wave_link_shift<kStaged>(l);
+        const uint64_t ye = apply<kStaged>(bits_of(Y), ex), yx = apply<kStaged>(bits_of(Y), l);
+        const uint64_t tb = kPolicy == kNaive ? ye + c : max_u64(ye, c);
+        stop = stop || yx >= wy.top;
+        const uint64_t m = __ballot(on && stop);
+        int step = m ? __builtin_ctzll(m) : (n - p < 64 ? n - p : 64);
+        if (lane < step) ring[(f0 + p + lane) & (kRing - 1)] = double_of(tb);
+        if (step > 0) {
+          if (kStaged) Q = double_of(read_lane64(qx, step - 1));
+          Y = double_of(read_lane64(yx, step - 1));
+        }
+        auto one = [&](double uk, double rk, double wk, int64_t f, bool rcp) -> double {
+          double tf = Y;
+          if (kPolicy == kNaive) tf = Y + rk;
+          if (kStaged) {
+            Q = __builtin_fmax(Q, wk);
+            Q = Q + rk;
+            tf = rcp ? div_rcp(Q, rt.p0, rt.rp0) : Q / rt.p0;
+            if (f > 0) tf = __builtin_fmax(tf, Y);
+          }
+          Y = tf + uk;
+          return tf;
+        };
+        if (m && ((__ballot(unknown) >> step) & 1u) == 0u) {
+          const double tf = one(rl_d(ul, step), rl_d(rl, step), rl_d(wl, step), f0 + p + step, false);
+          if (lane == 0) ring[(f0 + p + step) & (kRing - 1)] = tf;
+          ++step;
+        }
+        p += step;
+        if (step >= kPsMinWave || p >= n) continue;
+        // read by read
+        load(&ul, &rl, &wl, &gl);
+        const int nb = n - p < 64 ? n - p : 64;
+        double tl = 0.0;  // lane q: t of read p + q
+        auto steps = [&](bool rcp) {
           for (int q = 0; q < nb; ++q) {
-            Q = __builtin_fmax(Q, rl_d(W, q));
-            Q = Q + rl_d(rd, q);
-            Qb = lane == q ? Q : Qb;
+            const int gq = __builtin_amdgcn_readlane(gl, q) - p;
+            const double wk = kStaged && gq >= 0 ? rt.p0 * rl_d(tl, gq & 63) : rl_d(wl, q);
+            const double tf = one(rl_d(ul, q), rl_d(rl, q), wk, f0 + p + q, rcp);
+            tl = lane == q ? tf : tl;
+          }
+        };
+        // 64 reads of at most 2^363 seconds each (a 63-bit size over a rate
+        // above 2^-300) keep Q and its quotients inside the range of div_rcp
+        const bool plain = binade_of(Q).base != 0 && binade_of(Y).base != 0 && Q < 0x1p400 && Y < 0x1p400 &&
+                           __ballot(lane < nb && !(ul >= 0.0 && rl >= 0.0 && wl >= 0.0 && wl < 0x1p700)) == 0;
+        if (kStaged && rt.rcp && plain) steps(true);
+        else steps(false);
+        if (lane < nb) ring[(f0 + p + lane) & (kRing - 1)] = tl;
+        p += nb;
+      }
+      if (lane == 0) {
+        s_Q = Q;
+        s_Y = Y;
+      }
+    };
+
+    int pos = 0, shorts = 0;
+    bool first = true, io_slow = false;
+    if (near & 2u) {
+      // short windows: one wave from the start, another for the sums
+      stage();
+#pragma unroll
+      for (int j = 0; j < kPsPer; ++j) {
+        st_f[i0 + j] = fetch[j];
+        if (kPolicy == kNoPFS) st_c[i0 + j] = uint8_t(cls[j]);
+      }
+      __syncthreads();
+      if (tid == 0) s_near[(f0 / kPsChunk) & 1] = 0;
+      if (wave == 0) wave_chain(0);
+      if (wave == kPsWaves - 1 && io_check()) io_ordered(n);
+      __syncthreads();
+      Q = s_Q;
+      Y = s_Y;
+      pos = n;
+    }
+    while (pos < n) {
+      const Binade bq = binade_of(Q), by = binade_of(Y);
+      uint32_t stops = 0;  // bit j: the scan does not hold at this thread's read j
+      bool act[kPsPer];
+      Link lq[kPsPer];     // of each read
+      uint64_t qv[kPsPer]; // bits of Q after it
+      uint64_t q_in = 0, q_end = 0;
+#pragma unroll
+      for (int j = 0; j < kPsPer; ++j) act[j] = i0 + j >= pos && i0 + j < n;
+      if (kStaged) {
+        Link l{0, 0};
+#pragma unroll
+        for (int j = 0; j < kPsPer; ++j) {
+          bool stop = false;
+          if (near) {  // uniform
+            const double tg = ring[(f0 + g[j]) & (kRing - 1)];
+            if (g[j] >= 0 && g[j] < pos) W[j] = rt.p0 * tg;
+            stop = g[j] >= pos;
+          }
+          stop = stop || bits_of(W[j]) >= bq.top;
+          const uint64_t d = units(rd[j], bq, &stop);
+          lq[j] = act[j] ? Link{d, bits_of(W[j]) + d} : Link{0, 0};
+          if (act[j] && stop) stops |= 1u << j;
+          l = then<true>(l, lq[j]);
+        }
+        const Link inc = wave_link_scan<true>(l);
+        const Link ex = wave_link_shift<true>(inc);
+        if (lane == 63) s_q[wave] = inc;
+        __syncthreads();
+        uint64_t before;
+        block_links<true, kPsWaves>(s_q, wave, lane, bits_of(Q), &before, &q_end);
+        q_in = apply<true>(before, ex);
+        uint64_t x = q_in;
+#pragma unroll
+        for (int j = 0; j < kPsPer; ++j) {
+          x = apply<true>(x, lq[j]);
+          if (act[j] && x >= bq.top) stops |= 1u << j;
+          qv[j] = x;
+        }
+      } else if (kIo && first) {
+        __syncthreads();  // the units by class are in
+      }
+      if (kIo && first && wave == kPsWaves - 1) {
+        if (kStaged && lane == 0) s_near[(f0 / kPsChunk) & 1] = 0;  // read by every wave before the barrier
+        const bool slow = io_check();
+        if (slow && lane == 0) s_io_slow = 1;
+      }
+      // y: the same over u, with Q / p0 as the floor
+      Link ly[kPsPer];
+      uint64_t cb[kPsPer];   // bits of Q / p0 (Naive: the units of read(f))
+      uint64_t y_in = 0, y_end = 0;
+      {
+        Link l{0, 0};
+#pragma unroll
+        for (int j = 0; j < kPsPer; ++j) {
+          bool stop = false;
+          cb[j] = 0;
+          uint64_t d = units(u[j], by, &stop);
+          if (kStaged) {
+            cb[j] = bits_of(rt.rcp ? div_rcp(double_of(qv[j]), rt.p0, rt.rp0) : double_of(qv[j]) / rt.p0);
+            stop = stop || cb[j] >= by.top;
+          }
+          if (kPolicy == kNaive) {
+            cb[j] = units(rd[j], by, &stop);
+            d += cb[j];
+          }
+          ly[j] = act[j] ? Link{d, kStaged ? cb[j] + d : 0ull} : Link{0, 0};
+          if (act[j] && stop) stops |= 1u << j;
+          l = then<kStaged>(l, ly[j]);
+        }
+        const Link inc = wave_link_scan<kStaged>(l);
+        const Link ex = wave_link_shift<kStaged>(inc);
+        if (lane == 63) s_y[wave] = inc;
+        __syncthreads();
+        uint64_t before;
+        block_links<kStaged, kPsWaves>(s_y, wave, lane, bits_of(Y), &before, &y_end);
+        y_in = apply<kStaged>(before, ex);
+      }
+      {
+        uint64_t x = y_in;
+#pragma unroll
+        for (int j = 0; j < kPsPer; ++j) {
+          const uint64_t tb = kPolicy == kNaive ? x + cb[j] : max_u64(x, cb[j]);
+          x = apply<kStaged>(x, ly[j]);
+          if (act[j]) {
+            if (x >= by.top) stops |= 1u << j;
+            // values past the first stop are rewritten before anything reads them
+            ring[(f0 + i0 + j) & (kRing - 1)] = double_of(tb);
           }
         }
-        sl.Qb[lane] = Qb;
-        if (lane == 0) sl.near = 0;
-        q_done = true;
       }
-    }
-    if (wave == 1 && k >= 1) {
-      const int64_t fb = f0 - 64;
-      const PsSlot& sl = slot[(k - 1) & 1];
-      const int nb = Mi - fb < 64 ? int(Mi - fb) : 64;
-      const double u = sl.u[lane];
-      double tb = -1.0;
-      if (sl.near) {
-        // read by read, from the Q after the batch before
-        double Qs = s_Qend;
-        const double rd_l = sl.rd[lane], W_l = sl.W[lane];
-        const int32_t gq_l = sl.gq[lane];
-        const uint64_t inb = sl.inb;
-        for (int q = 0; q < nb; ++q) {
-          const double Wq = ((inb >> q) & 1) ? rt.p0 * rl_d(tb, __builtin_amdgcn_readlane(gq_l, q) & 63)
-                                             : rl_d(W_l, q);
-          Qs = __builtin_fmax(Qs, Wq);
-          Qs = Qs + rl_d(rd_l, q);
-          double tf = Qs / rt.p0;
-          if (fb + q > 0) tf = __builtin_fmax(tf, tprev + uprev);
-          tb = lane == q ? tf : tb;
-          tprev = tf;
-          uprev = rl_d(u, q);
-        }
-        if (lane == 0) s_Qend = Qs;
-      } else {
-        const double av = sl.Qb[lane] / rt.p0;
-        auto tstep = [&](int q) {
-          double tf = rl_d(av, q);
-          if (fb + q > 0) tf = __builtin_fmax(tf, tprev + uprev);
-          tb = lane == q ? tf : tb;
-          tprev = tf;
-          uprev = rl_d(u, q);
-        };
-        if (nb == 64) {
+      // the first read at which the scan does not hold
+      const uint32_t mine = stops ? uint32_t(i0 + __builtin_ctz(stops)) : ~0u;
+      const uint64_t has = __ballot(stops != 0u);
+      if (lane == 0) s_stop[wave] = ~0u;
+      if (has && lane == __builtin_ctzll(has)) s_stop[wave] = mine;
+      __syncthreads();
+      if (first) io_slow = s_io_slow != 0u;
+      first = false;
+      const uint32_t sv = s_stop[lane & (kPsWaves - 1)];
+      const uint64_t sm = __ballot(sv != ~0u) & ((1u << kPsWaves) - 1u);
+      if (sm == 0) {
+        if (kStaged) Q = double_of(q_end);
+        Y = double_of(y_end);
+        break;
+      }
+      const int k = __builtin_amdgcn_readlane(int(sv), __builtin_ctzll(sm));
+      if (k / kPsPer == tid) {
+        // this thread's read k: the values before it hold; step it with
+        // ordinary operations unless its wait is still unknown
+        uint64_t qx = q_in, yx = y_in;
+        double uk = 0, rk = 0, wk = 0;
+        int32_t gk = -1;
 #pragma unroll
-          for (int q = 0; q < 64; ++q) tstep(q);
-        } else {
-          for (int q = 0; q < nb; ++q) tstep(q);
+        for (int j = 0; j < kPsPer; ++j) {
+          if (j < (k % kPsPer)) {
+            if (kStaged) qx = apply<true>(qx, lq[j]);
+            yx = apply<kStaged>(yx, ly[j]);
+          }
+          if (j == (k % kPsPer)) {
+            uk = u[j];
+            rk = rd[j];
+            wk = W[j];
+            gk = g[j];
+          }
         }
+        double q = double_of(qx), y = double_of(yx);
+        const bool known = gk < pos;
+        if (known) {
+          double tf = y;
+          if (kPolicy == kNaive) tf = y + rk;
+          if (kStaged) {
+            q = __builtin_fmax(q, wk);
+            q = q + rk;
+            tf = q / rt.p0;
+            if (f0 + k > 0) tf = __builtin_fmax(tf, y);
+          }
+          ring[(f0 + k) & (kRing - 1)] = tf;
+          y = tf + uk;
+        }
+        s_Q = q;
+        s_Y = y;
+        s_pos = known ? k + 1 : k;
       }
-      const int64_t f = fb + lane;
-      if (f < Mi) {
-        tr[f] = tb;
-        ring[f & (kPsRing - 1)] = tb;
-      }
+      __syncthreads();
+      Q = s_Q;
+      Y = s_Y;
+      const int np = s_pos;
+      if (np - pos < kPsMinStep) ++shorts;
+      pos = np;
+      if (shorts < 2 || pos >= n) continue;
+
+      // one wave goes on from here
+      stage();
+      __syncthreads();
+      if (wave == 0) wave_chain(pos);
+      __syncthreads();
+      Q = s_Q;
+      Y = s_Y;
+      break;
     }
-    if (wave == 2 && k < nbat) {
-      const int32_t kk = kN, code = cN;
-      if (f0 + 64 < Mi) io_ids(f0 + 64, kN, cN);
-      const double s = double((kk >= 0 && kk < r.F) ? sizes[kk] : int64_t(0));
-      const int cls = ps_class(kPolicy, code, rt.J);
-      const double fetch = s / thr[cls];
-      const int nb = Mi - f0 < 64 ? int(Mi - f0) : 64;
-      if (kPolicy != kNoPFS && nb == 64) {
-        double a = rl_d(a0, 0);
+
+    if (kIo && io_slow) {
 #pragma unroll
-        for (int q = 0; q < 64; ++q) a = a + rl_d(fetch, q);
-        a0 = lane == 0 ? a : a0;
-      } else {
-        // lane c carries class c's sum (and class 64 + c's): every step adds
-        // the read's fetch time in its class's lane and 0.0 in the others,
-        // so each class's sum takes its reads in stream order (the sums are
-        // never -0, so adding +0.0 leaves them bit for bit)
-        auto cstep = [&](int q) {
-          const int cq = __builtin_amdgcn_readlane(cls, q);
-          const double fq = rl_d(fetch, q);
-          a0 = a0 + (cq == lane ? fq : 0.0);
-          if (K > 64) a1 = a1 + (cq == lane + 64 ? fq : 0.0);
-        };
-        if (nb == 64) {
+      for (int j = 0; j < kPsPer; ++j) {
+        st_f[i0 + j] = fetch[j];
+        if (kPolicy == kNoPFS) st_c[i0 + j] = uint8_t(cls[j]);
+      }
+      __syncthreads();
+      if (wave == 0) io_ordered(n);
+      if (tid == 0) s_io_slow = 0;
+      __syncthreads();
+    }
+
+    // the chunk's t, from the ring
+    double tv[kPsPer];
 #pragma unroll
-          for (int q = 0; q < 64; ++q) cstep(q);
-        } else {
-          for (int q = 0; q < nb; ++q) cstep(q);
-        }
-      }
+    for (int j = 0; j < kPsPer; ++j) tv[j] = ring[(f0 + i0 + j) & (kRing - 1)];
+    if (i0 + kPsPer <= n) {
+      __builtin_memcpy(tr + f0 + i0, tv, sizeof(tv));
+    } else {
+#pragma unroll
+      for (int j = 0; j < kPsPer; ++j)
+        if (i0 + j < n) tr[f0 + i0 + j] = tv[j];
     }
-    __syncthreads();  // A: batch k - 1's t, and a stepped batch's Q, are in
-    // ------------------------------------------------------------ phase 2
-    if (wave == 0 && k < nbat && !q_done) {
-      PsSlot& sl = slot[k & 1];
-      if (k > 0 && slot[(k - 1) & 1].near != 0) Q = s_Qend;
-      const bool inb = g >= f0;
-      const double tg = (g >= 0 && !inb) ? (g >= f0 - kPsRing ? ring[g & (kPsRing - 1)] : far) : 0.0;
-      const double W = (g >= 0 && !inb) ? rt.p0 * tg : 0.0;
-      const uint64_t inb_mask = __ballot(inb);
-      if (inb_mask == 0) {
-        const int nb = Mi - f0 < 64 ? int(Mi - f0) : 64;
-        double Qb = 0.0;
-        for (int q = 0; q < nb; ++q) {
-          Q = __builtin_fmax(Q, rl_d(W, q));
-          Q = Q + rl_d(rd, q);
-          Qb = lane == q ? Q : Qb;
-        }
-        sl.Qb[lane] = Qb;
-        if (lane == 0) sl.near = 0;
-      } else {
-        sl.W[lane] = W;
-        sl.gq[lane] = int32_t(g - f0);
-        if (lane == 0) {
-          sl.inb = inb_mask;
-          sl.near = 1;
-        }
-      }
-    }
-    __syncthreads();  // B: batch k's Q values or its stepping data are in
   }
-  if (wave == 1) {
-    for (int64_t f = Mi + lane; f < M; f += 64) tr[f] = -1.0;
-    if (lane == 0) finish[i] = Mi > 0 ? tprev + uprev : 0.0;
-  }
-  if (wave == 2) {
-    double* ior = io + i * K;
-    if (lane < K) ior[lane] = a0;
-    if (64 + lane < K) ior[64 + lane] = a1;
-  }
+  for (int64_t f = Mi + tid; f < M; f += kPsThreads) tr[f] = -1.0;
+  for (int c = tid; c < K; c += kPsThreads)
+    io[i * K + c] = kIo && c < kCls ? double_of(io_x[c]) : 0.0;
+  if (tid == 0) finish[i] = Mi > 0 ? Y : 0.0;
 }
 
 int policy_impl(const nopfs_job* job, const int32_t* R, const int64_t* sizes, const int16_t* src,
@@ -524,21 +824,36 @@ int policy_impl(const nopfs_job* job, const int32_t* R, const int64_t* sizes, co
   rt.wthr = model->beta < wb ? model->beta : wb;
   rt.c = model->c;
   rt.p0 = model->p0;
-  const dim3 grid(uint32_t(s.N));
-  switch (policy) {
-    case kPerfect:
-      return launch("ps_sim_perfect", ps_sim<kPerfect>, grid, dim3(ps_threads<kPerfect>()), 0, st, r, R, sizes, src, fill, rt, t,
-                    finish, io);
-    case kNaive:
-      return launch("ps_sim_naive", ps_sim<kNaive>, grid, dim3(ps_threads<kNaive>()), 0, st, r, R, sizes, src, fill, rt, t,
-                    finish, io);
-    case kStaging:
-      return launch("ps_sim_staging", ps_staged<kStaging>, grid, dim3(192), 0, st, r, R, sizes, src, fill,
-                    rt, t, finish, io);
-    default:
-      return launch("ps_sim_nopfs", ps_staged<kNoPFS>, grid, dim3(192), 0, st, r, R, sizes, src, fill,
-                    rt, t, finish, io);
-  }
+  bool ok = true;
+  auto reciprocal = [&](double b) {
+    const double y = 1.0 / b;
+    ok = ok && rcp_ok(b, y);
+    return y;
+  };
+  for (int c = 0; c < kPsClasses; ++c) rt.rthr[c] = reciprocal(rt.thr[c]);
+  rt.rwthr = reciprocal(rt.wthr);
+  rt.rc = reciprocal(rt.c);
+  rt.rp0 = reciprocal(rt.p0);
+  rt.rcp = ok;
+  auto run = [&](auto threads) {
+    constexpr int kT = decltype(threads)::value;
+    const dim3 grid(uint32_t(s.N)), block(kT);
+    switch (policy) {
+      case kPerfect:
+        return launch("ps_sim_perfect", ps_sim<kPerfect, kT>, grid, block, 0, st, r, R, sizes, src,
+                      fill, rt, t, finish, io);
+      case kNaive:
+        return launch("ps_sim_naive", ps_sim<kNaive, kT>, grid, block, 0, st, r, R, sizes, src,
+                      fill, rt, t, finish, io);
+      case kStaging:
+        return launch("ps_sim_staging", ps_sim<kStaging, kT>, grid, block, 0, st, r, R, sizes, src,
+                      fill, rt, t, finish, io);
+      default:
+        return launch("ps_sim_nopfs", ps_sim<kNoPFS, kT>, grid, block, 0, st, r, R, sizes, src,
+                      fill, rt, t, finish, io);
+    }
+  };
+  return s.N <= kPsUnits ? run(std::integral_constant<int, kPsFew>()) : run(std::integral_constant<int, kPsMany>());
 }
 
 }  // namespace
