@@ -5,12 +5,13 @@
 //
 // The rows are folded into one segment (E = 1 in SegParams, the epochs
 // counted by emul), so run c of a row is the window's reads inside span c
-// of 2^14 positions. A tile is (window of 2^14 samples, group of kGRows
-// rows); tiles are window-major, so the groups of one window and the tiles
-// of neighbouring windows (whose runs adjoin in memory) run together on one
-// XCD. Consecutive threads take consecutive reads of the tile's runs, so
-// loads and stores go out in run-long pieces (19 reads on average at
-// ImageNet-22k) instead of one store per lane into 64 different runs.
+// of 2^14 positions. A tile is (window, group of consecutive runs: rows in
+// order, a row's spans in order); tiles are window-major, so the groups of
+// one window and the tiles of neighbouring windows (whose runs adjoin in
+// memory) run together on one XCD. Consecutive threads take consecutive reads
+// of the tile's runs, so loads and stores go out in run-long pieces (19 reads
+// on average at ImageNet-22k) instead of one store per lane into 64
+// different runs.
 #pragma once
 
 #include "partition.hpp"
@@ -20,8 +21,14 @@ namespace nopfs {
 constexpr int kGatherWs = 14;                 // window: 2^14 samples of 8-byte values
 constexpr int kGatherWin = 1 << kGatherWs;    // 8-byte values held in LDS (128 KB)
 constexpr int kGThreads = 1024;
-constexpr int kGRows = 32;                    // rows per tile
+// A tile holds about kGReads reads: its window's values (128 KB of LDS) are
+// loaded once for all of them. With fewer than kGTiles such tiles (four per
+// compute unit, one at a time on each) they are made smaller, down to kGMin
+// reads.
+constexpr double kGReads = 163840, kGMin = 4096;
+constexpr int64_t kGTiles = 1024;
 constexpr int kGRuns = 1024;                  // runs per pass of a tile
+constexpr uint32_t kGLongRun = 96;            // mean reads per run from which waves take whole runs
 static_assert(kGRuns % kGThreads == 0, "gather tile shape");
 
 // kChunk: reads per inner pass (the run index map); each thread requests
@@ -35,12 +42,25 @@ struct GatherLds {
   };
   uint32_t pref[kGRuns + 1];  // reads before each run of the pass
   int32_t rpos[kGRuns];       // span start + run start, in the row
-  uint8_t rrow[kGRuns];       // row - first row of the tile
+  uint32_t rrow[kGRuns];      // row - first row of the tile
   uint16_t run_of[kChunk];    // run of each read of the inner pass
   uint32_t tmp[65];
 };
 
-inline uint32_t gather_ngroups(int64_t N) { return uint32_t(ceil_div(N, kGRows)); }
+// Runs per tile of a gather pass, and from it the groups per window. At
+// ImageNet-22k a window has 4,300 runs of 38 reads per 32 rows, one tile; at
+// ImageNet-1k on 16 workers 7,040 runs of 420 reads, which took one tile per
+// window (40 workgroups on 256 compute units: 3.3 ms for the staging
+// schedule's pass, 0.20 ms now).
+inline int64_t gather_runs(const SegParams& p) {
+  const int64_t runs = p.N * p.nsc;
+  const double run = run_mean(p);  // reads
+  int64_t per = int64_t(kGReads / run) + 1;
+  const int64_t split = ceil_div(runs * p.nbk, kGTiles);  // gives kGTiles tiles
+  const int64_t least = int64_t(kGMin / run) + 1;
+  if (per > split) per = split > least ? split : least;
+  return per < runs ? per : runs;
+}
 
 // Window width (log2) of a gather pass: kGatherWs, or wider by the test
 // hook's doublings (at most 4: the packed partition entries hold 18 bits of
@@ -59,14 +79,15 @@ inline int gather_ws() {
 template <typename V, int kChunk, typename Value, typename Emit>
 __device__ __forceinline__ void gather_tile(const SegParams& p, const uint32_t* __restrict__ Pk,
                                             const uint16_t* __restrict__ OT, uint32_t tile,
-                                            uint32_t ngroups, GatherLds<kChunk>& L, Value value,
-                                            Emit emit) {
+                                            uint32_t ngroups, int64_t per, GatherLds<kChunk>& L,
+                                            Value value, Emit emit) {
   constexpr int kPer = kChunk / kGThreads;
   const uint32_t kb = tile / ngroups;
-  const int64_t i0 = int64_t(tile - kb * ngroups) * kGRows;
-  const int64_t rows = p.N - i0 < kGRows ? p.N - i0 : kGRows;
   const int64_t nch = p.nsc;
-  const int64_t nruns = rows * nch;  // < 2^31
+  const int64_t run0 = int64_t(tile - kb * ngroups) * per;  // the tile's first run
+  const int64_t i0 = run0 / nch;                            // its row
+  const int64_t c0 = run0 - i0 * nch;                       // and span
+  const int64_t nruns = p.N * nch - run0 < per ? p.N * nch - run0 : per;  // c0 + nruns < 2^32
   const int64_t k0 = int64_t(kb) << p.ws;
   const int64_t kend = k0 + (int64_t(1) << p.ws) < p.F ? k0 + (int64_t(1) << p.ws) : p.F;
   constexpr int kWin = int(kGatherWin * sizeof(uint64_t) / sizeof(V));  // values per pass
@@ -96,14 +117,14 @@ __device__ __forceinline__ void gather_tile(const SegParams& p, const uint32_t* 
       for (int m = 0; m < kGRuns / kGThreads; ++m) {
         const uint32_t r = threadIdx.x * (kGRuns / kGThreads) + m;
         // loads for runs past nr read run r0's bounds and are dropped
-        const uint32_t rr = uint32_t(r0) + (r < nr ? r : 0u);
+        const uint32_t rr = uint32_t(c0 + r0) + (r < nr ? r : 0u);
         const uint32_t il = rr / uint32_t(nch), c = rr - il * uint32_t(nch);
         const uint16_t* o = OT + ((i0 + il) * (p.nbk + 1) + kb) * nch + c;
         const uint32_t a = o[0], b = o[nch];
         len[m] = r < nr ? b - a : 0u;
         if (r < nr) {
           L.rpos[r] = int32_t((int64_t(c) << kScShift) + a);
-          L.rrow[r] = uint8_t(il);
+          L.rrow[r] = il;
         }
         sum += len[m];
       }
@@ -116,6 +137,37 @@ __device__ __forceinline__ void gather_tile(const SegParams& p, const uint32_t* 
       }
       if (threadIdx.x == 0) L.pref[nr] = total;
       __syncthreads();
+      if (total >= kGLongRun * nr) {  // uniform
+        // long runs: kG waves to a run (one where there are as many runs as
+        // waves), each lane's loads of a step together. Through the map
+        // below, a run's owner would write the whole run's entries alone.
+        constexpr uint32_t kWaves = kGThreads / 64, kStep = 64 * kPer;
+        const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        uint32_t wpr = 1;
+        while (2 * wpr * nr <= kWaves) wpr *= 2;
+        for (uint32_t r = wave / wpr; r < nr; r += kWaves / wpr) {
+          const uint32_t rl = L.pref[r + 1] - L.pref[r];
+          const int64_t rrow = i0 + L.rrow[r];
+          const int64_t rbase = rrow * p.M_max + L.rpos[r];
+          for (uint32_t q0 = (wave & (wpr - 1)) * kStep; q0 < rl; q0 += wpr * kStep) {
+            int64_t pos[kPer], row[kPer];
+            uint32_t x[kPer];
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+              const uint32_t q = q0 + u * 64 + lane;
+              row[u] = rrow;
+              pos[u] = q < rl ? rbase + q : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) x[u] = Pk[pos[u] >= 0 ? pos[u] : rbase];  // unconditional
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) x[u] = pos[u] >= 0 ? (x[u] >> kScShift) - xoff : 0xFFFFFFFFu;
+            emit(pos, row, x, w0, wl);
+          }
+        }
+        __syncthreads();  // the run table is rewritten
+        continue;
+      }
       for (uint32_t x0 = 0; x0 < total; x0 += kChunk) {
         const uint32_t xl = total - x0 < kChunk ? total - x0 : kChunk;
         // run index of every read of the inner pass, written by the runs' owners

@@ -20,7 +20,7 @@
 //                 packed above the sample's size. A worker's own copy may be
 //                 that class: a remote copy of class j is never faster than
 //                 the local copy of j, so counting it never changes a choice.
-//   fm_gather  -- per (16K-sample window, group of 32 workers) of the
+//   fm_gather  -- per (16K-sample window, group of runs) of the
 //                 partition of R (rows folded into one segment of E * L_i
 //                 reads, cut into spans of 2^14): each read's source from
 //                 its own tier and the sample's best remote class; size and
@@ -150,14 +150,14 @@ constexpr int kFmGPer = kFmGChunk / kGThreads;
 __global__ void __launch_bounds__(kGThreads)
 fm_gather(SegParams p, const uint32_t* __restrict__ Pk, const uint16_t* __restrict__ OT,
           const int8_t* __restrict__ tier, const uint64_t* __restrict__ szb, Rates rt,
-          uint64_t* __restrict__ zP, uint32_t ngroups, uint32_t ntiles) {
+          uint64_t* __restrict__ zP, uint32_t ngroups, int64_t per, uint32_t ntiles) {
   __shared__ GatherLds<kFmGChunk> L;
   __shared__ SharedRates sr;
   const uint32_t tile = xcd_logical(blockIdx.x, gridDim.x);
   if (tile >= ntiles) return;
   load_rates(rt, sr);  // visible after the tile's first barrier
   gather_tile<uint64_t, kFmGChunk>(
-      p, Pk, OT, tile, ngroups, L, [&](int64_t k) { return szb[k]; },
+      p, Pk, OT, tile, ngroups, per, L, [&](int64_t k) { return szb[k]; },
       [&](const int64_t (&pos)[kFmGPer], const int64_t (&row)[kFmGPer], const uint32_t (&x)[kFmGPer],
           int64_t w0, uint32_t wl) {
         // each read's own tier: a byte of its row's window slice (cached),
@@ -488,8 +488,9 @@ int model_impl(const nopfs_job* job, const int32_t* R, const int8_t* tier, const
   p.emul = int32_t(s.E);
   p.E = 1;
   p.nsc = int32_t(nch);
-  const uint32_t ngroups = gather_ngroups(s.N);
+  const int64_t per = gather_runs(p);
   const int64_t nblk = s.N * int64_t(nch);
+  const uint32_t ngroups = uint32_t(ceil_div(nblk, per));
   const int64_t ntiles = int64_t(p.nbk) * ngroups;
   if (nblk >= (int64_t(1) << 31) || ntiles >= (int64_t(1) << 31))
     return fail(NOPFS_ERANGE, "job too large for one launch");
@@ -507,7 +508,7 @@ int model_impl(const nopfs_job* job, const int32_t* R, const int8_t* tier, const
     return rc;
   if ((rc = launch("fm_gather", fm_gather, dim3(xcd_padded(uint32_t(ntiles))), dim3(kGThreads), 0,
                    st, p, (const uint32_t*)Pk, (const uint16_t*)OT, tier, (const uint64_t*)szb, rt,
-                   zP, ngroups, uint32_t(ntiles))))
+                   zP, ngroups, per, uint32_t(ntiles))))
     return rc;
   if ((rc = launch("fm_sum", fm_sum, dim3(uint32_t(nblk)), dim3(kFmThreads), 0, st, p,
                    (const uint32_t*)Pk, (const uint64_t*)zP, rt, nch, sums)))

@@ -35,6 +35,15 @@ __device__ __forceinline__ int64_t seg_len(const SegParams& p, int64_t i) {
   return int64_t(p.emul) * (p.drop_last ? p.L : epoch_len(p.F, p.N, p.B, 0, i));
 }
 
+// Mean reads of a run for a uniform shuffle.
+inline double run_mean(const SegParams& p) {
+  const double seg = double(p.emul) * double(p.L);
+  const double span = seg < kSC ? seg : double(kSC);
+  const double win = p.F < (int64_t(1) << p.ws) ? double(p.F) : double(int64_t(1) << p.ws);
+  const double m = span * win / double(p.F);
+  return m > 1e-6 ? m : 1e-6;
+}
+
 __device__ __forceinline__ int64_t orow(const SegParams& p, int64_t i, int64_t e, int64_t sc) {
   return ((i * p.E + e) * p.nsc + sc) * int64_t(p.nbk + 1);
 }
@@ -144,33 +153,48 @@ __device__ __forceinline__ int64_t sub_len(int64_t Li, int64_t sc) {
   return len < 0 ? 0 : (len > kSC ? kSC : len);
 }
 
-// Calls fn(fb, q, v) for every read of runs r = r0, r0 + stride, ... of
-// window kb of worker i: fb is the stream position of the run's sub-chunk,
-// q the read's index in the sub-chunk's partitioned entries (its
-// partitioned position is fb + q) and v the packed read.
-template <typename Fn>
+// Lanes that share a run in walk_runs: about an eighth of a run's reads
+// (kRunBatch loads each), more where there are fewer runs than that many
+// groups of threads.
+inline int run_lanes(const SegParams& p, int threads) {
+  const double m = run_mean(p);
+  const int64_t runs = int64_t(p.E) * p.nsc;
+  int l = 1;
+  while (l < 64 && (l * kRunBatch < m || (2 * l * runs <= threads && l < m))) l *= 2;
+  return l;
+}
+
+// Calls fn(fb, q, v) for every read of window kb of worker i: fb is the
+// stream position of the run's sub-chunk, q the read's index in the
+// sub-chunk's partitioned entries (its partitioned position is fb + q) and v
+// the packed read. `lanes` consecutive threads of the workgroup share a run
+// (a power of two, at most 64).
+template <int NT, typename Fn>
 __device__ __forceinline__ void walk_runs(const SegParams& p, int64_t i, uint32_t kb,
                                           const uint32_t* __restrict__ Pk,
-                                          const uint16_t* __restrict__ OT, int64_t r0,
-                                          int64_t stride, Fn fn) {
+                                          const uint16_t* __restrict__ OT, uint32_t lanes, Fn fn) {
   const int64_t Li = seg_len(p, i);
   const int64_t runs = int64_t(p.E) * p.nsc;
   const uint16_t* oa = OT + (i * (p.nbk + 1) + kb) * runs;  // run starts in window kb
   const uint16_t* ob = oa + runs;                            // run ends
   const uint32_t* prow = Pk + i * p.M_max;
   const uint32_t nsc = uint32_t(p.nsc);
-  for (int64_t r = r0; r < runs; r += stride) {
+  const uint32_t sub = threadIdx.x & (lanes - 1);
+  for (int64_t r = threadIdx.x / lanes; r < runs; r += NT / lanes) {
     const uint32_t ra = oa[r], rb = ob[r];
     const uint32_t e = uint32_t(r) / nsc, sc = uint32_t(r) - e * nsc;
     const int64_t fb = int64_t(e) * Li + int64_t(sc) * kSC;
     const uint32_t* src = prow + fb;
-    for (uint32_t q = ra; q < rb; q += kRunBatch) {
+    for (uint32_t q = ra + sub; q < rb; q += kRunBatch * lanes) {
       uint32_t v[kRunBatch];
 #pragma unroll
-      for (int u = 0; u < kRunBatch; ++u) v[u] = q + u < rb ? src[q + u] : 0u;
+      for (int u = 0; u < kRunBatch; ++u) {
+        const uint32_t y = q + u * lanes;
+        v[u] = src[y < rb ? y : ra];  // unconditional
+      }
 #pragma unroll
       for (int u = 0; u < kRunBatch; ++u)
-        if (q + u < rb) fn(fb, q + u, v[u]);
+        if (q + u * lanes < rb) fn(fb, q + u * lanes, v[u]);
     }
   }
 }
