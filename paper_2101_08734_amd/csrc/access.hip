@@ -26,6 +26,7 @@
 // (walk the epochs backwards, remembering the last position per sample).
 #include <limits.h>
 
+#include <algorithm>
 #include <new>
 
 #include "partition.hpp"
@@ -160,7 +161,10 @@ constexpr int kRunLoads = NOPFS_RUN_LOADS;
 #ifndef NOPFS_STATS_SPLIT
 #define NOPFS_STATS_SPLIT 4
 #endif
-constexpr int kStatsSplit = NOPFS_STATS_SPLIT;  // most threads per run
+// Most threads per run, or a quarter of a run's reads where that is more
+// (a job of few, long runs: with four threads on each of its five runs of
+// 2,000 reads a tile of 10,000 samples took 74 us).
+constexpr int kStatsSplit = NOPFS_STATS_SPLIT;
 static_assert(kStatsSplit >= 1, "at least one thread per run");
 static_assert(kRunLoads % 4 == 0, "whole 16-byte loads");
 
@@ -192,7 +196,7 @@ __global__ void __launch_bounds__(kStatsThreads) __attribute__((amdgpu_waves_per
 stats_tile(SegParams p, const uint32_t* __restrict__ Pk, const uint16_t* __restrict__ OT,
            uint8_t* __restrict__ count, int32_t* __restrict__ first, uint32_t ntiles,
            uint32_t* __restrict__ cent, int32_t* __restrict__ cbase, uint32_t* __restrict__ cnum,
-           const ClassTable* __restrict__ classes) {
+           const ClassTable* __restrict__ classes, uint32_t split) {
   extern __shared__ uint32_t sm[];
   uint32_t* cw = sm;                                             // byte counters
   // first reads, kept as unsigned values from an initial 0xFFFFFFFF: the
@@ -241,11 +245,11 @@ stats_tile(SegParams p, const uint32_t* __restrict__ Pk, const uint16_t* __restr
     // the compiler from holding them in registers across the pass)
     uint32_t tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
-    // With fewer runs than threads, ns = min(threads / runs, kStatsSplit)
+    // With fewer runs than threads, ns = min(threads / runs, split)
     // threads share a run, taking turns at groups of kRunLoads reads (a run
     // of up to ns * kRunLoads reads then needs one round of loads).
     uint32_t ns = runs < kStatsThreads ? uint32_t(kStatsThreads / runs) : 1u;  // uniform
-    ns = ns < uint32_t(kStatsSplit) ? ns : uint32_t(kStatsSplit);
+    ns = ns < split ? ns : split;
     const uint32_t r_first = tid / ns;
     const uint32_t r_step = kStatsThreads / ns;
     const uint32_t q_off = (tid - r_first * ns) * kRunLoads;
@@ -705,18 +709,19 @@ int launch_stats(const SegParams& p, const uint32_t* Pk, const uint16_t* OT, uin
   const bool vec = (reinterpret_cast<uintptr_t>(count) & 3) == 0 &&
                    (reinterpret_cast<uintptr_t>(first) & 15) == 0;
   const dim3 grid(xcd_padded(ntiles)), block(kStatsThreads);
+  const uint32_t split = std::max(uint32_t(kStatsSplit), uint32_t(run_mean(p) / 4));
   uint32_t* ent = cc ? cc->ent : nullptr;
   int32_t* base = cc ? cc->base : nullptr;
   uint32_t* num = cc ? cc->num : nullptr;
   if (cc)
     return vec ? launch("stats_tile", stats_tile<true, true>, grid, block, smem, st, p, Pk, OT, count,
-                        first, ntiles, ent, base, num, classes)
+                        first, ntiles, ent, base, num, classes, split)
                : launch("stats_tile", stats_tile<false, true>, grid, block, smem, st, p, Pk, OT,
-                        count, first, ntiles, ent, base, num, classes);
+                        count, first, ntiles, ent, base, num, classes, split);
   return vec ? launch("stats_tile", stats_tile<true, false>, grid, block, smem, st, p, Pk, OT, count,
-                      first, ntiles, ent, base, num, classes)
+                      first, ntiles, ent, base, num, classes, split)
              : launch("stats_tile", stats_tile<false, false>, grid, block, smem, st, p, Pk, OT, count,
-                      first, ntiles, ent, base, num, classes);
+                      first, ntiles, ent, base, num, classes, split);
 }
 
 // Window width of the next-use pass: the widest whose expected reads stay
