@@ -20,6 +20,9 @@
 //                    read of its bucket (the "segmented sort plus shift").
 //                    The results go to a scratch array laid out like the
 //                    partitioned reads.
+//   next_walk     -- the same for jobs of few workers, over the counting
+//                    pass's windows: the window's epochs from the last to the
+//                    first, with each sample's last met position in LDS.
 //   next_unpartition -- per sub-chunk, scatter those results back to stream
 //                    order through LDS and write next[N][M_max].
 // A next_tile window whose reads do not fit in LDS takes an epoch-serial path
@@ -650,6 +653,140 @@ next_tile(SegParams p, const uint32_t* __restrict__ Pk, const uint16_t* __restri
   }
 }
 
+// Few workers, so that an epoch has hundreds of reads per window: one
+// workgroup per (worker, window) walks the window's runs from the last epoch
+// to the first and keeps, in LDS, the position at which each sample was last
+// met: the next use of the read that meets it now. The reads of one epoch are
+// distinct samples, so all runs of an epoch are taken between two barriers
+// (which wait for LDS work only). G = kWalkThreads / lanes runs of an epoch go
+// in one step, `lanes` threads each (a power of two), two reads per thread; the
+// bounds of a batch of steps are requested two batches ahead, its reads one.
+constexpr int kWalkWin = 8192;
+constexpr int kWalkThreads = 512;
+constexpr int kWalkSteps = 2;   // steps per batch (1: 0.47, 3: 0.67, 4: 0.46, 8: 0.69 ms)
+
+__global__ void __launch_bounds__(kWalkThreads)
+next_walk(SegParams p, const uint32_t* __restrict__ Pk, const uint16_t* __restrict__ OT,
+          int32_t* __restrict__ nextP, uint32_t ntiles, int32_t lanes_log) {
+  __shared__ int32_t last[kWalkWin];
+  const uint32_t tile = xcd_logical(blockIdx.x, gridDim.x);
+  if (tile >= ntiles) return;
+  const int64_t i = tile / p.nbk;
+  const uint32_t kb = tile - uint32_t(i) * p.nbk;
+  const uint32_t* prow = Pk + i * p.M_max;
+  int32_t* nrow = nextP + i * p.M_max;
+  const int64_t runs = int64_t(p.E) * p.nsc;
+  const uint16_t* oa = OT + (i * (p.nbk + 1) + kb) * runs;  // run starts in window kb
+  const uint16_t* ob = oa + runs;                            // run ends
+  const int32_t Li = int32_t(seg_len(p, i));                 // M_max < 2^31
+  const int32_t tid = threadIdx.x;
+  const uint32_t lanes = 1u << lanes_log;
+  const uint32_t sub = uint32_t(tid) & (lanes - 1);
+  const int32_t grp = tid >> lanes_log, G = kWalkThreads >> lanes_log;
+
+  // a step: the lanes' run, as [a, b) in the sub-chunk at stream position fb
+  struct Steps {
+    uint32_t a[kWalkSteps], b[kWalkSteps];
+    int32_t fb[kWalkSteps];
+  };
+  int32_t e = p.E - 1, sc = 0;  // the next step to request
+  auto bounds = [&](Steps& s) {
+#pragma unroll
+    for (int u = 0; u < kWalkSteps; ++u) {
+      const int32_t c = sc + grp;
+      const bool in = e >= 0 && c < p.nsc;
+      const int64_t r = in ? int64_t(e) * p.nsc + c : 0;
+      const uint32_t a = oa[r], b = ob[r];  // unconditional
+      s.a[u] = a;
+      s.b[u] = in ? b : a;
+      s.fb[u] = in ? e * Li + c * kSC : 0;
+      sc += G;
+      if (sc >= p.nsc) {
+        sc = 0;
+        --e;
+      }
+    }
+  };
+  auto read_at = [&](uint32_t q, uint32_t b, int32_t fb) {
+    return prow[q < b ? fb + int32_t(q) : 0];  // unconditional
+  };
+  auto request = [&](const Steps& s, uint32_t (&v)[kWalkSteps], uint32_t (&w)[kWalkSteps]) {
+#pragma unroll
+    for (int u = 0; u < kWalkSteps; ++u) v[u] = read_at(s.a[u] + sub, s.b[u], s.fb[u]);
+#pragma unroll
+    for (int u = 0; u < kWalkSteps; ++u) {
+      w[u] = 0;
+      if (__any(s.a[u] + sub + lanes < s.b[u])) w[u] = read_at(s.a[u] + sub + lanes, s.b[u], s.fb[u]);
+    }
+  };
+  auto meet = [&](uint32_t q, uint32_t b, int32_t fb, uint32_t v) {
+    if (q < b) {
+      const uint32_t x = v >> kScShift;
+      const int32_t nx = last[x];
+      last[x] = fb + int32_t(v & kJMask);
+      nrow[fb + int32_t(q)] = nx;
+    }
+  };
+
+  Steps s0, s1, s2;
+  uint32_t v0[kWalkSteps], w0[kWalkSteps], v1[kWalkSteps], w1[kWalkSteps];
+  bounds(s0);
+  bounds(s1);
+  for (int x = tid * 4; x < kWalkWin; x += 4 * kWalkThreads)
+    *reinterpret_cast<int4*>(&last[x]) = make_int4(-1, -1, -1, -1);
+  request(s0, v0, w0);
+  auto lds_barrier = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+  const int32_t spe = (p.nsc + G - 1) / G;  // steps per epoch
+  const int32_t steps = p.E * spe;
+  int32_t left = 0;                         // steps left of this epoch
+  for (int32_t st = 0; st < steps; st += kWalkSteps) {
+    bounds(s2);
+    request(s1, v1, w1);
+#pragma unroll
+    for (int u = 0; u < kWalkSteps; ++u) {
+      if (left == 0) {  // uniform: the table holds the later epochs' reads
+        lds_barrier();
+        left = spe;
+      }
+      --left;
+      const uint32_t q = s0.a[u] + sub, b = s0.b[u];
+      const int32_t fb = s0.fb[u];
+      meet(q, b, fb, v0[u]);
+      meet(q + lanes, b, fb, w0[u]);
+      for (uint32_t y = q + 2 * lanes; __any(y < b); y += 8 * lanes) {  // longer runs
+        uint32_t z[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) z[k] = read_at(y + k * lanes, b, fb);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) meet(y + k * lanes, b, fb, z[k]);
+      }
+    }
+    s0 = s1;
+    s1 = s2;
+#pragma unroll
+    for (int u = 0; u < kWalkSteps; ++u) {
+      v0[u] = v1[u];
+      w0[u] = w1[u];
+    }
+  }
+}
+
+// Runs of an epoch per step: as many as there are, while two reads per
+// thread hold a mean run and a quarter. At ImageNet-1k on 16 workers (90 epochs,
+// 512 reads per epoch and window) the pass takes 0.42 ms, 0.93 by chains (over
+// windows of 256 samples).
+int walk_lanes_log(const SegParams& p) {
+  const double m = run_mean(p);
+  int lanes_log = 9;
+  while (lanes_log > 0 && (kWalkThreads >> lanes_log) < p.nsc && 2.0 * (1 << (lanes_log - 1)) >= 1.25 * m)
+    --lanes_log;
+  return lanes_log;
+}
+
 constexpr int kUnpartThreads = 1024;
 
 __global__ void __launch_bounds__(kUnpartThreads)
@@ -724,7 +861,27 @@ int launch_stats(const SegParams& p, const uint32_t* Pk, const uint16_t* OT, uin
                       first, ntiles, ent, base, num, classes, split);
 }
 
-// Window width of the next-use pass: the widest whose expected reads stay
+// The walk takes jobs whose epochs have at least `reads` reads per window of the
+// counting pass: fewer leave most of its threads idle between two barriers.
+// Measured (next-use call, chains -> walk, ms): ImageNet-1k, 90 epochs, on 16
+// workers (512 reads) 1.53 -> 0.90, 32 (256) 1.24 -> 0.88, 64 (128) 1.16 -> 1.22;
+// 14.2M samples, 5 epochs, on 16 workers 0.69 -> 0.64, on 32 0.66 -> 0.74. In the
+// fused call the walk also saves the chains' own partition wherever their
+// windows are not the counting pass's (plan, ImageNet-1k on 64 workers: 3.41 ->
+// 3.26 ms, on 128 3.40 -> 3.92). With fewer tiles than compute units a tile's chain of
+// epochs is all there is to wait for (2,000 samples, 200 epochs, 8 workers:
+// 0.05 -> 0.11 ms), so those jobs walk up to 64 epochs only.
+constexpr int kWalkWs = NOPFS_STATS_WS;
+static_assert((1 << kWalkWs) <= kWalkWin, "a window's samples fit the walk's table");
+constexpr double kWalkReads = 384, kWalkReadsFused = 128;
+
+bool walks(const SegParams& p, double reads) {
+  const double win = p.F < (int64_t(1) << p.ws) ? double(p.F) : double(int64_t(1) << p.ws);
+  return p.ws == kWalkWs && double(p.L) * win / double(p.F) >= reads &&
+         (p.N * p.nbk >= 256 || p.E <= 64);
+}
+
+// Window width of the next-use pass by chains: the widest whose expected reads stay
 // within three quarters of the fast-path capacity (windows that overflow it
 // take the epoch-serial path).
 int next_ws(const Shape& s) {
@@ -735,22 +892,27 @@ int next_ws(const Shape& s) {
   return ws;
 }
 
-SegParams next_params(const Shape& s) {
+SegParams chain_params(const Shape& s) {
   SegParams p = seg_params(s, next_ws(s));
   if (debug_value(2) > 0 && debug_value(2) < kNextEnt) p.ent_cap = int32_t(debug_value(2));
   return p;
 }
 
 // nextP: scratch laid out like the partitioned reads (N * M_max int32).
-int launch_next(const SegParams& p, const uint32_t* Pk, const uint16_t* OT, int32_t* nextP,
+int launch_next(const SegParams& p, bool walk, const uint32_t* Pk, const uint16_t* OT, int32_t* nextP,
                 int32_t* next, hipStream_t st) {
   int rc;
   const uint32_t ntiles = uint32_t(p.N * p.nbk);
   size_t smem = sizeof(NextSmem);
   if (smem < size_t(kSlowWin) * 4) smem = size_t(kSlowWin) * 4;
-  if ((rc = launch("next_tile", next_tile, dim3(xcd_padded(ntiles)), dim3(kNextThreads), smem, st, p,
-                   Pk, OT, nextP, ntiles)))
+  if (walk) {
+    if ((rc = launch("next_walk", next_walk, dim3(xcd_padded(ntiles)), dim3(kWalkThreads), 0, st, p, Pk, OT,
+                     nextP, ntiles, int32_t(walk_lanes_log(p)))))
+      return rc;
+  } else if ((rc = launch("next_tile", next_tile, dim3(xcd_padded(ntiles)), dim3(kNextThreads), smem,
+                          st, p, Pk, OT, nextP, ntiles))) {
     return rc;
+  }
   const int64_t wgs = p.N * p.E * p.nsc;
   if ((rc = launch("next_unpartition", next_unpartition, dim3(uint32_t(wgs)), dim3(kUnpartThreads), 0,
                    st, p, Pk, (const int32_t*)nextP, next)))
@@ -833,21 +995,25 @@ int next_impl(const nopfs_job* job, const int32_t* R, int32_t* next, hipStream_t
   if (rc) return rc;
   if (s.M_max == 0) return NOPFS_OK;  // R and next have no elements and may be NULL
   if (!R || !next) return fail(NOPFS_EINVAL, "R and next must be non-NULL");
-  const SegParams p = next_params(s);
+  SegParams p = seg_params(s, kWalkWs);
+  const bool walk = walks(p, kWalkReads);
+  if (!walk) p = chain_params(s);
   Scratch scr(st);
   uint32_t* Pk;
   uint16_t* OT;
   int32_t* nextP;
   if ((rc = run_partition(p, R, scr, &Pk, &OT, st))) return rc;
   if ((rc = scr.alloc_n(&nextP, size_t(s.N * s.M_max)))) return rc;
-  return launch_next(p, Pk, OT, nextP, next, st);
+  return launch_next(p, walk, Pk, OT, nextP, next, st);
 }
 
 int access_fused(const Shape& s, const int32_t* R, const ClassTable* classes, uint8_t* count,
                  int32_t* first, int32_t* next, CompactCells* cc, Scratch& keep, hipStream_t st) {
   int rc;
   const SegParams ps = seg_params(s, NOPFS_STATS_WS);
-  const SegParams pn = next_params(s);
+  SegParams pn = chain_params(s);
+  const bool walk = walks(ps, pn.ws == ps.ws ? kWalkReads : kWalkReadsFused);
+  if (walk) pn = ps;
   uint32_t *Pk, *Pn;
   uint16_t *OT, *OTn;
   int32_t* nextP;
@@ -864,7 +1030,7 @@ int access_fused(const Shape& s, const int32_t* R, const ClassTable* classes, ui
   if (pn.ws != ps.ws)
     if ((rc = run_partition(pn, R, keep, &Pn, &OTn, st))) return rc;
   if ((rc = keep.alloc_n(&nextP, size_t(s.N * s.M_max)))) return rc;
-  return launch_next(pn, Pn, OTn, nextP, next, st);
+  return launch_next(pn, walk, Pn, OTn, nextP, next, st);
 }
 
 }  // namespace nopfs
