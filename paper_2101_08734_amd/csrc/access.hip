@@ -164,7 +164,8 @@ constexpr int kRunLoads = NOPFS_RUN_LOADS;
 #ifndef NOPFS_STATS_SPLIT
 #define NOPFS_STATS_SPLIT 4
 #endif
-// Most threads per run, or a quarter of a run's reads where that is more
+// Threads per run where there are fewer runs than threads: at most this many,
+// or as many as it takes to load a mean run at once where that is more
 // (a job of few, long runs: with four threads on each of its five runs of
 // 2,000 reads a tile of 10,000 samples took 74 us).
 constexpr int kStatsSplit = NOPFS_STATS_SPLIT;
@@ -199,7 +200,7 @@ __global__ void __launch_bounds__(kStatsThreads) __attribute__((amdgpu_waves_per
 stats_tile(SegParams p, const uint32_t* __restrict__ Pk, const uint16_t* __restrict__ OT,
            uint8_t* __restrict__ count, int32_t* __restrict__ first, uint32_t ntiles,
            uint32_t* __restrict__ cent, int32_t* __restrict__ cbase, uint32_t* __restrict__ cnum,
-           const ClassTable* __restrict__ classes, uint32_t split) {
+           const ClassTable* __restrict__ classes, uint32_t ns) {
   extern __shared__ uint32_t sm[];
   uint32_t* cw = sm;                                             // byte counters
   // first reads, kept as unsigned values from an initial 0xFFFFFFFF: the
@@ -248,11 +249,8 @@ stats_tile(SegParams p, const uint32_t* __restrict__ Pk, const uint16_t* __restr
     // the compiler from holding them in registers across the pass)
     uint32_t tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
-    // With fewer runs than threads, ns = min(threads / runs, split)
-    // threads share a run, taking turns at groups of kRunLoads reads (a run
-    // of up to ns * kRunLoads reads then needs one round of loads).
-    uint32_t ns = runs < kStatsThreads ? uint32_t(kStatsThreads / runs) : 1u;  // uniform
-    ns = ns < split ? ns : split;
+    // ns threads share a run, taking turns at groups of kRunLoads reads (a
+    // run of up to ns * kRunLoads reads needs one round of loads).
     const uint32_t r_first = tid / ns;
     const uint32_t r_step = kStatsThreads / ns;
     const uint32_t q_off = (tid - r_first * ns) * kRunLoads;
@@ -846,19 +844,21 @@ int launch_stats(const SegParams& p, const uint32_t* Pk, const uint16_t* OT, uin
   const bool vec = (reinterpret_cast<uintptr_t>(count) & 3) == 0 &&
                    (reinterpret_cast<uintptr_t>(first) & 15) == 0;
   const dim3 grid(xcd_padded(ntiles)), block(kStatsThreads);
-  const uint32_t split = std::max(uint32_t(kStatsSplit), uint32_t(run_mean(p) / 4));
+  const int64_t runs = int64_t(p.E) * p.nsc;
+  const int64_t split = std::max(int64_t(kStatsSplit), int64_t(run_mean(p) / kRunLoads));
+  const uint32_t ns = uint32_t(std::max(int64_t(1), std::min(kStatsThreads / runs, split)));
   uint32_t* ent = cc ? cc->ent : nullptr;
   int32_t* base = cc ? cc->base : nullptr;
   uint32_t* num = cc ? cc->num : nullptr;
   if (cc)
     return vec ? launch("stats_tile", stats_tile<true, true>, grid, block, smem, st, p, Pk, OT, count,
-                        first, ntiles, ent, base, num, classes, split)
+                        first, ntiles, ent, base, num, classes, ns)
                : launch("stats_tile", stats_tile<false, true>, grid, block, smem, st, p, Pk, OT,
-                        count, first, ntiles, ent, base, num, classes, split);
+                        count, first, ntiles, ent, base, num, classes, ns);
   return vec ? launch("stats_tile", stats_tile<true, false>, grid, block, smem, st, p, Pk, OT, count,
-                      first, ntiles, ent, base, num, classes, split)
+                      first, ntiles, ent, base, num, classes, ns)
              : launch("stats_tile", stats_tile<false, false>, grid, block, smem, st, p, Pk, OT, count,
-                      first, ntiles, ent, base, num, classes, split);
+                      first, ntiles, ent, base, num, classes, ns);
 }
 
 // The walk takes jobs whose epochs have at least `reads` reads per window of the
