@@ -52,9 +52,8 @@ STAGES = {
     "streams": ("stream_count", "stream_offsets", "stream_scan", "stream_scatter", "stream_split",
                 "stream_sort", "stream_pad"),
     "stats": ("seg_partition", "offsets_transpose", "stats_tile", "fill_stats_empty"),
-    "next": ("next_tile", "next_unpartition", "pad_rows"),
-    "plan": ("plan_classes", "plan_binsum", "plan_hist", "plan_cut", "plan_btier", "plan_write",
-             "plan_resolve", "plan_exact", "fill_u64", "fill_i32"),
+    "next": ("next_walk", "next_tile", "next_unpartition", "pad_rows"),
+    "plan": ("plan_init", "plan_hist", "plan_cut", "plan_write", "plan_resolve"),
 }
 
 

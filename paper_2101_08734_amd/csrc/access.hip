@@ -1007,6 +1007,8 @@ int next_impl(const nopfs_job* job, const int32_t* R, int32_t* next, hipStream_t
   return launch_next(p, walk, Pk, OT, nextP, next, st);
 }
 
+int counting_ws(const Shape& s) { return seg_params(s, NOPFS_STATS_WS).ws; }
+
 int access_fused(const Shape& s, const int32_t* R, const ClassTable* classes, uint8_t* count,
                  int32_t* first, int32_t* next, CompactCells* cc, Scratch& keep, hipStream_t st) {
   int rc;

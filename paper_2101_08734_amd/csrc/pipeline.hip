@@ -39,7 +39,7 @@ int plan_job_impl(const nopfs_job* job, const int64_t* sizes, const int64_t* cap
     }
   } free_plan{cp};
   const ClassTable* classes = nullptr;
-  if ((rc = compact_plan_prepare(s, caps, J, keep, st, &cp, &classes))) return rc;
+  if ((rc = compact_plan_prepare(s, sizes, caps, J, counting_ws(s), keep, st, &cp, &classes))) return rc;
   CompactCells cc;
   if ((rc = access_fused(s, R, classes, count, first, next, &cc, keep, st))) return rc;
   return compact_plan_run(cp, cc, count, first, sizes, tier, used, st);

@@ -51,17 +51,18 @@ struct CompactCells {
 // nopfs_access_stats and nopfs_reuse_next); the counting pass also fills *cc,
 // binning the read cells with `classes`. Scratch that must outlive the call
 // (the list) is taken from `keep`. Requires M_max > 0.
+int counting_ws(const Shape& s);  // log2 of the counting pass's windows
 int access_fused(const Shape& s, const int32_t* R, const ClassTable* classes, uint8_t* count,
                  int32_t* first, int32_t* next, CompactCells* cc, Scratch& keep, hipStream_t st);
 
 // Tier plan (the stage of nopfs_tier_plan) from the compact list, in two
 // steps: prepare() checks the arguments, allocates from `keep` and fills the
-// class table the counting pass bins with; run() does the rest. count and
+// class table the counting pass (over windows of 2^ws samples) bins with; run() does the rest. count and
 // first are the dense tables of the same call (first read for candidate
 // cells, both for a worker whose candidate list overflows).
 struct CompactPlan;
-int compact_plan_prepare(const Shape& s, const int64_t* caps, int32_t J, Scratch& keep,
-                         hipStream_t st, CompactPlan** out, const ClassTable** classes);
+int compact_plan_prepare(const Shape& s, const int64_t* sizes, const int64_t* caps, int32_t J, int ws,
+                         Scratch& keep, hipStream_t st, CompactPlan** out, const ClassTable** classes);
 int compact_plan_run(CompactPlan* cp, const CompactCells& cc, const uint8_t* count,
                      const int32_t* first, const int64_t* sizes, int8_t* tier, int64_t* used,
                      hipStream_t st);

@@ -8,7 +8,8 @@
 // that no longer fits ("first misfit"), so the plan is fixed by J cut points
 // along the ranking. They are found without sorting the N*F cells:
 //
-//   plan_binsum  -- bytes of every run of 256 consecutive ids.
+//   plan_init    -- bytes of every run of 256 consecutive ids; the histogram
+//                   and the counters zeroed.
 //   plan_hist    -- weighted histogram of sizes over rank-ordered bins of the
 //                   key, LDS-privatised per (worker, slice of 2^19 samples)
 //                   and flushed once per slice. Bins of class count>=1 split
@@ -27,14 +28,16 @@
 //   plan_write   -- every cell's tier from its bin; cells in a candidate bin
 //                   get a placeholder and are appended to a per-worker list.
 //   plan_resolve -- per worker: the candidates sorted by key in LDS and the
-//                   greedy fill replayed over them exactly; writes their
-//                   tiers and the bytes used per tier.
-//   plan_exact   -- per worker whose candidate list overflowed: an exact
-//                   weighted radix select over the full row for every cut,
-//                   then a full rewrite of the row (slow, rarely taken).
+//                   greedy fill found over them exactly (running bytes, one
+//                   search per tier); writes their tiers and the bytes used
+//                   per tier. A worker whose candidate list overflowed takes
+//                   an exact weighted radix select over its full row for
+//                   every cut instead, then a full rewrite of the row (slow,
+//                   rarely taken).
 #include <limits.h>
 #include <math.h>
 
+#include <algorithm>
 #include <new>
 #include <vector>
 
@@ -44,7 +47,9 @@ namespace nopfs {
 namespace {
 
 constexpr int kThreads = 512;
-constexpr int64_t kSliceCells = int64_t(1) << 19;  // samples per (worker, slice) tile
+constexpr int64_t kSliceCells = int64_t(1) << 19;  // most samples per (worker, slice) tile
+constexpr int64_t kSliceMin = int64_t(1) << 13;    // fewest, and how many tiles call for fewer:
+constexpr int64_t kSliceTiles = 512;               // two per compute unit
 constexpr int kClass0Shift = 8;           // 256 ids per class-0 bin
 constexpr int kSliceBins0 = int(kSliceCells >> kClass0Shift);
 constexpr uint32_t kBins1Budget = 4096;   // bins for classes count >= 1
@@ -62,35 +67,36 @@ constexpr bool kHistSizesAhead = NOPFS_HIST_SIZES_AHEAD != 0;
 
 typedef long long I64x2 __attribute__((ext_vector_type(2)));
 
+constexpr int8_t kCandMark = 127;  // per-bin tier table: a bin that may hold a cut
+
 struct PlanArgs {
   int64_t F, N, M_max;
   int32_t E, J;
   uint32_t nbin1, nb0, nbin;
   uint32_t btp;  // row pitch of the per-bin tier table (nbin rounded up to 16)
   int32_t cmax;
+  int64_t slice;       // samples per (worker, slice) tile of the histogram and dense passes
   uint16_t nbc[256];   // bins of class c (1 <= c <= E)
   int64_t caps[128];
 };
 
+// One class per thread (at least 256 threads), from class 255 down: a class's
+// first bin is the sum of the higher classes' bins.
 __device__ void build_class_table(const PlanArgs& a, ClassTable& t) {
-  if (threadIdx.x == 0) {
-    uint32_t b = 0;
-    for (int c = a.E; c >= 1; --c) {
-      const float scale = float(a.nbc[c]) / float(a.M_max > 0 ? a.M_max : 1);
-      t.e[c] = make_float2(scale, __uint_as_float((b << 16) | (a.nbc[c] - 1u)));
-      b += a.nbc[c];
-    }
-    t.e[0] = make_float2(0.f, __uint_as_float(b << 16));
+  __shared__ uint32_t tmp[65];
+  const int c = 255 - int(threadIdx.x);
+  const uint32_t v = c >= 1 && c <= a.E ? a.nbc[c] : 0u;
+  uint32_t total;
+  const uint32_t b = block_exclusive_scan<false>(v, tmp, &total);
+  if (c >= 0) {
     // counts above E break the precondition; they bin like class E
-    for (int c = a.E + 1; c < 256; ++c) t.e[c] = t.e[a.E];
+    const int d = c > a.E ? a.E : c;
+    const float scale = float(a.nbc[d]) / float(a.M_max > 0 ? a.M_max : 1);
+    t.e[c] = c == 0 ? make_float2(0.f, __uint_as_float(total << 16))
+                    : make_float2(scale, __uint_as_float((b << 16) | (a.nbc[d] - 1u)));
   }
   __syncthreads();
 }
-
-// The same table computed once into global memory (the fused call's
-// counting pass bins the read cells with it).
-__global__ void plan_classes(PlanArgs a, ClassTable* g) { build_class_table(a, *g); }
-
 
 // Rank-ordered bin of a cell; identical in every kernel that uses it.
 __device__ __forceinline__ uint32_t bin_of(const PlanArgs& a, const ClassTable& t, uint32_t c,
@@ -105,27 +111,33 @@ __device__ __forceinline__ uint64_t rank_key(const PlanArgs& a, uint32_t c, int3
   return hi | (c ? uint64_t(uint32_t(f)) : uint64_t(k));
 }
 
-__global__ void fill_u64(uint64_t* p, int64_t n) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  for (; i < n; i += stride) p[i] = 0;
-}
-
-__global__ void fill_i32(int32_t* p, int64_t n) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  for (; i < n; i += stride) p[i] = 0;
-}
-
-// -- histogram -----------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-plan_binsum(int64_t F, uint32_t nb0, const int64_t* __restrict__ sizes, uint64_t* __restrict__ binsum) {
-  const uint32_t b = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (b >= nb0) return;
+// What the passes below start from, in one launch: the histogram and the
+// candidate counters zeroed (the first `zb` blocks), the bytes of every run
+// of 256 consecutive ids (one wave each), and in the last block the class
+// table in memory, with which the fused call's counting pass bins the read
+// cells. (Four launches before: 20 us of a small job's plan.)
+constexpr int kInitThreads = 256;
+__global__ void __launch_bounds__(kInitThreads)
+plan_init(PlanArgs a, int64_t hn, uint32_t zb, uint64_t* __restrict__ H, int32_t* __restrict__ ccount,
+          const int64_t* __restrict__ sizes, uint64_t* __restrict__ binsum, ClassTable* __restrict__ gct) {
+  if (blockIdx.x < zb) {
+    const int64_t stride = int64_t(zb) * kInitThreads;
+    const int64_t t0 = int64_t(blockIdx.x) * kInitThreads + threadIdx.x;
+    for (int64_t t = t0; t < hn; t += stride) H[t] = 0;
+    for (int64_t t = t0; t < a.N; t += stride) ccount[t] = 0;
+    return;
+  }
+  const uint32_t blk = blockIdx.x - zb;
+  const uint32_t b = blk * 4 + (threadIdx.x >> 6);
+  if (blk * 4 >= a.nb0) {
+    build_class_table(a, *gct);
+    return;
+  }
+  if (b >= a.nb0) return;
   const int64_t k0 = int64_t(b) << kClass0Shift;
   uint64_t v = 0;
   for (int x = __lane_id(); x < (1 << kClass0Shift); x += 64)
-    if (k0 + x < F) v += uint64_t(sizes[k0 + x]);
+    if (k0 + x < a.F) v += uint64_t(sizes[k0 + x]);
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
   if (__lane_id() == 0) binsum[b] = v;
@@ -167,8 +179,8 @@ plan_hist(PlanArgs a, const uint8_t* __restrict__ count, const int32_t* __restri
   if (t >= uint32_t(a.N) * nslices) return;
   const int64_t sl = t / a.N, i = t - sl * a.N;
   build_class_table(a, ct);
-  const int64_t ks = sl * kSliceCells;
-  const int64_t ke = ks + kSliceCells < a.F ? ks + kSliceCells : a.F;
+  const int64_t ks = sl * a.slice;
+  const int64_t ke = ks + a.slice < a.F ? ks + a.slice : a.F;
   const uint32_t zb0 = uint32_t(ks >> kClass0Shift);
   const uint32_t nz = uint32_t((ke - ks + (1 << kClass0Shift) - 1) >> kClass0Shift);
   for (uint32_t b = threadIdx.x; b < a.nbin1; b += kThreads) h1[b] = 0;
@@ -277,8 +289,9 @@ plan_hist(PlanArgs a, const uint8_t* __restrict__ count, const int32_t* __restri
 // the ids this worker reads (Z).
 __global__ void __launch_bounds__(1024)
 plan_cut(PlanArgs a, const uint64_t* __restrict__ binsum, const uint64_t* __restrict__ Z,
-         uint64_t* __restrict__ H, int32_t* __restrict__ ranges) {
+         uint64_t* __restrict__ H, int32_t* __restrict__ ranges, int8_t* __restrict__ btier) {
   __shared__ uint64_t tmp[65];
+  __shared__ int32_t rg[256];
   const int64_t i = blockIdx.x;
   uint64_t* Hi = H + i * int64_t(a.nbin + 1);
   const uint64_t* Zi = Z + i * int64_t(a.nb0);
@@ -295,41 +308,58 @@ plan_cut(PlanArgs a, const uint64_t* __restrict__ binsum, const uint64_t* __rest
   }
   if (threadIdx.x == 0) Hi[a.nbin] = carry;
   __syncthreads();
-  if (threadIdx.x != 0) return;
   const uint64_t total = carry;
   const int32_t nbin = int32_t(a.nbin);
-  uint64_t s_lo = 0, s_hi = 0;
-  int32_t* rg = ranges + i * 2 * a.J;
-  for (int j = 0; j < a.J; ++j) {
-    const uint64_t cap = uint64_t(a.caps[j]);
-    const uint64_t t_lo = s_lo + cap < s_lo ? ~0ull : s_lo + cap;
-    const uint64_t t_hi = s_hi + cap < s_hi ? ~0ull : s_hi + cap;
-    if (t_lo >= total) {
-      for (int jj = j; jj < a.J; ++jj) {
-        rg[2 * jj] = nbin;
-        rg[2 * jj + 1] = nbin;
+  auto cuts = [&]() {
+    uint64_t s_lo = 0, s_hi = 0;
+    for (int j = 0; j < a.J; ++j) {
+      const uint64_t cap = uint64_t(a.caps[j]);
+      const uint64_t t_lo = s_lo + cap < s_lo ? ~0ull : s_lo + cap;
+      const uint64_t t_hi = s_hi + cap < s_hi ? ~0ull : s_hi + cap;
+      if (t_lo >= total) {
+        for (int jj = j; jj < a.J; ++jj) {
+          rg[2 * jj] = nbin;
+          rg[2 * jj + 1] = nbin;
+        }
+        return;
       }
-      return;
+      // lo: first bin b with cum_after(b) = Hi[b+1] > t_lo
+      int32_t lo = 1, hi = nbin;  // search x in [1, nbin] for the first Hi[x] > t_lo
+      while (lo < hi) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (Hi[mid] > t_lo) hi = mid; else lo = mid + 1;
+      }
+      const int32_t blo = lo - 1;
+      // hi: last bin b < nbin with cum_before(b) = Hi[b] <= t_hi
+      lo = 0;
+      hi = nbin - 1;
+      while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (Hi[mid] <= t_hi) lo = mid; else hi = mid - 1;
+      }
+      const int32_t bhi = lo;
+      rg[2 * j] = blo;
+      rg[2 * j + 1] = bhi;
+      s_lo = Hi[blo];
+      s_hi = t_hi < total ? t_hi : total;
     }
-    // lo: first bin b with cum_after(b) = Hi[b+1] > t_lo
-    int32_t lo = 1, hi = nbin;  // search x in [1, nbin] for the first Hi[x] > t_lo
-    while (lo < hi) {
-      const int32_t mid = (lo + hi) >> 1;
-      if (Hi[mid] > t_lo) hi = mid; else lo = mid + 1;
+  };
+  if (threadIdx.x == 0) cuts();
+  __syncthreads();
+  if (!btier) {
+    for (int x = threadIdx.x; x < 2 * a.J; x += 1024) ranges[i * 2 * a.J + x] = rg[x];
+    return;
+  }
+  // the tier (or the candidate mark) of every bin
+  for (int32_t b = threadIdx.x; b < nbin; b += 1024) {
+    bool cand = false;
+    int tv = 0;
+    for (int j = 0; j < a.J; ++j) {
+      const int32_t lo = rg[2 * j], hi = rg[2 * j + 1];
+      cand |= b >= lo && b <= hi;
+      tv += hi < b;
     }
-    const int32_t blo = lo - 1;
-    // hi: last bin b < nbin with cum_before(b) = Hi[b] <= t_hi
-    lo = 0;
-    hi = nbin - 1;
-    while (lo < hi) {
-      const int32_t mid = (lo + hi + 1) >> 1;
-      if (Hi[mid] <= t_hi) lo = mid; else hi = mid - 1;
-    }
-    const int32_t bhi = lo;
-    rg[2 * j] = blo;
-    rg[2 * j + 1] = bhi;
-    s_lo = Hi[blo];
-    s_hi = t_hi < total ? t_hi : total;
+    btier[i * a.btp + b] = cand ? kCandMark : (tv >= a.J ? int8_t(-1) : int8_t(tv));
   }
 }
 
@@ -357,8 +387,8 @@ plan_write(PlanArgs a, const uint8_t* __restrict__ count, const int32_t* __restr
   build_class_table(a, ct);
   for (int x = threadIdx.x; x < 2 * a.J; x += kThreads) rg[x] = ranges[i * 2 * a.J + x];
   __syncthreads();
-  const int64_t ks = sl * kSliceCells;
-  const int64_t ke = ks + kSliceCells < a.F ? ks + kSliceCells : a.F;
+  const int64_t ks = sl * a.slice;
+  const int64_t ke = ks + a.slice < a.F ? ks + a.slice : a.F;
   const uint32_t b0_slice = a.nbin1 + uint32_t(ks >> kClass0Shift);
   const uint32_t nb_slice = uint32_t((ke - ks + (1 << kClass0Shift) - 1) >> kClass0Shift);
   for (uint32_t x = threadIdx.x; x < a.nbin1 + nb_slice; x += kThreads) {
@@ -462,128 +492,18 @@ plan_write(PlanArgs a, const uint8_t* __restrict__ count, const int32_t* __restr
   }
 }
 
-// -- exact resolution of the candidates --------------------------------------------------
-struct ResolveSmem {
-  uint64_t key[kCandMax];  // rank keys; after the sort, the bytes of the whole bins before each
-  uint32_t k[kCandMax];
-  uint64_t sz[kCandMax];   // each candidate's size
+// -- exact fallback: weighted radix select over the whole row ------------------------------
+struct ExactSmem {
+  uint64_t hist[256];
+  uint64_t cuts[128];
+  uint64_t prefix, acc, total;
 };
 
-__global__ void __launch_bounds__(kResolveThreads)
-plan_resolve(PlanArgs a, const uint64_t* __restrict__ H, const CandRec* __restrict__ cand,
-             const int32_t* __restrict__ ccount, const int64_t* __restrict__ sizes,
-             int8_t* __restrict__ tier, int64_t* __restrict__ used, int32_t* __restrict__ overflow) {
-  __shared__ ResolveSmem s;
-  const int64_t i = blockIdx.x;
-  const int32_t n = ccount[i];
-  if (threadIdx.x == 0) overflow[i] = n > a.cmax ? 1 : 0;
-  if (n > a.cmax) return;
-  const uint64_t* Hi = H + i * int64_t(a.nbin + 1);
-  const CandRec* ci = cand + i * int64_t(a.cmax);
-  int32_t P2 = 1;
-  while (P2 < n) P2 <<= 1;
-  for (int32_t x = threadIdx.x; x < P2; x += kResolveThreads) {
-    if (x < n) {
-      s.key[x] = ci[x].key;
-      s.k[x] = ci[x].k;
-    } else {
-      s.key[x] = ~0ull;
-      s.k[x] = 0xFFFFFFFFu;
-    }
-  }
-  __syncthreads();
-  // bitonic sort by key (keys are unique)
-  for (int32_t kk = 2; kk <= P2; kk <<= 1) {
-    for (int32_t j = kk >> 1; j > 0; j >>= 1) {
-      for (int32_t x = threadIdx.x; x < P2; x += kResolveThreads) {
-        const int32_t y = x ^ j;
-        if (y > x) {
-          const bool up = (x & kk) == 0;
-          const uint64_t kx = s.key[x], ky = s.key[y];
-          if ((kx > ky) == up) {
-            s.key[x] = ky; s.key[y] = kx;
-            const uint32_t t = s.k[x]; s.k[x] = s.k[y]; s.k[y] = t;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  }
-  // every thread gathers, for its candidates in sorted order, the size and
-  // the bytes of the whole bins between the previous candidate's bin and
-  // this one's (zero within a bin), so the serial fill below reads LDS only
-  constexpr int kPerT = kCandMax / kResolveThreads;
-  static_assert(kCandMax % kResolveThreads == 0, "candidates per thread");
-  const int64_t last_bin = n > 0 ? int64_t(s.key[n - 1] >> 32) : -1;
-  uint64_t gap[kPerT], hb[kPerT], hp[kPerT], sk[kPerT];
-  // loads first, unconditional (clamped to entry 0), so they are in flight together
-#pragma unroll
-  for (int q = 0; q < kPerT; ++q) {
-    const int32_t x = int32_t(threadIdx.x) + q * kResolveThreads;
-    const bool in = x < n;
-    const int64_t b = in ? int64_t(s.key[x] >> 32) : 0;
-    const int64_t pb = in && x > 0 ? int64_t(s.key[x - 1] >> 32) : -1;
-    hb[q] = Hi[b];
-    hp[q] = Hi[pb + 1];
-    sk[q] = uint64_t(sizes[in ? s.k[x] : 0u]);
-  }
-#pragma unroll
-  for (int q = 0; q < kPerT; ++q) {
-    const int32_t x = int32_t(threadIdx.x) + q * kResolveThreads;
-    gap[q] = 0;
-    if (x < n) {
-      const int64_t b = int64_t(s.key[x] >> 32);
-      const int64_t pb = x > 0 ? int64_t(s.key[x - 1] >> 32) : -1;
-      if (b != pb) gap[q] = hb[q] - (pb < 0 ? 0ull : hp[q]);
-      s.sz[x] = sk[q];
-    }
-  }
-  __syncthreads();  // every key is read before any is replaced
-#pragma unroll
-  for (int q = 0; q < kPerT; ++q) {
-    const int32_t x = int32_t(threadIdx.x) + q * kResolveThreads;
-    if (x < n) s.key[x] = gap[q];
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  // replay the greedy fill: definite bins between candidates are added whole
-  int64_t* ui = used + i * a.J;
-  int8_t* trow = tier + i * a.F;
-  int j = 0;
-  uint64_t u = 0;
-  for (int32_t x = 0; x < n; ++x) {
-    u += s.key[x];
-    const uint64_t sz = s.sz[x];
-    while (j < a.J && u + sz > uint64_t(a.caps[j])) {
-      ui[j] = int64_t(u);
-      ++j;
-      u = 0;
-    }
-    if (j < a.J) {
-      trow[s.k[x]] = int8_t(j);
-      u += sz;
-    } else {
-      trow[s.k[x]] = int8_t(-1);
-    }
-  }
-  if (j < a.J) {
-    const uint64_t gap_start = last_bin < 0 ? 0ull : Hi[last_bin + 1];
-    u += Hi[a.nbin] - gap_start;
-    ui[j] = int64_t(u);
-    for (int jj = j + 1; jj < a.J; ++jj) ui[jj] = 0;
-  }
-}
-
-// -- exact fallback: weighted radix select over the whole row ------------------------------
-__global__ void __launch_bounds__(1024)
-plan_exact(PlanArgs a, const uint8_t* __restrict__ count, const int32_t* __restrict__ first,
-           const int64_t* __restrict__ sizes, const int32_t* __restrict__ overflow,
-           int8_t* __restrict__ tier, int64_t* __restrict__ used) {
-  __shared__ uint64_t hist[256];
-  __shared__ uint64_t cuts[128];
-  __shared__ uint64_t sh_prefix, sh_acc, sh_total;
-  const int64_t i = blockIdx.x;
-  if (!overflow[i]) return;
+__device__ void plan_exact(const PlanArgs& a, int64_t i, const uint8_t* __restrict__ count,
+                           const int32_t* __restrict__ first, const int64_t* __restrict__ sizes,
+                           int8_t* __restrict__ tier, int64_t* __restrict__ used, ExactSmem& sh) {
+  uint64_t* hist = sh.hist;
+  uint64_t* cuts = sh.cuts;
   const uint8_t* crow = count + i * a.F;
   const int32_t* frow = first + i * a.F;
   int8_t* trow = tier + i * a.F;
@@ -617,7 +537,7 @@ plan_exact(PlanArgs a, const uint8_t* __restrict__ count, const int32_t* __restr
         if (level == 0) {
           uint64_t t = 0;
           for (int d = 0; d < 256; ++d) t += hist[d];
-          sh_total = t;
+          sh.total = t;
         }
         uint64_t run = acc;
         int d = 0;
@@ -625,14 +545,14 @@ plan_exact(PlanArgs a, const uint8_t* __restrict__ count, const int32_t* __restr
           if (run + hist[d] > target) break;
           run += hist[d];
         }
-        sh_prefix = (prefix << 8) | uint64_t(d < 256 ? d : 255);
-        sh_acc = run;
+        sh.prefix = (prefix << 8) | uint64_t(d < 256 ? d : 255);
+        sh.acc = run;
       }
       __syncthreads();
-      if (level == 0) total = sh_total;
+      if (level == 0) total = sh.total;
       if (total <= target) break;  // everything left fits
-      prefix = sh_prefix;
-      acc = sh_acc;
+      prefix = sh.prefix;
+      acc = sh.acc;
       __syncthreads();
     }
     if (total <= target) {
@@ -660,6 +580,164 @@ plan_exact(PlanArgs a, const uint8_t* __restrict__ count, const int32_t* __restr
   }
 }
 
+// -- exact resolution of the candidates --------------------------------------------------
+struct ResolveSmem {
+  uint64_t key[kCandMax];  // rank keys; after the sort, bytes up to and with each candidate
+  uint32_t k[kCandMax];
+  uint64_t sz[kCandMax];   // each candidate's size
+  int32_t start[130];      // first candidate of each tier, and of what is uncached
+  uint64_t tmp[65];
+};
+
+__global__ void __launch_bounds__(kResolveThreads)
+plan_resolve(PlanArgs a, const uint64_t* __restrict__ H, const CandRec* __restrict__ cand,
+             const int32_t* __restrict__ ccount, const uint8_t* __restrict__ count,
+             const int32_t* __restrict__ first, const int64_t* __restrict__ sizes,
+             int8_t* __restrict__ tier, int64_t* __restrict__ used) {
+  __shared__ union {
+    ResolveSmem r;
+    ExactSmem x;
+  } sh;
+  ResolveSmem& s = sh.r;
+  const int64_t i = blockIdx.x;
+  const int32_t n = ccount[i];
+  if (n > a.cmax) {  // uniform
+    plan_exact(a, i, count, first, sizes, tier, used, sh.x);
+    return;
+  }
+  const uint64_t* Hi = H + i * int64_t(a.nbin + 1);
+  const CandRec* ci = cand + i * int64_t(a.cmax);
+  int32_t P2 = 1;
+  while (P2 < n) P2 <<= 1;
+  for (int32_t x = threadIdx.x; x < P2; x += kResolveThreads) {
+    if (x < n) {
+      s.key[x] = ci[x].key;
+      s.k[x] = ci[x].k;
+    } else {
+      s.key[x] = ~0ull;
+      s.k[x] = 0xFFFFFFFFu;
+    }
+  }
+  __syncthreads();
+  // bitonic sort by key (keys are unique); steps inside 64 consecutive
+  // entries stay inside a wave and need no barrier
+  for (int32_t kk = 2; kk <= P2; kk <<= 1) {
+    for (int32_t j = kk >> 1; j > 0; j >>= 1) {
+      for (int32_t x = threadIdx.x; x < P2; x += kResolveThreads) {
+        const int32_t y = x ^ j;
+        if (y > x) {
+          const bool up = (x & kk) == 0;
+          const uint64_t kx = s.key[x], ky = s.key[y];
+          if ((kx > ky) == up) {
+            s.key[x] = ky; s.key[y] = kx;
+            const uint32_t t = s.k[x]; s.k[x] = s.k[y]; s.k[y] = t;
+          }
+        }
+      }
+      if (j >= 64 || (j == 1 && kk >= 64)) {
+        __syncthreads();
+      } else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+  }
+  __syncthreads();
+  // every thread gathers, for its candidates in sorted order, the size and
+  // the bytes of the whole bins between the previous candidate's bin and
+  // this one's (zero within a bin)
+  constexpr int kPerT = kCandMax / kResolveThreads;
+  static_assert(kCandMax % kResolveThreads == 0, "candidates per thread");
+  const int64_t last_bin = n > 0 ? int64_t(s.key[n - 1] >> 32) : -1;
+  uint64_t gap[kPerT], hb[kPerT], hp[kPerT], sk[kPerT];
+  // loads first, unconditional (clamped to entry 0), so they are in flight together
+#pragma unroll
+  for (int q = 0; q < kPerT; ++q) {
+    const int32_t x = int32_t(threadIdx.x) + q * kResolveThreads;
+    const bool in = x < n;
+    const int64_t b = in ? int64_t(s.key[x] >> 32) : 0;
+    const int64_t pb = in && x > 0 ? int64_t(s.key[x - 1] >> 32) : -1;
+    hb[q] = Hi[b];
+    hp[q] = Hi[pb + 1];
+    sk[q] = uint64_t(sizes[in ? s.k[x] : 0u]);
+  }
+#pragma unroll
+  for (int q = 0; q < kPerT; ++q) {
+    const int32_t x = int32_t(threadIdx.x) + q * kResolveThreads;
+    gap[q] = 0;
+    if (x < n) {
+      const int64_t b = int64_t(s.key[x] >> 32);
+      const int64_t pb = x > 0 ? int64_t(s.key[x - 1] >> 32) : -1;
+      if (b != pb) gap[q] = hb[q] - (pb < 0 ? 0ull : hp[q]);
+      s.sz[x] = sk[q];
+    }
+  }
+  __syncthreads();  // every key is read before any is replaced
+#pragma unroll
+  for (int q = 0; q < kPerT; ++q) {
+    const int32_t x = int32_t(threadIdx.x) + q * kResolveThreads;
+    if (x < n) s.key[x] = gap[q];
+  }
+  __syncthreads();
+  // key[x] becomes the bytes of the ranking up to and with candidate x
+  {
+    uint64_t v[kPerT], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kPerT; ++q) {
+      const int32_t x = int32_t(threadIdx.x) * kPerT + q;
+      sum += x < n ? s.key[x] + s.sz[x] : 0ull;
+      v[q] = sum;
+    }
+    uint64_t total;
+    const uint64_t ex = block_exclusive_scan64(sum, s.tmp, &total);
+#pragma unroll
+    for (int q = 0; q < kPerT; ++q) {
+      const int32_t x = int32_t(threadIdx.x) * kPerT + q;
+      if (x < n) s.key[x] = ex + v[q];
+    }
+  }
+  __syncthreads();
+  // the greedy fill: a tier that starts after `base` bytes of the ranking
+  // takes what fits; the first candidate that does not (a search over the
+  // running bytes) starts the next. One by one over the 1,500 to 2,000
+  // candidates of a worker this took 0.2 ms.
+  if (threadIdx.x == 0) {
+    int64_t* ui = used + i * a.J;
+    int32_t x0 = 0;
+    uint64_t base = 0;
+    int j = 0;
+    for (; j < a.J; ++j) {
+      s.start[j] = x0;
+      int32_t lo = x0, hi = n;
+      while (lo < hi) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (s.key[mid] - base > uint64_t(a.caps[j])) hi = mid;
+        else lo = mid + 1;
+      }
+      if (lo == n) break;  // everything left fits
+      const uint64_t before = s.key[lo] - s.sz[lo];
+      ui[j] = int64_t(before - base);
+      x0 = lo;
+      base = before;
+    }
+    if (j < a.J) {
+      const uint64_t gap_start = last_bin < 0 ? 0ull : Hi[last_bin + 1];
+      ui[j] = int64_t((n > 0 ? s.key[n - 1] : 0ull) - base + (Hi[a.nbin] - gap_start));
+      for (int jj = j + 1; jj < a.J; ++jj) ui[jj] = 0;
+      for (int jj = j + 1; jj <= a.J; ++jj) s.start[jj] = n;
+    } else {
+      s.start[a.J] = x0;
+    }
+  }
+  __syncthreads();
+  int8_t* trow = tier + i * a.F;
+  for (int32_t x = threadIdx.x; x < n; x += kResolveThreads) {
+    int tv = 0;
+    for (int j = 1; j <= a.J; ++j) tv += s.start[j] <= x;
+    trow[s.k[x]] = tv >= a.J ? int8_t(-1) : int8_t(tv);
+  }
+}
+
 // -- passes over the compact read-cell list (fused planning call) -----------------
 // The counting pass lists, per (worker, window of 2^ws samples), the cells the
 // worker reads: bin << kListOffBits | offset in window. Cells missing from the
@@ -678,7 +756,7 @@ struct CompactArgs {
 constexpr int kHistCU = NOPFS_HIST_CU;  // list entries per lane in flight
 
 // Histogram of one (worker, slice): each wave takes whole windows of the
-// slice; class-0 read bytes and class >= 1 bins as in plan_hist. The list
+// slice (or a share of one, where there are fewer windows than waves); class-0 read bytes and class >= 1 bins as in plan_hist. The list
 // bounds of up to kHistWins windows are staged in LDS at once, and a wave
 // requests the next window's entries before waiting for this window's sizes.
 constexpr uint32_t kHistWins = 1024;
@@ -694,8 +772,8 @@ plan_hist_c(PlanArgs a, CompactArgs c, const int64_t* __restrict__ sizes, uint64
   const uint32_t t = xcd_logical(blockIdx.x, gridDim.x);
   if (t >= uint32_t(a.N) * nslices) return;
   const int64_t sl = t / a.N, i = t - sl * a.N;
-  const int64_t ks = sl * kSliceCells;
-  const int64_t ke = ks + kSliceCells < a.F ? ks + kSliceCells : a.F;
+  const int64_t ks = sl * a.slice;
+  const int64_t ke = ks + a.slice < a.F ? ks + a.slice : a.F;
   const uint32_t zb0 = uint32_t(ks >> kClass0Shift);
   const uint32_t nz = uint32_t((ke - ks + (1 << kClass0Shift) - 1) >> kClass0Shift);
   for (uint32_t b = threadIdx.x; b < a.nbin1; b += kThreads) h1[b] = 0;
@@ -724,15 +802,22 @@ plan_hist_c(PlanArgs a, CompactArgs c, const int64_t* __restrict__ sizes, uint64
                 static_cast<unsigned long long>(sz));
       atomicAdd(&zs[uint32_t(k >> kClass0Shift) - zb0], static_cast<unsigned long long>(sz));
     };
+    // `split` waves share a window's steps where a slice has fewer windows
+    // than there are waves
+    uint32_t split = 1;
+    while (2 * split * c.wps <= kWaves) split *= 2;
+    const uint32_t q00 = (wave % split) * kStep;
     auto window = [&](uint32_t kb, uint32_t& n, const uint32_t*& e) {
       n = kb < g1 ? wnum[kb - g0] : 0u;
       e = erow + (kb < g1 ? wbase[kb - g0] : 0);
     };
-    auto next_window = [&](uint32_t& kb, uint32_t& n, const uint32_t*& e) {
-      do {
-        kb += kWaves;
+    // on to the wave's next step that has entries
+    auto settle = [&](uint32_t& kb, uint32_t& q0, uint32_t& n, const uint32_t*& e) {
+      while (kb < g1 && q0 >= n) {
+        kb += kWaves / split;
+        q0 = q00;
         window(kb, n, e);
-      } while (kb < g1 && n == 0u);
+      }
     };
     auto load = [&](uint32_t (&dst)[kHistCU], const uint32_t* e, uint32_t q0, uint32_t n) {
       const uint32_t last = n ? n - 1 : 0u;  // entry 0 of the row exists (M_max >= 1)
@@ -742,23 +827,20 @@ plan_hist_c(PlanArgs a, CompactArgs c, const int64_t* __restrict__ sizes, uint64
         dst[u] = e[q < last ? q : last];
       }
     };
-    uint32_t kb = g0 + wave, q0 = 0, n;
+    uint32_t kb = g0 + wave / split, q0 = q00, n;
     const uint32_t* e;
     window(kb, n, e);
-    if (kb < g1 && n == 0u) next_window(kb, n, e);
+    settle(kb, q0, n, e);
     uint32_t cur[kHistCU];
-    load(cur, e, 0, n);
+    load(cur, e, q0, n);
     while (kb < g1) {
       const int64_t kw = int64_t(kb) << c.ws;
       uint64_t sz[kHistCU];
 #pragma unroll
       for (int u = 0; u < kHistCU; ++u) sz[u] = uint64_t(sizes[kw + (cur[u] & kListOffMask)]);
-      uint32_t nkb = kb, nq0 = q0 + kStep, nn = n;
+      uint32_t nkb = kb, nq0 = q0 + kStep * split, nn = n;
       const uint32_t* ne = e;
-      if (nq0 >= n) {
-        nq0 = 0;
-        next_window(nkb, nn, ne);
-      }
+      settle(nkb, nq0, nn, ne);
       uint32_t nxt[kHistCU];
       load(nxt, ne, nq0, nn);
 #pragma unroll
@@ -779,25 +861,6 @@ plan_hist_c(PlanArgs a, CompactArgs c, const int64_t* __restrict__ sizes, uint64
   for (uint32_t b = threadIdx.x; b < a.nbin1; b += kThreads)
     if (h1[b]) atomicAdd(reinterpret_cast<unsigned long long*>(&Hi[b]),
                          static_cast<unsigned long long>(h1[b]));
-}
-
-// Tier (or the candidate mark) of every bin of every worker, from the cut ranges.
-constexpr int8_t kCandMark = 127;
-
-__global__ void __launch_bounds__(256)
-plan_btier(PlanArgs a, const int32_t* __restrict__ ranges, int8_t* __restrict__ btier) {
-  const int64_t i = blockIdx.y;
-  const int32_t b = int32_t(blockIdx.x) * 256 + int32_t(threadIdx.x);
-  if (b >= int32_t(a.nbin)) return;
-  const int32_t* rg = ranges + i * 2 * a.J;
-  bool cand = false;
-  int tv = 0;
-  for (int j = 0; j < a.J; ++j) {
-    const int32_t lo = rg[2 * j], hi = rg[2 * j + 1];
-    cand |= b >= lo && b <= hi;
-    tv += hi < b;
-  }
-  btier[i * a.btp + b] = cand ? kCandMark : (tv >= a.J ? int8_t(-1) : int8_t(tv));
 }
 
 // Tier row of one (worker, window): every cell starts with its class-0 bin's
@@ -1005,11 +1068,12 @@ void class_bins(int64_t F, int64_t E, int64_t L, uint16_t* nbc, uint32_t* nbin1)
 
 struct PlanBufs {
   uint64_t *H, *binsum, *Z;
-  int32_t *ranges, *ccount, *overflow;
+  int32_t *ranges, *ccount;
   CandRec* cand;
 };
 
-void plan_args(const Shape& s, const int64_t* caps, int32_t J, PlanArgs* a) {
+// slice_min: the fewest samples a slice may hold (a power of two).
+void plan_args(const Shape& s, const int64_t* caps, int32_t J, int64_t slice_min, PlanArgs* a) {
   a->F = s.F;
   a->N = s.N;
   a->M_max = s.M_max;
@@ -1019,14 +1083,18 @@ void plan_args(const Shape& s, const int64_t* caps, int32_t J, PlanArgs* a) {
   a->nb0 = uint32_t(ceil_div(s.F, int64_t(1) << kClass0Shift));
   a->nbin = a->nbin1 + a->nb0;
   a->btp = (a->nbin + 15u) & ~15u;
+  // slices of 2^19 samples; of fewer where that leaves compute units idle (48
+  // tiles at ImageNet-1k on 16 workers: the histogram of the list 0.26 ms)
+  a->slice = kSliceCells;
+  while (a->slice > slice_min && s.N * ceil_div(s.F, a->slice) < kSliceTiles) a->slice >>= 1;
   a->cmax = kCandMax;
   if (debug_value(2) > 0 && debug_value(2) < kCandMax) a->cmax = int32_t(debug_value(2));
   for (int j = 0; j < 128; ++j) a->caps[j] = j < J ? caps[j] : 0;
 }
 
-// Scratch of both plan paths, the zeroed histogram and candidate counters,
-// and the per-bin byte totals of the sizes.
-int plan_begin(const Shape& s, const PlanArgs& a, const int64_t* sizes, Scratch& scr,
+// Scratch of both plan paths, and what they start from (gct: the class table
+// in memory, NULL where it is not needed).
+int plan_begin(const Shape& s, const PlanArgs& a, const int64_t* sizes, ClassTable* gct, Scratch& scr,
                PlanBufs* b, hipStream_t st) {
   int rc;
   const int64_t hn = s.N * int64_t(a.nbin + 1);
@@ -1035,31 +1103,21 @@ int plan_begin(const Shape& s, const PlanArgs& a, const int64_t* sizes, Scratch&
   if ((rc = scr.alloc_n(&b->Z, size_t(s.N) * a.nb0))) return rc;
   if ((rc = scr.alloc_n(&b->ranges, size_t(s.N * 2 * a.J)))) return rc;
   if ((rc = scr.alloc_n(&b->ccount, size_t(s.N)))) return rc;
-  if ((rc = scr.alloc_n(&b->overflow, size_t(s.N)))) return rc;
   if ((rc = scr.alloc_n(&b->cand, size_t(s.N * a.cmax)))) return rc;
-  int64_t fb = ceil_div(hn, 1024);
-  if (fb > 65536) fb = 65536;
-  if ((rc = launch("fill_u64", fill_u64, dim3(uint32_t(fb)), dim3(256), 0, st, b->H, hn))) return rc;
-  if ((rc = launch("fill_i32", fill_i32, dim3(uint32_t(ceil_div(s.N, 256))), dim3(256), 0, st,
-                   b->ccount, s.N)))
-    return rc;
-  if (!sizes) return NOPFS_OK;  // the caller sums the bins later
-  return launch("plan_binsum", plan_binsum, dim3(uint32_t(ceil_div(a.nb0, 4))), dim3(256), 0, st,
-                s.F, a.nb0, sizes, b->binsum);
+  const uint32_t zb = uint32_t(std::min(ceil_div(hn, 1024), int64_t(65536)));
+  const uint32_t blocks = zb + uint32_t(ceil_div(a.nb0, 4)) + (gct ? 1u : 0u);
+  return launch("plan_init", plan_init, dim3(blocks), dim3(kInitThreads), 0, st, a, hn, zb, b->H,
+                b->ccount, sizes, b->binsum, gct);
 }
 
-// Exact resolution of the candidates, and the full-row fallback for workers
-// whose candidate list overflowed.
+// Exact resolution of the candidates, or of the whole row for workers whose
+// candidate list overflowed.
 int plan_end(const Shape& s, const PlanArgs& a, const PlanBufs& b, const uint8_t* count,
              const int32_t* first, const int64_t* sizes, int8_t* tier, int64_t* used,
              hipStream_t st) {
-  int rc;
-  if ((rc = launch("plan_resolve", plan_resolve, dim3(uint32_t(s.N)), dim3(kResolveThreads), 0, st,
-                   a, (const uint64_t*)b.H, (const CandRec*)b.cand, (const int32_t*)b.ccount, sizes,
-                   tier, used, b.overflow)))
-    return rc;
-  return launch("plan_exact", plan_exact, dim3(uint32_t(s.N)), dim3(1024), 0, st, a, count, first,
-                sizes, (const int32_t*)b.overflow, tier, used);
+  return launch("plan_resolve", plan_resolve, dim3(uint32_t(s.N)), dim3(kResolveThreads), 0, st, a,
+                (const uint64_t*)b.H, (const CandRec*)b.cand, (const int32_t*)b.ccount, count, first,
+                sizes, tier, used);
 }
 
 }  // namespace
@@ -1082,15 +1140,15 @@ int plan_impl(const nopfs_job* job, const uint8_t* count, const int32_t* first,
     return fail(NOPFS_EINVAL, "count, first, sizes, caps, tier and used must be non-NULL");
   if ((rc = plan_check(caps, J))) return rc;
   PlanArgs a;
-  plan_args(s, caps, J, &a);
+  plan_args(s, caps, J, kSliceMin, &a);
   Scratch scr(st);
   PlanBufs b;
-  if ((rc = plan_begin(s, a, sizes, scr, &b, st))) return rc;
+  if ((rc = plan_begin(s, a, sizes, nullptr, scr, &b, st))) return rc;
   // vector loads need 4-byte aligned count/tier rows and 16-byte aligned first rows
   const bool vec = (reinterpret_cast<uintptr_t>(count) & 3) == 0 &&
                    (reinterpret_cast<uintptr_t>(tier) & 3) == 0 &&
                    (reinterpret_cast<uintptr_t>(first) & 15) == 0;
-  const uint32_t nslices = uint32_t(ceil_div(s.F, kSliceCells));
+  const uint32_t nslices = uint32_t(ceil_div(s.F, a.slice));
   const uint32_t ntiles = uint32_t(s.N) * nslices;
   const size_t hsmem = (size_t(a.nbin1) + kSliceBins0) * 8;
   if ((rc = vec ? launch("plan_hist", plan_hist<true>, dim3(xcd_padded(ntiles)), dim3(kThreads), hsmem,
@@ -1099,7 +1157,7 @@ int plan_impl(const nopfs_job* job, const uint8_t* count, const int32_t* first,
                          st, a, count, first, sizes, b.Z, b.H, nslices)))
     return rc;
   if ((rc = launch("plan_cut", plan_cut, dim3(uint32_t(s.N)), dim3(1024), 0, st, a,
-                   (const uint64_t*)b.binsum, (const uint64_t*)b.Z, b.H, b.ranges)))
+                   (const uint64_t*)b.binsum, (const uint64_t*)b.Z, b.H, b.ranges, (int8_t*)nullptr)))
     return rc;
   if ((rc = vec ? launch("plan_write", plan_write<true>, dim3(xcd_padded(ntiles)), dim3(kThreads), 0,
                          st, a, count, first, (const int32_t*)b.ranges, tier, b.cand, b.ccount, nslices)
@@ -1118,19 +1176,19 @@ struct CompactPlan {
   int8_t* btier;
 };
 
-int compact_plan_prepare(const Shape& s, const int64_t* caps, int32_t J, Scratch& keep,
-                         hipStream_t st, CompactPlan** out, const ClassTable** classes) {
+int compact_plan_prepare(const Shape& s, const int64_t* sizes, const int64_t* caps, int32_t J, int ws,
+                         Scratch& keep, hipStream_t st, CompactPlan** out, const ClassTable** classes) {
   int rc;
   if ((rc = plan_check(caps, J))) return rc;
   CompactPlan* cp = new CompactPlan;
   *out = cp;
   cp->s = s;
-  plan_args(s, caps, J, &cp->a);
+  // a slice holds whole windows of the counting pass
+  plan_args(s, caps, J, std::max(kSliceMin, int64_t(1) << ws), &cp->a);
   if ((rc = keep.alloc_n(&cp->gct, 1))) return rc;
   if ((rc = keep.alloc_n(&cp->btier, size_t(s.N) * cp->a.btp))) return rc;
-  if ((rc = plan_begin(s, cp->a, nullptr, keep, &cp->b, st))) return rc;
   *classes = cp->gct;
-  return launch("plan_classes", plan_classes, dim3(1), dim3(64), 0, st, cp->a, cp->gct);
+  return plan_begin(s, cp->a, sizes, cp->gct, keep, &cp->b, st);
 }
 
 int compact_plan_run(CompactPlan* cp, const CompactCells& cc, const uint8_t* count,
@@ -1141,21 +1199,15 @@ int compact_plan_run(CompactPlan* cp, const CompactCells& cc, const uint8_t* cou
   const Shape& s = cp->s;
   const PlanArgs& a = cp->a;
   const PlanBufs& b = cp->b;
-  if ((rc = launch("plan_binsum", plan_binsum, dim3(uint32_t(ceil_div(a.nb0, 4))), dim3(256), 0, st,
-                   s.F, a.nb0, sizes, b.binsum)))
-    return rc;
-  const CompactArgs c{cc.ent, cc.base, cc.num, cc.ws, cc.nbk, uint32_t(kSliceCells >> cc.ws)};
-  const uint32_t nslices = uint32_t(ceil_div(s.F, kSliceCells));
+  const CompactArgs c{cc.ent, cc.base, cc.num, cc.ws, cc.nbk, uint32_t(a.slice >> cc.ws)};
+  const uint32_t nslices = uint32_t(ceil_div(s.F, a.slice));
   const uint32_t nht = uint32_t(s.N) * nslices;
   const size_t hsmem = (size_t(a.nbin1) + kSliceBins0) * 8;
   if ((rc = launch("plan_hist", plan_hist_c, dim3(xcd_padded(nht)), dim3(kThreads), hsmem, st, a, c,
                    sizes, b.Z, b.H, nslices)))
     return rc;
   if ((rc = launch("plan_cut", plan_cut, dim3(uint32_t(s.N)), dim3(1024), 0, st, a,
-                   (const uint64_t*)b.binsum, (const uint64_t*)b.Z, b.H, b.ranges)))
-    return rc;
-  if ((rc = launch("plan_btier", plan_btier, dim3(uint32_t(ceil_div(a.nbin, 256)), uint32_t(s.N)),
-                   dim3(256), 0, st, a, (const int32_t*)b.ranges, cp->btier)))
+                   (const uint64_t*)b.binsum, (const uint64_t*)b.Z, b.H, b.ranges, cp->btier)))
     return rc;
   const uint32_t ntiles = uint32_t(s.N) * cc.nbk;
   const bool vec = (reinterpret_cast<uintptr_t>(tier) & 15) == 0;  // 16-byte row stores
