@@ -49,8 +49,8 @@ DEFAULT_WORKLOAD = "imagenet22k"
 # launch names). The counting and next-use passes share one partition of R in
 # the fused call; its kernels are counted with the counting stage.
 STAGES = {
-    "streams": ("stream_count", "stream_offsets", "stream_scan", "stream_scatter", "stream_split",
-                "stream_sort", "stream_pad"),
+    "streams": ("stream_count", "stream_offsets", "stream_scan", "stream_scatter", "stream_sort",
+                "stream_pad"),
     "stats": ("seg_partition", "offsets_transpose", "stats_tile", "fill_stats_empty"),
     "next": ("next_walk", "next_tile", "next_unpartition", "pad_rows"),
     "plan": ("plan_init", "plan_hist", "plan_cut", "plan_write", "plan_resolve"),

@@ -310,6 +310,22 @@ plan_cut(PlanArgs a, const uint64_t* __restrict__ binsum, const uint64_t* __rest
   __syncthreads();
   const uint64_t total = carry;
   const int32_t nbin = int32_t(a.nbin);
+  // first x in [lo, hi) with Hi[x] > t, else hi, by one wave: 64 probes a
+  // round (three rounds over 60,000 bins; a search by one thread waits for
+  // 16 loads in a row)
+  auto first_above = [&](int32_t lo, int32_t hi, uint64_t t) {
+    while (lo < hi) {
+      const int32_t step = (hi - lo + 63) / 64;
+      const int32_t x = lo + int32_t(__lane_id()) * step;
+      const uint64_t v = Hi[x < hi ? x : lo];  // unconditional
+      const int below = __builtin_popcountll(__ballot(x < hi && v <= t));
+      if (below == 0) return lo;
+      const int32_t nlo = lo + (below - 1) * step + 1;
+      hi = lo + below * step < hi ? lo + below * step : hi;
+      lo = nlo;
+    }
+    return lo;
+  };
   auto cuts = [&]() {
     uint64_t s_lo = 0, s_hi = 0;
     for (int j = 0; j < a.J; ++j) {
@@ -317,34 +333,25 @@ plan_cut(PlanArgs a, const uint64_t* __restrict__ binsum, const uint64_t* __rest
       const uint64_t t_lo = s_lo + cap < s_lo ? ~0ull : s_lo + cap;
       const uint64_t t_hi = s_hi + cap < s_hi ? ~0ull : s_hi + cap;
       if (t_lo >= total) {
-        for (int jj = j; jj < a.J; ++jj) {
+        for (int jj = j + int(__lane_id()); jj < a.J; jj += 64) {
           rg[2 * jj] = nbin;
           rg[2 * jj + 1] = nbin;
         }
         return;
       }
-      // lo: first bin b with cum_after(b) = Hi[b+1] > t_lo
-      int32_t lo = 1, hi = nbin;  // search x in [1, nbin] for the first Hi[x] > t_lo
-      while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
-        if (Hi[mid] > t_lo) hi = mid; else lo = mid + 1;
+      // blo: first bin with cum_after = Hi[b + 1] > t_lo (Hi[nbin] = total is)
+      const int32_t blo = first_above(1, nbin, t_lo) - 1;
+      // bhi: last bin with cum_before = Hi[b] <= t_hi (Hi[0] = 0 is)
+      const int32_t bhi = first_above(1, nbin, t_hi) - 1;
+      if (__lane_id() == 0) {
+        rg[2 * j] = blo;
+        rg[2 * j + 1] = bhi;
       }
-      const int32_t blo = lo - 1;
-      // hi: last bin b < nbin with cum_before(b) = Hi[b] <= t_hi
-      lo = 0;
-      hi = nbin - 1;
-      while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        if (Hi[mid] <= t_hi) lo = mid; else hi = mid - 1;
-      }
-      const int32_t bhi = lo;
-      rg[2 * j] = blo;
-      rg[2 * j + 1] = bhi;
       s_lo = Hi[blo];
       s_hi = t_hi < total ? t_hi : total;
     }
   };
-  if (threadIdx.x == 0) cuts();
+  if (threadIdx.x < 64) cuts();
   __syncthreads();
   if (!btier) {
     for (int x = threadIdx.x; x < 2 * a.J; x += 1024) ranges[i * 2 * a.J + x] = rg[x];
@@ -876,6 +883,7 @@ constexpr int kWriteWin = 8192;  // cells held in LDS at once
 #ifndef NOPFS_WRITE_ENT
 #define NOPFS_WRITE_ENT 6
 #endif
+constexpr uint32_t kCandTile = 512;  // candidates of a pass appended together
 constexpr int kWriteEnt = NOPFS_WRITE_ENT;  // list entries per thread loaded up front
 
 constexpr uint32_t kBt1Max = ((kBins1Budget + 256 + 15) / 16) * 16;  // class >= 1 bins, padded
@@ -890,8 +898,17 @@ plan_write_c(PlanArgs a, CompactArgs c, const int32_t* __restrict__ first,
   __shared__ int8_t t0[kWriteWin / (1 << kClass0Shift) + 1];
   int8_t* tb = reinterpret_cast<int8_t*>(tbw);
   __shared__ int s_c0cand;
+  // candidates of a pass with a long list: one claim on the worker's list for
+  // all of them. A claim by each lane kept the tile waiting on the list's counter
+  // (ImageNet-1k on 16 workers, 8,150 entries a tile: 0.27 ms, now 0.054); a
+  // short list meets a candidate or two, and the claim's barriers cost more
+  // (ImageNet-22k, 1,190 entries a tile: 1.17 ms against 1.14).
+  __shared__ uint32_t s_cand[kCandTile];
+  __shared__ uint32_t s_nc;
+  __shared__ int32_t s_cbase;
   const uint32_t tile = xcd_logical(blockIdx.x, gridDim.x);
   if (tile >= ntiles) return;
+  if (threadIdx.x == 0) s_nc = 0;
   const int64_t i = tile / c.nbk;
   const uint32_t kb = tile - uint32_t(i) * c.nbk;
   const int8_t* bt = btier + i * int64_t(a.btp);  // 16-byte aligned rows
@@ -917,6 +934,7 @@ plan_write_c(PlanArgs a, CompactArgs c, const int32_t* __restrict__ first,
       bt[a.nbin1 + uint32_t(k0 >> kClass0Shift) + (threadIdx.x < nzb_first ? threadIdx.x : 0u)];
   const uint32_t n = c.num[tix];
   const uint32_t* ent = c.ent + i * a.M_max + c.base[tix];
+  const bool many = n > uint32_t(kWriteEnt * kWriteThreads);
   // round two: the list entries
   uint32_t ev[kWriteEnt];
 #pragma unroll
@@ -942,8 +960,11 @@ plan_write_c(PlanArgs a, CompactArgs c, const int32_t* __restrict__ first,
       const uint32_t b = v >> kListOffBits;
       const int8_t tv = bt1[b];
       if (tv == kCandMark) {
-        // the rank key needs the first read itself (few cells per worker)
-        append((uint64_t(b) << 32) | uint64_t(uint32_t(frow[w0 + x])), w0 + x);
+        // the rank key needs the first read itself (few cells per worker):
+        // noted here, appended together after the pass
+        const uint32_t at = many ? atomicAdd(&s_nc, 1u) : kCandTile;
+        if (at < kCandTile) s_cand[at] = v;
+        else append((uint64_t(b) << 32) | uint64_t(uint32_t(frow[w0 + x])), w0 + x);
         tb[x + sh] = 0;
       } else {
         tb[x + sh] = tv;
@@ -1008,6 +1029,20 @@ plan_write_c(PlanArgs a, CompactArgs c, const int32_t* __restrict__ first,
     for (uint32_t q = threadIdx.x + kWriteEnt * kWriteThreads; q < n; q += kWriteThreads)
       apply(ent[q], xoff, wlen, w0, sh);
     __syncthreads();
+    const uint32_t nc = !many ? 0u : (s_nc < kCandTile ? s_nc : kCandTile);  // uniform
+    if (nc) {
+      if (threadIdx.x == 0) s_cbase = atomicAdd(&ccount[i], int32_t(nc));
+      __syncthreads();
+      for (uint32_t q = threadIdx.x; q < nc; q += kWriteThreads) {
+        const uint32_t v = s_cand[q];
+        const int64_t k = k0 + (v & kListOffMask);
+        const int32_t slot = s_cbase + int32_t(q);
+        if (slot < a.cmax)
+          ci[slot] = CandRec{(uint64_t(v >> kListOffBits) << 32) | uint64_t(uint32_t(frow[k])), uint32_t(k), 0u};
+      }
+      __syncthreads();
+      if (threadIdx.x == 0) s_nc = 0;  // the next pass's barriers come before its first use
+    }
     if (s_c0cand) {
       // unread cells of candidate class-0 bins (read ones were overwritten)
       for (uint32_t x = threadIdx.x; x < wlen; x += kWriteThreads) {

@@ -100,8 +100,10 @@ __device__ __forceinline__ uint32_t philox_key(uint32_t id, uint32_t e, uint32_t
 // -- 1. histogram of buckets per chunk ----------------------------------------
 // cnt layout: [epoch][chunk][bucket of the pass]
 __global__ void __launch_bounds__(kThreads)
-stream_count(StreamParams p, uint32_t* __restrict__ cnt) {
+stream_count(StreamParams p, uint32_t* __restrict__ cnt, uint32_t* __restrict__ wpos) {
   extern __shared__ uint32_t hist[];
+  // the first pass over an epoch's keys starts at its first position
+  if (p.wb0 == 0 && blockIdx.x == 0 && threadIdx.x == 0) wpos[blockIdx.y] = 0;
   const uint32_t nbw = p.nbw;
   for (uint32_t b = threadIdx.x; b < nbw; b += kThreads) hist[b] = 0;
   __syncthreads();
@@ -196,10 +198,6 @@ stream_scan(uint32_t nbw, const uint32_t* __restrict__ tot, uint32_t* __restrict
     wbase[blockIdx.x] = w;
     wpos[blockIdx.x] = w + carry;
   }
-}
-
-__global__ void stream_zero(uint32_t* __restrict__ a, uint32_t n) {
-  for (uint32_t x = threadIdx.x; x < n; x += blockDim.x) a[x] = 0;
 }
 
 // -- 4. scatter ------------------------------------------------------------------
@@ -746,11 +744,10 @@ int streams_impl(const nopfs_job* job, int32_t* R, hipStream_t st, int32_t e_beg
   for (int64_t e0 = 0; e0 < s.E; e0 += EB) {
     const uint32_t eb = uint32_t(e0 + EB <= s.E ? EB : s.E - e0);
     p.e0 = int32_t(e_begin + e0);
-    if ((rc = launch("stream_zero", stream_zero, dim3(1), dim3(256), 0, st, wpos, eb))) return rc;
     for (uint32_t wb0 = 0; wb0 < nb; wb0 += nbw) {
       p.wb0 = wb0;
       if ((rc = launch("stream_count", stream_count, dim3(nchunks, eb), dim3(kThreads),
-                       size_t(nbw) * 4, st, p, cnt)))
+                       size_t(nbw) * 4, st, p, cnt, wpos)))
         return rc;
       if ((rc = launch("stream_offsets", stream_offsets, dim3(uint32_t(ceil_div(nbw, 64)), eb),
                        dim3(256), 0, st, p, cnt, offb, tot)))
