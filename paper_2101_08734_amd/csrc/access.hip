@@ -70,7 +70,7 @@ constexpr int kPartThreads = 512;
 
 __global__ void __launch_bounds__(kPartThreads)
 seg_partition(SegParams p, const int32_t* __restrict__ R, uint32_t* __restrict__ Pk,
-              uint16_t* __restrict__ O) {
+              uint16_t* __restrict__ O, uint16_t* __restrict__ OT) {
   extern __shared__ uint32_t sm[];
   __shared__ uint32_t tmp[65];
   const uint32_t nbk = p.nbk;
@@ -112,9 +112,13 @@ seg_partition(SegParams p, const int32_t* __restrict__ R, uint32_t* __restrict__
   }
   __syncthreads();
   block_scan_array(hist, nbk, tmp);
-  uint16_t* o = O + orow(p, i, e, sc);
-  for (uint32_t b = threadIdx.x; b < nbk; b += kPartThreads) o[b] = uint16_t(hist[b]);
-  if (threadIdx.x == 0) o[nbk] = uint16_t(len);
+  // the window offsets, sub-chunk-major into O, or straight to their
+  // window-major place where there is no O
+  uint16_t* o = O ? O + orow(p, i, e, sc)
+                  : OT + int64_t(i) * (nbk + 1) * per_worker + rem;
+  const int64_t pitch = O ? 1 : int64_t(per_worker);
+  for (uint32_t b = threadIdx.x; b < nbk; b += kPartThreads) o[b * pitch] = uint16_t(hist[b]);
+  if (threadIdx.x == 0) o[nbk * pitch] = uint16_t(len);
   __syncthreads();  // the offsets are read above before they become cursors below
 #pragma unroll
   for (int r = 0; r < kPer; ++r) {
@@ -524,14 +528,18 @@ __device__ void next_tile_slow(const SegParams& p, int64_t i, uint32_t kb, const
     const uint32_t xoff = uint32_t(w0 - k0);
     for (uint32_t x = threadIdx.x; x < wlen; x += kNextThreads) last[x] = -1;
     __syncthreads();
-    for (int64_t e = p.E - 1; e >= 0; --e) {
+    const int64_t epoch = seg_len(p, i) / p.emul;
+    for (int64_t e = int64_t(p.E) * p.emul - 1; e >= 0; --e) {
       // reads of one epoch are distinct samples: no two threads share a slot
-      for_each_read(p, i, kb, O, prow, rt, e, e + 1,
+      // (with the epochs folded, those of the epoch among all the row's)
+      const int64_t seg = p.emul == 1 ? e : 0;
+      for_each_read(p, i, kb, O, prow, rt, seg, seg + 1,
                     [&](int64_t pos, int64_t fbase, uint32_t v, uint32_t) {
                       const uint32_t x = (v >> kScShift) - xoff;
-                      if (x < wlen) {
+                      const int64_t f = fbase + (v & kJMask);
+                      if (x < wlen && f >= e * epoch && f < (e + 1) * epoch) {
                         nrow[pos] = last[x];
-                        last[x] = int32_t(fbase + (v & kJMask));
+                        last[x] = int32_t(f);
                       }
                     });
       __syncthreads();
@@ -845,7 +853,7 @@ int launch_stats(const SegParams& p, const uint32_t* Pk, const uint16_t* OT, uin
                    (reinterpret_cast<uintptr_t>(first) & 15) == 0;
   const dim3 grid(xcd_padded(ntiles)), block(kStatsThreads);
   const int64_t runs = int64_t(p.E) * p.nsc;
-  const int64_t split = std::max(int64_t(kStatsSplit), int64_t(run_mean(p) / kRunLoads));
+  const int64_t split = std::max(int64_t(kStatsSplit), int64_t((run_mean(p) * 1.25 + 24) / kRunLoads));
   const uint32_t ns = uint32_t(std::max(int64_t(1), std::min(kStatsThreads / runs, split)));
   uint32_t* ent = cc ? cc->ent : nullptr;
   int32_t* base = cc ? cc->base : nullptr;
@@ -894,6 +902,7 @@ int next_ws(const Shape& s) {
 
 SegParams chain_params(const Shape& s) {
   SegParams p = seg_params(s, next_ws(s));
+  fold_epochs(p);
   if (debug_value(2) > 0 && debug_value(2) < kNextEnt) p.ent_cap = int32_t(debug_value(2));
   return p;
 }
@@ -945,6 +954,8 @@ SegParams seg_params(const Shape& s, int ws) {
   return p;
 }
 
+constexpr size_t kDirectOffsets = size_t(1) << 16;
+
 static size_t partition_smem(const SegParams& p) {
   return size_t(((p.nbk + 4) & ~3u) + kSC) * 4;
 }
@@ -957,10 +968,14 @@ int run_partition(const SegParams& p, const int32_t* R, Scratch& scr, uint32_t**
   if ((rc = scr.alloc_n(Pk, size_t(p.N * p.M_max)))) return rc;
   if ((rc = scr.alloc_n(&O, on))) return rc;
   if ((rc = scr.alloc_n(OT, on))) return rc;
+  // few offsets go straight to their window-major places (a launch less, 5 us);
+  // many would scatter 2-byte stores over the table
+  const bool direct = on <= kDirectOffsets;
   const int64_t wgs = p.N * p.E * p.nsc;
   if ((rc = launch("seg_partition", seg_partition, dim3(uint32_t(wgs)), dim3(kPartThreads),
-                   partition_smem(p), st, p, R, *Pk, O)))
+                   partition_smem(p), st, p, R, *Pk, direct ? (uint16_t*)nullptr : O, *OT)))
     return rc;
+  if (direct) return NOPFS_OK;
   const int64_t runs = int64_t(p.E) * p.nsc;
   return launch("offsets_transpose", offsets_transpose,
                 dim3(uint32_t(ceil_div(runs, 64)), uint32_t(ceil_div(p.nbk + 1, 64)), uint32_t(p.N)),
@@ -982,6 +997,7 @@ int stats_impl(const nopfs_job* job, const int32_t* R, uint8_t* count, int32_t* 
                   count, first);
   }
   SegParams p = seg_params(s, NOPFS_STATS_WS);
+  fold_epochs(p);
   Scratch scr(st);
   uint32_t* Pk;
   uint16_t* OT;
@@ -1012,10 +1028,11 @@ int counting_ws(const Shape& s) { return seg_params(s, NOPFS_STATS_WS).ws; }
 int access_fused(const Shape& s, const int32_t* R, const ClassTable* classes, uint8_t* count,
                  int32_t* first, int32_t* next, CompactCells* cc, Scratch& keep, hipStream_t st) {
   int rc;
-  const SegParams ps = seg_params(s, NOPFS_STATS_WS);
+  SegParams ps = seg_params(s, NOPFS_STATS_WS);
   SegParams pn = chain_params(s);
   const bool walk = walks(ps, pn.ws == ps.ws ? kWalkReads : kWalkReadsFused);
-  if (walk) pn = ps;
+  if (walk) pn = ps;  // epoch by epoch
+  else fold_epochs(ps);
   uint32_t *Pk, *Pn;
   uint16_t *OT, *OTn;
   int32_t* nextP;

@@ -35,6 +35,22 @@ __device__ __forceinline__ int64_t seg_len(const SegParams& p, int64_t i) {
   return int64_t(p.emul) * (p.drop_last ? p.L : epoch_len(p.F, p.N, p.B, 0, i));
 }
 
+// For the passes that do not depend on the order of a run's reads: epochs of
+// at most half a sub-chunk are folded into one segment per row, cut into
+// sub-chunks of 2^14 positions, so that short epochs share a workgroup.
+// CosmoFlow (256 reads an epoch, 1,024 workers): 40,960 workgroups of 256 reads
+// become 1,024 of 10,240, seg_partition 0.27 -> 0.024, next_unpartition 0.17 ->
+// 0.021 ms; ImageNet-1k on 256 workers (5,004 reads): partition 0.16 -> 0.12 ms.
+// Long epochs stay as they are: folded at ImageNet-22k (55,456 reads, 3.4
+// sub-chunks) the partition took 0.93 ms against 0.87 and the unpartition 1.36
+// against 1.25.
+inline void fold_epochs(SegParams& p) {
+  if (p.L > kSC / 2 || p.M_max == 0) return;
+  p.nsc = int32_t(ceil_div(p.M_max, kSC));
+  p.emul = p.E;
+  p.E = 1;
+}
+
 // Mean reads of a run for a uniform shuffle.
 inline double run_mean(const SegParams& p) {
   const double seg = double(p.emul) * double(p.L);
@@ -82,8 +98,20 @@ __device__ __forceinline__ uint32_t load_runs(const SegParams& p, int64_t i, uin
   uint32_t total;
   const uint32_t ex = block_exclusive_scan<false>(len, rt.tmp, &total);  // closed below
   rt.pref[threadIdx.x] = ex;
-  if (total <= kRunMap)
-    for (uint32_t q = 0; q < len; ++q) rt.run_of[ex + q] = uint16_t(threadIdx.x);
+  if (total <= kRunMap) {
+    if (runs - r0 > NT / 4) {
+      for (uint32_t q = 0; q < len; ++q) rt.run_of[ex + q] = uint16_t(threadIdx.x);
+    } else {
+      // few runs: 2^lg threads write a run's entries (one alone would write a
+      // run of hundreds)
+      __syncthreads();
+      int lg = 2;
+      while ((runs - r0) << (lg + 1) <= NT) ++lg;
+      const uint32_t run = threadIdx.x >> lg, per = 1u << lg;
+      const uint32_t z = rt.pref[run + 1];
+      for (uint32_t q = rt.pref[run] + (threadIdx.x & (per - 1)); q < z; q += per) rt.run_of[q] = uint16_t(run);
+    }
+  }
   __syncthreads();
   return total;
 }

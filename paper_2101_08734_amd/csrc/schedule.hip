@@ -888,12 +888,13 @@ int prefetch_impl(const nopfs_job* job, const int32_t* R, const int8_t* tier, in
   if (s.M_max > 0 && (!R || !order)) return fail(NOPFS_EINVAL, "R and order must be non-NULL");
   if (J < 1) return fail(NOPFS_EINVAL, "J must be >= 1");
   if (J > 127) return fail(NOPFS_ERANGE, "J must be <= 127");
-  const SegParams p = seg_params(s, kSchedWs);
-  const uint32_t nch = uint32_t(s.E * p.nsc);  // sub-chunks per worker
-  const int64_t nblk = s.N * int64_t(nch);
+  SegParams p = seg_params(s, kSchedWs);
   const int64_t ntiles = s.N * int64_t(p.nbk);
-  if (nblk >= (int64_t(1) << 31) || ntiles >= (int64_t(1) << 31))
+  if (s.N * s.E * int64_t(p.nsc) >= (int64_t(1) << 31) || ntiles >= (int64_t(1) << 31))
     return fail(NOPFS_ERANGE, "job too large for one launch");
+  fold_epochs(p);
+  const uint32_t nch = uint32_t(p.E) * uint32_t(p.nsc);  // sub-chunks per worker
+  const int64_t nblk = s.N * int64_t(nch);
   Scratch scr(st);
   int64_t* tot;
   int32_t* cnt;
