@@ -9,7 +9,43 @@
 // held bytes exceed d0, the furthest key is discarded (possibly n itself).
 // The size of the sample held under key x is that of the sample read at x,
 // sizes[R[x]].
-// The replay is sequential per worker and the workers are independent.
+// The workers are independent. Two ways to replay one:
+//
+// In the order of next uses (kb_*). A discard takes the furthest keys first,
+// so whether key k stays does not depend on later keys. Take the candidates
+// (reads f with a next use k and a size s <= d0, held over [f, k)) by
+// increasing k. Let load(t) be the bytes of the accepted earlier keys held
+// after read t, and T the last time any earlier key was discarded (a key
+// discarded at T takes every later key held then with it). Then k stays, and
+// its read hits, exactly when f > T and load(t) + s <= d0 for every t in
+// [f, k); otherwise, when f > T, it is discarded at the first t where that
+// fails, which becomes T. In a shuffled stream T moves only a few times per
+// epoch (18 times over the 160,000 candidates of an ImageNet-22k worker, 350
+// over 5.9M at ImageNet-1k on 16 workers): in between, everything with f > T
+// is accepted, thousands of candidates at a time, as long as the load provably
+// stays within d0.
+//   kb_init  -- hit flags to 0 (-1 in padding), previous uses to -1.
+//   kb_prev  -- previous uses, prev[next[f]] = f.
+//   kb_sim   -- one workgroup per worker. A batch is the candidates whose next
+//               uses lie in up to 4,096 consecutive positions. Per block of
+//               positions (8,192 blocks a row) U is the bytes of the accepted
+//               candidates and the batch's that touch the block, kept as
+//               differences in LDS: at least load(t) anywhere in it. If no U
+//               after T exceeds d0 the batch is accepted. Otherwise the
+//               blocks in question are looked into position by position; what
+//               U is above the true maximum by is remembered with the block,
+//               which settles most of them for good. A true excess is first
+//               narrowed to a batch of few candidates, then found by taking
+//               candidates back from the load, last to first, at every
+//               position in question.
+// ImageNet-22k, 5 GB: 102 ms in stream order, 9.1 in the order of next uses
+// (kb_sim 6.8, kb_prev 1.5, kb_init 0.7); 300,000 samples, 10 epochs, 2 workers
+// 620 -> 4.4; 10,000 samples, 5 epochs, 4 workers 2.6 -> 0.7. What bounds kb_sim:
+// per batch two block-wide scans and five barriers, per change of T several
+// looks into blocks (about 50 us).
+//
+// In stream order (bs_sim), where an epoch brings too few candidates for that
+// (the rule in buffer_impl), or memory for the previous uses is missing:
 //
 //   bs_sim   -- one wave per worker. Held keys in a three-level bitmap: a
 //               bit per position in 64-bit words in global memory, one word
@@ -33,7 +69,9 @@
 
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <new>
+#include <string>
 
 #include "common.hpp"
 
@@ -352,6 +390,479 @@ bs_sim(BsShape r, const int32_t* __restrict__ R, const int32_t* __restrict__ nex
   }
 }
 
+// -- the replay in the order of next uses ---------------------------------------
+constexpr int kKbThreads = 512;
+constexpr int kKbWaves = kKbThreads / 64;
+constexpr int kKbPer = 8;                            // positions per thread and window
+constexpr int kKbWindow = kKbThreads * kKbPer;       // 4,096
+constexpr int kKbList = 2048;                        // candidates per batch
+constexpr int kKbBlocks = 8192;                      // time blocks
+constexpr int kKbMinShift = 6;                       // of at least 64 positions
+constexpr int kKbSeg = kKbBlocks / kKbThreads;       // blocks per thread in the scan
+constexpr uint32_t kKbFew = 128;   // a batch of more candidates is cut before its record is searched
+constexpr uint32_t kKbMany = 32;   // as is one that puts more blocks than this over
+constexpr int kKbMinSpan = 256;    // but not below this many positions
+constexpr double kKbMinCands = 300;  // candidates per worker and epoch
+constexpr int64_t kKbMaxD0 = int64_t(1) << 50;       // sums over a block and a batch stay below 2^63
+
+// padded index: a thread's 16 consecutive blocks start on different banks
+__device__ __forceinline__ int kb_slot(int b) { return b + (b >> 4); }
+
+struct KbCand {
+  int32_t f, k;  // held from its read f to its next use k
+  int64_t s;
+};
+
+struct KbSmem {
+  int64_t dd[kKbBlocks + kKbBlocks / 16 + 2];   // differences of U between blocks (or U itself)
+  uint32_t adj[kKbBlocks + kKbBlocks / 16 + 2]; // what U is known to be above the exact maximum by
+  KbCand cand[kKbList];                         // the batch's candidates
+  uint16_t flag[kKbBlocks];                     // blocks to look into; bit 15: over capacity
+  int64_t wtot[kKbWaves];
+  uint32_t cnt[kKbWaves];
+  uint32_t nflag, nviol;
+  unsigned long long best;
+  int64_t hc, hb;
+};
+
+// hit: 0 up to the row's length, -1 behind it; prev: -1
+__global__ void __launch_bounds__(256)
+kb_init(BsShape r, int32_t* __restrict__ prev, int8_t* __restrict__ hit) {
+  const int64_t i = blockIdx.y;
+  const int64_t Mi = bs_row_len(r, i);
+  const int64_t f0 = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 16;
+  int32_t* p = prev + i * r.M_max;
+  int8_t* h = hit + i * r.M_max;
+  // 16 positions per thread; a position at a time only at the end of the row
+  if (f0 + 16 <= Mi) {
+    const int4 v = make_int4(-1, -1, -1, -1);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) __builtin_memcpy(p + f0 + 4 * u, &v, 16);
+    const int4 z = make_int4(0, 0, 0, 0);
+    __builtin_memcpy(h + f0, &z, 16);
+    return;
+  }
+  for (int64_t f = f0; f < f0 + 16 && f < r.M_max; ++f) {
+    p[f] = -1;
+    h[f] = f < Mi ? 0 : -1;
+  }
+}
+
+// prev[next[f]] = f
+__global__ void __launch_bounds__(256)
+kb_prev(BsShape r, const int32_t* __restrict__ next, int32_t* __restrict__ prev) {
+  const int64_t i = blockIdx.y;
+  const int64_t Mi = bs_row_len(r, i);
+  const int64_t f0 = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 4;
+  const int32_t* x = next + i * r.M_max;
+  int32_t* p = prev + i * r.M_max;
+  int32_t v[4] = {-1, -1, -1, -1};
+  if (f0 + 4 <= Mi) {
+    __builtin_memcpy(v, x + f0, 16);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (f0 + u < Mi) v[u] = x[f0 + u];
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (v[u] > f0 + u && v[u] < Mi) p[v[u]] = int32_t(f0 + u);
+}
+
+__global__ void __launch_bounds__(kKbThreads)
+kb_sim(BsShape r, const int32_t* __restrict__ R, const int32_t* __restrict__ next,
+       const int64_t* __restrict__ sizes, int64_t d0, int ash, int sh,
+       const int32_t* __restrict__ prev, int8_t* __restrict__ hit, int64_t* __restrict__ hits) {
+  __shared__ KbSmem m;
+  const int64_t i = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t Mi = int32_t(bs_row_len(r, i));  // < 2^24
+  const int32_t* Rr = R + i * r.M_max;
+  const int32_t* Xr = next + i * r.M_max;
+  const int32_t* Pr = prev + i * r.M_max;
+  int8_t* hrow = hit + i * r.M_max;
+  auto size_of = [&](int32_t id) -> int64_t {
+    const bool in = id >= 0 && id < r.F;
+    const int64_t v = sizes[in ? id : 0];  // unconditional
+    return in ? v : 0;
+  };
+  // an interval [f, k) of s bytes joins the blocks it touches (or leaves, s < 0)
+  auto join = [&](int32_t f, int32_t k, int64_t s) {
+    const int b0 = f >> sh, b1 = ((k - 1) >> sh) + 1;  // f < k
+    atomicAdd(reinterpret_cast<unsigned long long*>(&m.dd[kb_slot(b0)]), (unsigned long long)(s));
+    if (b1 < kKbBlocks)
+      atomicAdd(reinterpret_cast<unsigned long long*>(&m.dd[kb_slot(b1)]), (unsigned long long)(-s));
+  };
+
+  // windows of kKbWindow positions, eight consecutive ones per thread:
+  // previous uses and ids two windows ahead, sizes one
+  int32_t pv[kKbPer], pvN[kKbPer], idN[kKbPer], pvA[kKbPer], idA[kKbPer];
+  int64_t sz[kKbPer], szN[kKbPer];
+  auto load_ids = [&](int32_t w0, int32_t (&p)[kKbPer], int32_t (&id)[kKbPer]) {
+    const int32_t at = w0 + kKbPer * tid;
+    if (w0 + kKbWindow <= Mi) {
+#pragma unroll
+      for (int u = 0; u < kKbPer; u += 4) {
+        __builtin_memcpy(&p[u], Pr + at + u, 16);
+        __builtin_memcpy(&id[u], Rr + at + u, 16);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < kKbPer; ++u) {
+        const int32_t q = at + u < Mi ? at + u : 0;
+        p[u] = Pr[q];
+        id[u] = Rr[q];
+        if (at + u >= Mi) p[u] = -1;
+      }
+    }
+  };
+  auto load_sizes = [&](const int32_t (&p)[kKbPer], const int32_t (&id)[kKbPer], int64_t (&s)[kKbPer]) {
+#pragma unroll
+    for (int u = 0; u < kKbPer; ++u) s[u] = size_of(p[u] >= 0 ? id[u] : -1);
+  };
+
+  int32_t T = -1;          // starts up to T are discarded
+  int32_t p0 = 0, pe = 0;  // the batch: next uses in [p0, pe)
+  int32_t span = kKbWindow;
+  // four steps of 64 positions, one position per lane and step: step u's at
+  // p[u], of the block [bs[u], be[u]). With every candidate of the batch
+  // accepted: what a position's own start adds, and that less what its own
+  // end takes away.
+  constexpr int kEv = 4;
+  typedef int32_t Steps[kEv];
+  auto events = [&](const Steps& p, const Steps& bs, const Steps& be, int64_t (&start)[kEv],
+                    int64_t (&change)[kEv]) {
+    int32_t q[kEv], nx[kEv], pq[kEv], id[kEv];
+#pragma unroll
+    for (int u = 0; u < kEv; ++u) {  // unconditional loads, all steps in flight together
+      q[u] = p[u] < be[u] ? p[u] : bs[u];
+      nx[u] = Xr[q[u]];
+      pq[u] = Pr[q[u]];
+      id[u] = Rr[q[u]];
+    }
+    int64_t s[kEv];
+    int8_t hn[kEv], hq[kEv];
+#pragma unroll
+    for (int u = 0; u < kEv; ++u) {
+      if (!(nx[u] > q[u] && nx[u] < Mi)) nx[u] = -1;
+      s[u] = size_of(id[u]);
+      hn[u] = hrow[nx[u] >= 0 ? nx[u] : q[u]];
+      hq[u] = hrow[q[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < kEv; ++u) {
+      const bool in = p[u] < be[u];
+      const bool st = in && nx[u] >= 0 && s[u] <= d0 &&
+                      (nx[u] < p0 ? hn[u] == 1 : nx[u] < pe && q[u] > T);
+      const bool en = in && q[u] > bs[u] &&
+                      (q[u] < p0 ? hq[u] == 1 : pq[u] > T && pq[u] >= 0 && q[u] < pe && s[u] <= d0);
+      start[u] = st ? s[u] : 0;
+      change[u] = start[u] - (en ? s[u] : 0);
+    }
+  };
+  // Blocks of 64 positions are looked into four at a time, longer ones in
+  // four steps at a time; x counts the flagged blocks.
+  const uint32_t at_once = sh == kKbMinShift ? kEv : 1;
+  struct Look {
+    Steps p, bs, be, b;  // b: -1 past the last flagged block
+  };
+  auto look = [&](uint32_t x, uint32_t nx, int32_t y) {
+    Look l;
+#pragma unroll
+    for (int u = 0; u < kEv; ++u) {
+      const uint32_t xu = at_once == 1 ? x : x + u;
+      const bool in = xu < nx;
+      l.b[u] = in ? m.flag[in ? xu : 0] & 0x7FFF : -1;
+      l.bs[u] = in ? l.b[u] << sh : 0;
+      l.be[u] = in ? (Mi - l.bs[u] < (1 << sh) ? Mi : l.bs[u] + (1 << sh)) : 0;
+      l.p[u] = l.bs[u] + y + (at_once == 1 ? 64 * u : 0) + lane;
+    }
+    return l;
+  };
+  const int32_t block = 1 << sh, stride = at_once == 1 ? 64 * kEv : block;
+
+  for (int b = tid; b < kKbBlocks + kKbBlocks / 16 + 2; b += kKbThreads) {
+    m.dd[b] = 0;
+    m.adj[b] = 0;
+  }
+  if (tid == 0) {
+    m.hc = 0;
+    m.hb = 0;
+  }
+  int64_t hc = 0, hb = 0;
+  int32_t w0 = 0;
+  if (Mi > 0) {
+    load_ids(0, pv, idN);
+    load_sizes(pv, idN, sz);
+    load_ids(kKbWindow, pvN, idN);
+  }
+  bool fresh = true;  // the window's loads for the ones after it are to be issued
+  __syncthreads();
+  while (p0 < Mi) {
+    if (p0 >= w0 + kKbWindow) {
+      w0 += kKbWindow;
+#pragma unroll
+      for (int u = 0; u < kKbPer; ++u) {
+        pv[u] = pvN[u];
+        sz[u] = szN[u];
+        pvN[u] = pvA[u];
+        idN[u] = idA[u];
+      }
+      fresh = true;
+    }
+    if (fresh) {
+      load_sizes(pvN, idN, szN);
+      load_ids(w0 + 2 * kKbWindow, pvA, idA);
+      fresh = false;
+    }
+    // the batch's candidates (starts after T that fit) in order of next use
+    pe = w0 + kKbWindow;
+    if (p0 + span < pe) pe = p0 + span;
+    if (pe > Mi) pe = Mi;
+    uint32_t cand = 0;
+#pragma unroll
+    for (int u = 0; u < kKbPer; ++u) {
+      const int32_t p = w0 + kKbPer * tid + u;
+      if (p >= p0 && p < pe && pv[u] > T && pv[u] >= 0 && sz[u] <= d0) cand |= 1u << u;
+    }
+    const uint32_t n = __popc(cand);
+    const uint32_t inc = wave_inclusive_scan(n);
+    if (lane == 63) m.cnt[wave] = inc;
+    if (tid == 0) {
+      m.nflag = 0;
+      m.nviol = 0;
+      m.best = ~0ull;
+    }
+    __syncthreads();
+    uint32_t slot = inc - n, total = 0;
+#pragma unroll
+    for (int w = 0; w < kKbWaves; ++w) {
+      const uint32_t c = m.cnt[w];
+      slot += w < wave ? c : 0u;
+      total += c;
+    }
+    if (total > uint32_t(kKbList)) {  // uniform: half the positions
+      span = (pe - p0 + 1) / 2;
+      __syncthreads();
+      continue;
+    }
+#pragma unroll
+    for (int u = 0; u < kKbPer; ++u)
+      if ((cand >> u) & 1u) {
+        const int32_t k = w0 + kKbPer * tid + u;
+        m.cand[slot++] = KbCand{pv[u], k, sz[u]};
+        join(pv[u], k, sz[u]);
+      }
+    __syncthreads();
+    // U per block: the bytes of all accepted intervals and the batch's
+    // candidates that touch it, at least the exact maximum inside it plus adj.
+    // Only times after T can go over.
+    bool alarm = false;
+    int64_t base = 0;
+    const int bT = T >= 0 ? T >> sh : 0;
+    if (total > 0) {
+      int64_t run = 0, most = INT64_MIN;
+#pragma unroll
+      for (int q = 0; q < kKbSeg; ++q) {
+        const int b = tid * kKbSeg + q;
+        run += m.dd[kb_slot(b)];
+        const int64_t over = run - (int64_t(m.adj[kb_slot(b)]) << ash);
+        most = b >= bT && over > most ? over : most;
+      }
+      const int64_t ri = int64_t(wave_inclusive_scan64(uint64_t(run)));
+      if (lane == 63) m.wtot[wave] = ri;
+      __syncthreads();
+      base = ri - run;
+#pragma unroll
+      for (int w = 0; w < kKbWaves; ++w) base += w < wave ? m.wtot[w] : 0;
+      alarm = __syncthreads_or(most != INT64_MIN && base + most > d0);
+    }
+    uint32_t accept = total;  // of the batch's candidates
+    bool record = false, retry = false;
+    if (alarm) {
+      // U in place of the differences; the blocks over capacity by it
+      int64_t run = base;
+#pragma unroll
+      for (int q = 0; q < kKbSeg; ++q) {
+        const int b = tid * kKbSeg + q;
+        run += m.dd[kb_slot(b)];
+        m.dd[kb_slot(b)] = run;
+        if (b >= bT && run - (int64_t(m.adj[kb_slot(b)]) << ash) > d0)
+          m.flag[atomicAdd(&m.nflag, 1u)] = uint16_t(b);
+      }
+      __syncthreads();
+      const uint32_t nflag = m.nflag;
+      // many candidates and many blocks: fewer candidates first
+      retry = total > kKbFew && pe - p0 > kKbMinSpan && nflag > kKbMany;
+      // the exact maximum of each after T
+      for (uint32_t x = wave * at_once; x < nflag && !retry; x += kKbWaves * at_once) {
+        int64_t carry = 0, started[kEv] = {}, most[kEv];
+#pragma unroll
+        for (int u = 0; u < kEv; ++u) most[u] = INT64_MIN;
+        Look l;
+        for (int32_t y = 0; y < block; y += stride) {
+          l = look(x, nflag, y);
+          int64_t st[kEv], ch[kEv];
+          events(l.p, l.bs, l.be, st, ch);
+#pragma unroll
+          for (int u = 0; u < kEv; ++u) {
+            int64_t v = int64_t(wave_inclusive_scan64(uint64_t(ch[u])));
+            if (at_once == 1) {
+              v += carry;
+              carry = rl64(v, 63);
+            }
+            if (l.p[u] < l.be[u] && l.p[u] > T && v > most[u]) most[u] = v;
+            started[u] += st[u];
+          }
+        }
+        if (at_once == 1) {
+#pragma unroll
+          for (int u = 1; u < kEv; ++u) {
+            most[0] = most[u] > most[0] ? most[u] : most[0];
+            started[0] += started[u];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < kEv; ++u) {
+          if (u > 0 && at_once == 1) break;
+          const int64_t sum = int64_t(read_lane64(wave_inclusive_scan64(uint64_t(started[u])), 63));
+          int64_t top = most[u];
+#pragma unroll
+          for (int d = 32; d >= 1; d >>= 1) {
+            const int64_t o = __shfl_xor(top, d, 64);
+            top = o > top ? o : top;
+          }
+          if (lane == 0 && l.b[u] >= 0) {
+            const int64_t U = m.dd[kb_slot(l.b[u])];
+            // no time after T in the block: nothing more can start in it
+            const int64_t exact = top == INT64_MIN ? 0 : U - sum + top;
+            if (exact > d0) {
+              m.flag[x + u] = uint16_t(l.b[u] | 0x8000);
+              atomicAdd(&m.nviol, 1u);
+            }
+            const uint64_t a = exact < U ? uint64_t(U - exact) >> ash : 0u;
+            m.adj[kb_slot(l.b[u])] = a < 0xFFFFFFFFull ? uint32_t(a) : 0xFFFFFFFFu;
+          }
+        }
+      }
+      __syncthreads();
+      record = retry || m.nviol != 0u;
+      retry = record && total > kKbFew && pe - p0 > kKbMinSpan;
+      if (record && !retry) {
+        // the first candidate whose bytes exceed the capacity somewhere, and
+        // the first position at which they do: from the load with the whole
+        // batch, candidates are taken away from the last to the first
+        for (uint32_t x = wave * at_once; x < nflag; x += kKbWaves * at_once) {
+          bool over = false;
+          for (uint32_t u = 0; u < at_once; ++u) over = over || (x + u < nflag && (m.flag[x + u] & 0x8000u));
+          if (!over) continue;
+          // the bytes before each block's first position: U less what starts inside
+          int64_t before[kEv] = {};
+          for (int32_t y = 0; y < block; y += stride) {
+            const Look l = look(x, nflag, y);
+            int64_t st[kEv], ch[kEv];
+            events(l.p, l.bs, l.be, st, ch);
+#pragma unroll
+            for (int u = 0; u < kEv; ++u) before[u] -= st[u];
+          }
+          if (at_once == 1) {
+#pragma unroll
+            for (int u = 1; u < kEv; ++u) before[0] += before[u];
+          }
+#pragma unroll
+          for (int u = 0; u < kEv; ++u) {
+            before[u] = int64_t(read_lane64(wave_inclusive_scan64(uint64_t(before[u])), 63));
+            const uint32_t xu = at_once == 1 ? x : x + u;
+            if (xu < nflag) before[u] += m.dd[kb_slot(m.flag[xu] & 0x7FFF)];
+          }
+          int64_t carry = before[0];
+          for (int32_t y = 0; y < block; y += stride) {
+            const Look l = look(x, nflag, y);
+            int64_t st[kEv], ch[kEv], v[kEv];
+            events(l.p, l.bs, l.be, st, ch);
+            bool any = false;
+            int best[kEv];
+#pragma unroll
+            for (int u = 0; u < kEv; ++u) {
+              v[u] = (at_once == 1 ? carry : before[u]) + int64_t(wave_inclusive_scan64(uint64_t(ch[u])));
+              carry = rl64(v[u], 63);
+              if (l.p[u] >= l.be[u] || l.p[u] <= T) v[u] = INT64_MIN;
+              any = any || v[u] > d0;
+              best[u] = -1;
+            }
+            if (!__any(any)) continue;
+            for (int j = int(total) - 1; j >= 0; --j) {
+              const KbCand c = m.cand[j];
+#pragma unroll
+              for (int u = 0; u < kEv; ++u)
+                if (v[u] > d0 && c.f <= l.p[u] && l.p[u] < c.k) {
+                  best[u] = j;
+                  v[u] -= c.s;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kEv; ++u)
+              if (best[u] >= 0)
+                atomicMin(&m.best, (static_cast<unsigned long long>(best[u]) << 32) | uint32_t(l.p[u]));
+          }
+        }
+        __syncthreads();
+        record = m.best != ~0ull;
+      }
+      // back to differences; where the batch does not stay whole, what was
+      // found out about the blocks looked into does not hold
+      {
+        int64_t u[kKbSeg + 1];
+        u[0] = tid > 0 ? m.dd[kb_slot(tid * kKbSeg - 1)] : 0;
+#pragma unroll
+        for (int q = 0; q < kKbSeg; ++q) u[q + 1] = m.dd[kb_slot(tid * kKbSeg + q)];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kKbSeg; ++q) m.dd[kb_slot(tid * kKbSeg + q)] = u[q + 1] - u[q];
+      }
+      if (record) {
+        for (uint32_t x = tid; x < nflag; x += kKbThreads) m.adj[kb_slot(m.flag[x] & 0x7FFF)] = 0;
+        accept = retry ? 0u : uint32_t(m.best >> 32);
+        __syncthreads();
+        for (uint32_t j = accept + tid; j < total; j += kKbThreads) {
+          const KbCand c = m.cand[j];
+          join(c.f, c.k, -c.s);
+        }
+      }
+    }
+    if (retry) {
+      // fewer candidates, so that the search is short
+      span = (pe - p0 + 3) / 4 > kKbMinSpan ? (pe - p0 + 3) / 4 : kKbMinSpan;
+    } else {
+      // accepted: hits at their next use
+      for (uint32_t j = tid; j < accept; j += kKbThreads) {
+        hrow[m.cand[j].k] = 1;
+        hc += 1;
+        hb += m.cand[j].s;
+      }
+      if (record) {
+        // the candidate is discarded at t, and with it every later key that
+        // starts up to t
+        p0 = m.cand[accept].k + 1;
+        T = int32_t(uint32_t(m.best));
+      } else {
+        p0 = pe;
+        span = 2 * span < kKbWindow ? 2 * span : kKbWindow;
+      }
+    }
+    __syncthreads();
+  }
+  // the worker's sums
+  atomicAdd(reinterpret_cast<unsigned long long*>(&m.hc), (unsigned long long)(hc));
+  atomicAdd(reinterpret_cast<unsigned long long*>(&m.hb), (unsigned long long)(hb));
+  __syncthreads();
+  if (tid == 0) {
+    hits[i * 2] = m.hc;
+    hits[i * 2 + 1] = m.hb;
+  }
+}
+
 int buffer_impl(const nopfs_job* job, const int32_t* R, const int32_t* next, const int64_t* sizes,
                 int64_t d0, int8_t* hit, int64_t* hits, hipStream_t st) {
   Shape s;
@@ -367,6 +878,35 @@ int buffer_impl(const nopfs_job* job, const int32_t* R, const int32_t* next, con
   Scratch scr(st);
   uint64_t* L0;
   if ((rc = scr.alloc_n(&L0, size_t(s.N * W0)))) return rc;
+  // Candidates per worker and epoch of a uniform shuffle (a read has an
+  // earlier one with probability 1 - (1 - p)^e in epoch e, p = L / F). The order
+  // of next uses pays per change of T, a few per epoch, the stream order per
+  // candidate. Measured, the least gain over buffers of 2% to 150% of an
+  // epoch: 74 candidates 0.3x, 132 0.6x, 240 0.9x (2.2x typical), 480 1.6x,
+  // 520 1.0x (3.0x), 780 1.3x (4.3x), 1,030 1.05x (4.6x).
+  const double p = double(s.L) / double(s.F), pe = p * double(s.E);
+  const double cands = s.M_max > 0 ? double(s.L) * (1.0 - (1.0 - pow(1.0 - p, double(s.E))) / pe) : 0.0;
+  if (cands >= kKbMinCands && d0 < kKbMaxD0 && s.N < 65536) {
+    // without memory for the previous uses (4 bytes per position) the replay
+    // in stream order takes the job
+    const std::string detail = nopfs_last_error();
+    int32_t* prev;
+    if (scr.alloc_n(&prev, size_t(s.N * s.M_max)) == NOPFS_OK) {
+      int ash = 0;  // units of adj: 2^ash bytes, at most 2^26 of them in d0
+      while ((d0 >> ash) >= (int64_t(1) << 26)) ++ash;
+      int sh = kKbMinShift;  // time blocks of 2^sh positions
+      while (((s.M_max - 1) >> sh) >= kKbBlocks) ++sh;
+      if ((rc = launch("kb_init", kb_init, dim3(uint32_t(ceil_div(s.M_max, 4096)), uint32_t(s.N)),
+                       dim3(256), 0, st, r, prev, hit)))
+        return rc;
+      if ((rc = launch("kb_prev", kb_prev, dim3(uint32_t(ceil_div(s.M_max, 1024)), uint32_t(s.N)),
+                       dim3(256), 0, st, r, next, prev)))
+        return rc;
+      return launch("kb_sim", kb_sim, dim3(uint32_t(s.N)), dim3(kKbThreads), 0, st, r, R, next, sizes,
+                    d0, ash, sh, (const int32_t*)prev, hit, hits);
+    }
+    set_last_error(detail);
+  }
   return launch("bs_sim", bs_sim, dim3(uint32_t(s.N)), dim3(64), 0, st, r, R, next, sizes, d0, L0, hit,
                 hits);
 }
