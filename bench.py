@@ -130,10 +130,9 @@ def committed_traffic(workload, kernel):
 
 
 POLICY_NAMES = ("perfect", "naive", "staging", "nopfs")
-SEQUENTIAL_NOTE = ("sequential per worker (each read depends on every earlier one), one "
-                   "workgroup per worker whose waves split the chains: bound by instruction "
-                   "issue and latency on the chain, not by HBM; frac is the HBM fraction for "
-                   "reference")
+BUFFER_NOTE = ("one workgroup per worker accepts its candidates batch by batch: bound by the "
+               "batches' barriers and scans and by latency, not by HBM bandwidth; frac is the HBM "
+               "fraction for reference")
 POLICY_NOTE = ("one workgroup per worker scans its chains chunk by chunk: bound by the random "
                "gathers of the sizes and by instruction issue, not by HBM bandwidth; frac is the "
                "HBM fraction for reference")
@@ -152,6 +151,8 @@ def _kernel_short_name(full):
     policy = targ.split(",")[0].strip()
     if name == "ps_sim" and policy.isdigit() and int(policy) < len(POLICY_NAMES):
         return f"ps_sim_{POLICY_NAMES[int(policy)]}"
+    if name == "kb_sim":  # the buffer's replay, in the order of next uses
+        return "bs_sim"
     if name == "st_unpart" and targ.strip() == "true":  # the 8-byte-size form, launched as such
         return "st_unpart8"
     return name
@@ -438,8 +439,7 @@ def time_model(nopfs, torch, wl, w, job, M, M_w, R, tier, sizes, steps, warmup, 
 
 def time_buffer(nopfs, torch, w, job, M, M_w, R, nxt, sizes, steps, warmup, stream):
     """The clairvoyant buffer replay of the planned job's streams with the
-    staging buffer's capacity (a sequential replay per worker, so fewer
-    calls are timed)."""
+    staging buffer's capacity."""
     d0 = int(w.staging)
     dev = R.device
     hit = torch.empty((job.N, M), dtype=torch.int8, device=dev)
@@ -454,7 +454,7 @@ def time_buffer(nopfs, torch, w, job, M, M_w, R, nxt, sizes, steps, warmup, stre
     out["hit_rate"] = round(int(h[:, 0].sum()) / A, 4)
     out["hit_bytes"] = int(h[:, 1].sum())
     out["reads_per_s_per_worker"] = round(A / job.N / (out["buffer_sim"]["ms_per_call"] * 1e-3), 1)
-    out["buffer_sim"]["roofline"]["note"] = SEQUENTIAL_NOTE
+    out["buffer_sim"]["roofline"]["note"] = BUFFER_NOTE
     return out
 
 
@@ -462,7 +462,7 @@ def time_policies(nopfs, torch, wl, w, job, M, M_w, R, tier, sizes, steps, warmu
     """The four data-loading policies of the simulator on the planned job:
     its streams and placement, the fetch model's sources (the simulated
     cluster's parameters) and the staging schedule of the workload's
-    staging buffer. Each policy is one sequential replay per worker."""
+    staging buffer."""
     dev = R.device
     d0 = int(w.staging)
     model = nopfs.make_model(**wl.LASSEN_MODEL)

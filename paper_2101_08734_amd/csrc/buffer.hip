@@ -902,7 +902,7 @@ int buffer_impl(const nopfs_job* job, const int32_t* R, const int32_t* next, con
       if ((rc = launch("kb_prev", kb_prev, dim3(uint32_t(ceil_div(s.M_max, 1024)), uint32_t(s.N)),
                        dim3(256), 0, st, r, next, prev)))
         return rc;
-      return launch("kb_sim", kb_sim, dim3(uint32_t(s.N)), dim3(kKbThreads), 0, st, r, R, next, sizes,
+      return launch("bs_sim", kb_sim, dim3(uint32_t(s.N)), dim3(kKbThreads), 0, st, r, R, next, sizes,
                     d0, ash, sh, (const int32_t*)prev, hit, hits);
     }
     set_last_error(detail);
