@@ -43,10 +43,12 @@ __device__ __forceinline__ int64_t seg_len(const SegParams& p, int64_t i) {
 // 0.021 ms; ImageNet-1k on 256 workers (5,004 reads): partition 0.16 -> 0.12 ms.
 // Long epochs stay as they are: folded at ImageNet-22k (55,456 reads, 3.4
 // sub-chunks) the partition took 0.93 ms against 0.87 and the unpartition 1.36
-// against 1.25.
+// against 1.25. So do those of jobs that would be left with fewer than 64
+// sub-chunks (10,000 samples on 4 workers, 5 epochs: prefetch tiles 16 -> 40 us).
 inline void fold_epochs(SegParams& p) {
-  if (p.L > kSC / 2 || p.M_max == 0) return;
-  p.nsc = int32_t(ceil_div(p.M_max, kSC));
+  const int64_t nsc = ceil_div(p.M_max, kSC);
+  if (p.L > kSC / 2 || p.N * nsc < 64) return;
+  p.nsc = int32_t(nsc);
   p.emul = p.E;
   p.E = 1;
 }
@@ -188,7 +190,7 @@ inline int run_lanes(const SegParams& p, int threads) {
   const double m = run_mean(p);
   const int64_t runs = int64_t(p.E) * p.nsc;
   int l = 1;
-  while (l < 64 && (l * kRunBatch < m || (2 * l * runs <= threads && l < m))) l *= 2;
+  while (2 * l <= threads && (l * kRunBatch < m || (2 * l * runs <= threads && l < m))) l *= 2;
   return l;
 }
 
@@ -196,7 +198,7 @@ inline int run_lanes(const SegParams& p, int threads) {
 // stream position of the run's sub-chunk, q the read's index in the
 // sub-chunk's partitioned entries (its partitioned position is fb + q) and v
 // the packed read. `lanes` consecutive threads of the workgroup share a run
-// (a power of two, at most 64).
+// (a power of two, at most NT).
 template <int NT, typename Fn>
 __device__ __forceinline__ void walk_runs(const SegParams& p, int64_t i, uint32_t kb,
                                           const uint32_t* __restrict__ Pk,

@@ -55,6 +55,16 @@ constexpr int kChunkRounds = NOPFS_CHUNK_ROUNDS;           // smallest chunk, in
 constexpr uint32_t kMaxChunks = 2048;                      // chunks per epoch (sort's run table)
 constexpr uint32_t kMaxWin = 4096;                         // buckets per pass
 constexpr int64_t kMeanBucket = 7700;                      // largest mean bucket size
+// Small jobs. With the sizes above, 10,000 ids and 5 epochs are 5 chunks to
+// scatter, whose counts all fall on one LDS word, and 10 buckets to sort: a few
+// workgroups and a serial chain of LDS atomics. Smaller chunks and buckets:
+// scatter 27 -> 12, sort 17 -> 11 us; 70,003 ids x 3 epochs: scatter 23 -> 13,
+// sort 20 -> 21; the whole stream of 400,000 ids (17 full chunks) 45 -> 33 us,
+// of 1,000,003 (41) 48 both ways, of 700,000 x 3 (87) 57 -> 60, of 3,000,000
+// (123) 71 -> 94.
+constexpr int64_t kSmallBucket = 512, kFewBuckets = 512;
+constexpr int kSmallBlocks = 2;
+constexpr int64_t kSmallChunk = kThreads * 4 * kSmallBlocks, kFewChunks = 48;
 constexpr int kBlkShift = 3;                               // run-table lookup granularity
 
 #ifndef NOPFS_SORT_CAP
@@ -72,7 +82,7 @@ struct StreamParams {
   uint32_t m;        // log2 of the buckets per epoch
   uint32_t wb0;      // first bucket of this pass
   uint32_t nbw;      // buckets of this pass
-  uint32_t C;        // ids per chunk (a multiple of kRound)
+  uint32_t C;        // ids per chunk (a multiple of kRound, or kSmallChunk)
   uint32_t cbits;    // C <= 2^cbits
   uint32_t nchunks;  // chunks per epoch
   int32_t e0;        // epoch of the batch's first keys
@@ -201,22 +211,24 @@ stream_scan(uint32_t nbw, const uint32_t* __restrict__ tot, uint32_t* __restrict
 }
 
 // -- 4. scatter ------------------------------------------------------------------
-// One workgroup per (chunk, epoch). Per round of kRound ids (the larger the
+// One workgroup per (chunk, epoch). Per round of kR ids (the larger the
 // round, the longer each bucket's run and the fewer partly written cache
 // lines: 24,576 ids take 126 KB of LDS, one workgroup per CU, which measured
 // 1.54 ms at ImageNet-22k against 1.82 ms for 12,288-id rounds at two per
-// CU): the pass's keys
+// CU; of few chunks, rounds of 8,192): the pass's keys
 // are counting-sorted by bucket in LDS (16-bit counts, two per word) and
 // written as words, consecutive threads on consecutive positions; the bucket
 // of staged position q is found from a table of the bucket at every 8th
 // position and a short forward walk over the bucket starts.
+template <int kBlocks>
 __global__ void __launch_bounds__(kThreads)
 stream_scatter(StreamParams p, const uint32_t* __restrict__ wst, const uint32_t* __restrict__ offc,
                uint32_t* __restrict__ words) {
-  __shared__ uint32_t stage[kRound];                      // staged words
+  constexpr int kR = kThreads * 4 * kBlocks;              // ids per round
+  __shared__ uint32_t stage[kR];                          // staged words
   __shared__ uint32_t cntw[kMaxWin / 2 + 1];              // 16-bit counts / starts
   __shared__ int32_t dl[kMaxWin];                         // run position - start, per bucket
-  __shared__ uint16_t blk[kRound >> kBlkShift];           // bucket at every 8th position
+  __shared__ uint16_t blk[kR >> kBlkShift];               // bucket at every 8th position
   __shared__ uint32_t tmp[65];
   const uint32_t nbw = p.nbw;
   uint16_t* c16 = reinterpret_cast<uint16_t*>(cntw);      // bucket b at [b]
@@ -238,14 +250,14 @@ stream_scatter(StreamParams p, const uint32_t* __restrict__ wst, const uint32_t*
     dlv[m] = int32_t(st[bc] + oc[bc]);
   }
   const int64_t id_chunk = int64_t(chunk) * p.C;
-  for (int64_t r0 = id_chunk; r0 < id_chunk + p.C && r0 < p.F; r0 += kRound) {
+  for (int64_t r0 = id_chunk; r0 < id_chunk + p.C && r0 < p.F; r0 += kR) {
     for (uint32_t x = threadIdx.x; x < (nbw + 2) / 2; x += kThreads) cntw[x] = 0;
     __syncthreads();
     // per id: its word, and its bucket and slot packed as b << 16 | slot
-    // (b < 4096, slot < kRound), or ~0 when the id is not in this pass
-    uint32_t wd[kRoundBlocks][4], bs[kRoundBlocks][4];
+    // (b < 4096, slot < kR), or ~0 when the id is not in this pass
+    uint32_t wd[kBlocks][4], bs[kBlocks][4];
 #pragma unroll
-    for (int it = 0; it < kRoundBlocks; ++it) {
+    for (int it = 0; it < kBlocks; ++it) {
       const int64_t blk4 = r0 / 4 + it * kThreads + threadIdx.x;
       const int64_t id0 = blk4 * 4;
       const Philox4 r = philox_block(uint32_t(blk4), e, p.seed_lo, p.seed_hi);
@@ -291,7 +303,7 @@ stream_scatter(StreamParams p, const uint32_t* __restrict__ wst, const uint32_t*
     __syncthreads();
     if (threadIdx.x == 0) c16[nbw] = uint16_t(total);
 #pragma unroll
-    for (int it = 0; it < kRoundBlocks; ++it)
+    for (int it = 0; it < kBlocks; ++it)
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         if (bs[it][c] != 0xFFFFFFFFu) stage[c16[bs[it][c] >> 16] + (bs[it][c] & 0xFFFFu)] = wd[it][c];
@@ -401,9 +413,9 @@ constexpr int kSortDigits = 1 << kSortDigitBits;
 constexpr int kCountWords = kSortDigits / 2;
 constexpr uint32_t kSlotBits = 13;  // bits of a counting-sort slot
 static_assert(kSortCap <= (1 << kSlotBits), "slots fit kSlotBits");
-// kb has 32 - cbits bits and C >= kRound, so cbits >= kSlotBits and
+// kb has 32 - cbits bits and C >= kSmallChunk, so cbits >= kSlotBits and
 // kb << kSlotBits | slot fits 32 bits
-static_assert((1 << kSlotBits) <= kRound, "kb and slot fit one word");
+static_assert((1 << kSlotBits) <= kSmallChunk && kSmallChunk <= kRound, "kb and slot fit one word");
 static_assert(kMaxChunks + 1 + (kSortCap >> kBlkShift) / 2 <= kCountWords,
               "the run table fits the digit counts' space");
 
@@ -702,10 +714,15 @@ int streams_impl(const nopfs_job* job, int32_t* R, hipStream_t st, int32_t e_beg
   // 2^m buckets per epoch, the fewest with a mean of at most kMeanBucket
   uint32_t m = 0;
   while (m < 31 && (s.F >> m) > kMeanBucket) ++m;
+  // a job of few buckets: smaller ones (of more than 512 keys), until there are
+  // two per compute unit to sort
+  while ((s.F >> m) > 2 * kSmallBucket && (s.E << m) < kFewBuckets) ++m;
   const uint32_t nb = 1u << m;
   const uint32_t nbw = nb < kMaxWin ? nb : kMaxWin;
   // chunks: multiples of a scatter round, at most kMaxChunks per epoch
+  // (of the smaller round where there would be only a few)
   int64_t C = int64_t(kRound) * kChunkRounds;
+  if (s.E * ceil_div(s.F, C) < kFewChunks) C = kSmallChunk;
   while (ceil_div(s.F, C) > int64_t(kMaxChunks)) C *= 2;
   uint32_t cbits = 0;
   while ((int64_t(1) << cbits) < C) ++cbits;
@@ -755,8 +772,10 @@ int streams_impl(const nopfs_job* job, int32_t* R, hipStream_t st, int32_t e_beg
       if ((rc = launch("stream_scan", stream_scan, dim3(eb), dim3(1024), 0, st, nbw,
                        (const uint32_t*)tot, wst, wpos, wbase)))
         return rc;
-      if ((rc = launch("stream_scatter", stream_scatter, dim3(xcd_padded(nchunks), eb),
-                       dim3(kThreads), 0, st, p, (const uint32_t*)wst,
+      if ((rc = launch("stream_scatter",
+                       C < kRound ? stream_scatter<kSmallBlocks> : stream_scatter<kRoundBlocks>,
+                       dim3(xcd_padded(nchunks), eb), dim3(kThreads), 0, st, p,
+                       (const uint32_t*)wst,
                        (const uint32_t*)cnt, words)))
         return rc;
       if ((rc = launch("stream_sort", stream_sort, dim3(xcd_padded(nbw), eb), dim3(kThreads),
