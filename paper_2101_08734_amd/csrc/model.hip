@@ -13,7 +13,7 @@
 // worker consumes it at
 //   t(f) = max(avail(f), t(f-1) + s(f-1) / c) = U(f) + max over g <= f of (avail(g) - U(g)),
 // U(f) = sum of s(m) / c over m < f (the recurrence unrolled): a prefix sum
-// and a prefix maximum, evaluated per sub-chunk and combined per worker.
+// and a prefix maximum, evaluated per sub-chunk and chained along the worker's row.
 //
 //   fm_holders -- per sample: the best remote class among all workers'
 //                 copies (highest min(b_c, r_j / p_j), lower tier on ties),
@@ -25,14 +25,12 @@
 //                 reads, cut into spans of 2^14): each read's source from
 //                 its own tier and the sample's best remote class; size and
 //                 source in partitioned order.
-//   fm_sum     -- per span of 2^14 reads: every entry loaded once into
-//                 the LDS slot of its stream position (the whole sub-chunk,
-//                 135 KB), then scanned in four parts of 4,096 positions:
+//   fm_final   -- per span of 2^14 reads: every entry loaded once into the LDS
+//                 slot of its stream position (the whole sub-chunk, 135 KB);
 //                 its read-time sum, compute-time sum and maximum of
-//                 avail - U relative to its start.
-//   fm_scan    -- per worker: what enters each span.
-//   fm_final   -- per span: the same scans, combined with what enters
-//                 it; source codes and consumption times in stream order.
+//                 avail - U are scanned and published, what enters it is
+//                 chained from the spans before; source codes and consumption
+//                 times in stream order.
 #include <math.h>
 
 #include <new>
@@ -43,19 +41,14 @@
 namespace nopfs {
 namespace {
 
-#ifndef NOPFS_FM_THREADS
-#define NOPFS_FM_THREADS 1024  // threads of the scan kernels (tuning only)
-#endif
-
 constexpr int kMaxClasses = 32;
 constexpr uint32_t kNoClass = 255;
 constexpr int kSizeBits = 56;
 constexpr uint64_t kSizeMask = (uint64_t(1) << kSizeBits) - 1;
-constexpr int kFmThreads = NOPFS_FM_THREADS;
-constexpr int kFmPart = kSC / 4;                // positions per LDS pass
-constexpr int kFmPer = kFmPart / kFmThreads;    // positions per thread and pass
-constexpr int kFmEnt = kSC / kFmThreads;        // entries per thread
-static_assert(kFmPer * kFmThreads == kFmPart && kFmEnt * kFmThreads == kSC, "fm shape");
+constexpr int kFmThreads = 1024;
+constexpr int kFmPer = kSC / kFmThreads;        // positions (and entries) per thread
+constexpr uint32_t kFmBlocks = 256;             // workgroups in flight: one per CU
+static_assert(kFmPer == 16, "16 consecutive positions stay within one pad of fm_slot");
 
 // Source codes inside the library: 0 the PFS, 1 + j another worker's tier j,
 // 1 + kMaxClasses + j the worker's own tier j.
@@ -70,8 +63,8 @@ struct Rates {
   double c, p0;
   // reciprocals for the per-read times (a product instead of a division:
   // within two units in the last place of the quotient)
-  double inv_own[kMaxClasses], inv_rem[kMaxClasses];
-  double inv_pfs, inv_wthr, inv_c;
+  double inv[1 + 2 * kMaxClasses];  // by source code
+  double inv_wthr, inv_c;
   int32_t J;
   uint8_t rank_cls[kMaxClasses];  // classes by remote rate, best first, lower tier on ties
   uint8_t cls_rank[kMaxClasses];  // the inverse
@@ -79,7 +72,7 @@ struct Rates {
 
 struct SharedRates {
   double own[kMaxClasses], rem[kMaxClasses];
-  double inv_own[kMaxClasses], inv_rem[kMaxClasses];
+  double inv[1 + 2 * kMaxClasses];
   uint8_t rank_cls[kMaxClasses], cls_rank[kMaxClasses];
 };
 
@@ -87,26 +80,24 @@ __device__ __forceinline__ void load_rates(const Rates& r, SharedRates& s) {
   if (threadIdx.x < kMaxClasses) {
     s.own[threadIdx.x] = r.own[threadIdx.x];
     s.rem[threadIdx.x] = r.rem[threadIdx.x];
-    s.inv_own[threadIdx.x] = r.inv_own[threadIdx.x];
-    s.inv_rem[threadIdx.x] = r.inv_rem[threadIdx.x];
     s.rank_cls[threadIdx.x] = r.rank_cls[threadIdx.x];
     s.cls_rank[threadIdx.x] = r.cls_rank[threadIdx.x];
   }
-}
-
-// 1 / (the rate of a source code)
-__device__ __forceinline__ double inv_rate_of(const Rates& r, const SharedRates& s, uint32_t code) {
-  return code == 0 ? r.inv_pfs : (code < kOwn0 ? s.inv_rem[code - 1] : s.inv_own[code - kOwn0]);
+  for (uint32_t x = threadIdx.x; x < 1 + 2 * kMaxClasses; x += blockDim.x) s.inv[x] = r.inv[x];
 }
 
 // ---------------------------------------------------------------- holders --
 __global__ void __launch_bounds__(256)
 fm_holders(int64_t F, int64_t N, const int8_t* __restrict__ tier, const int64_t* __restrict__ sizes,
-           Rates rt, uint64_t* __restrict__ szb) {
+           Rates rt, uint64_t* __restrict__ szb, uint64_t* __restrict__ state, int64_t nstate,
+           uint32_t* __restrict__ ticket) {
   __shared__ SharedRates sr;
   load_rates(rt, sr);
   __syncthreads();
   const int64_t k = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  // the spans' states and the ticket of the last kernel
+  for (int64_t x = k; x < nstate; x += int64_t(gridDim.x) * 256) state[x] = ~uint64_t(0);
+  if (k == 0) *ticket = 0;
   if (k >= F) return;
   uint32_t best = kNoClass;  // as a rank: lower is better
   constexpr int kRows = 8;
@@ -245,44 +236,110 @@ __device__ __forceinline__ double block_excl_max(double v, double* tmp, double* 
   return fmax(tmp[wave], lane == 0 ? -INFINITY : before_lane);
 }
 
-// LDS slot of position p: one pad per 32 positions, so the four
-// consecutive positions each thread takes fall on distinct banks across a
-// half-wave
+// LDS slot of position p: one pad per 32 positions, so the 16 consecutive
+// positions each thread takes fall on distinct banks across a half-wave
 __device__ __forceinline__ int fm_slot(int p) { return p + (p >> 5); }
 
-struct FmLds {
-  uint64_t sv[kSC + kSC / 32];  // the span's entries by position, then results
-  double2 tmp2[65];             // the two sum scans
-  double tmpm[65];              // the maximum scan
-  uint16_t code[kFmPart + kFmPart / 32];  // a part's source codes for the transpose
-  SharedRates sr;
-};
-
-// What enters sub-chunk c of worker i: read-time sum and compute-time sum
-// of the reads before it, and the largest avail(g) - U(g) over them.
+// What enters a span of worker i: read-time sum and compute-time sum of the
+// reads before it, and the largest avail(g) - U(g) over them. A span's own
+// sums have the same form, relative to its start.
 struct Enter {
   double a, u, m;
 };
 
-// One sub-chunk in stream order: per position, its code and the scans.
-// kFinal: also the consumption times t and source codes, written out.
+// `in` followed by a span with the sums `x`
+__device__ __forceinline__ Enter fm_then(const Enter& in, const Enter& x, double inv_p0) {
+  return Enter{in.a + x.a, in.u + x.u, fmax(in.m, in.a * inv_p0 - in.u + x.m)};
+}
+
+// What a span publishes: its own sums as soon as they are known, then what
+// leaves it. Each word is valid by itself once it is no longer all ones (a
+// NaN that no arithmetic makes), so no fence goes with it.
+struct FmState {
+  uint64_t own[3], out[3];
+};
+constexpr uint64_t kFmUnset = ~uint64_t(0);
+
+__device__ __forceinline__ void fm_publish(uint64_t (&w)[3], const Enter& e) {
+  const double d[3] = {e.a, e.u, e.m};
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const uint64_t b = uint64_t(__double_as_longlong(d[k]));
+    __hip_atomic_store(&w[k], b == kFmUnset ? b - 1 : b, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+__device__ __forceinline__ bool fm_read(const uint64_t (&w)[3], Enter& e) {
+  uint64_t b[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    b[k] = __hip_atomic_load(&w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  e = Enter{__longlong_as_double(int64_t(b[0])), __longlong_as_double(int64_t(b[1])),
+            __longlong_as_double(int64_t(b[2]))};
+  return b[0] != kFmUnset && b[1] != kFmUnset && b[2] != kFmUnset;
+}
+
+// What enters span c of a row (one whole wave): lane l looks at span
+// c - 1 - l; from the nearest span whose output is there, the own sums of
+// those after it are added in span order, so the result is that of the
+// sequential sum whichever span that was. The wait ends: every span before
+// this one was taken earlier by a running workgroup, and publishes its own
+// sums before it waits for anything.
+__device__ Enter fm_enter(const FmState* row, int64_t c, double inv_p0) {
+  const int64_t q = c - 1 - __lane_id();
+  for (;;) {
+    Enter own{0, 0, 0}, out{0, 0, -INFINITY};
+    bool has_own = false, has_out = q == -1;  // nothing enters the row's first span
+    if (q >= 0) {
+      has_own = fm_read(row[q].own, own);
+      has_out = fm_read(row[q].out, out);
+    }
+    const uint64_t mo = __ballot(has_out), mw = __ballot(has_own);
+    if (mo) {
+      const int f = __ffsll(static_cast<unsigned long long>(mo)) - 1;
+      const uint64_t need = (uint64_t(1) << f) - 1;
+      if ((mw & need) == need) {
+        Enter e{__shfl(out.a, f, 64), __shfl(out.u, f, 64), __shfl(out.m, f, 64)};
+        for (int l = f - 1; l >= 0; --l)
+          e = fm_then(e, Enter{__shfl(own.a, l, 64), __shfl(own.u, l, 64), __shfl(own.m, l, 64)},
+                      inv_p0);
+        return e;
+      }
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+}
+
+struct FmLds {
+  uint64_t sv[kSC + kSC / 32];  // the span's entries by position, then the times
+  uint32_t code[kSC / 4];       // source codes by position, a byte each
+  double2 tmp2[65];             // the two sum scans
+  double tmpm[65];              // the maximum scan
+  Enter in;
+  uint32_t ticket;
+  SharedRates sr;
+};
+
 // A span's entries as loaded by one thread: entries t, t + kFmThreads, ...
 // of its partitioned order (packed position, size and source). The loads
 // are unconditional (past the span's end they read its first entry and are
 // dropped when stored), so they are in flight together.
 struct FmRegs {
-  uint32_t j[kFmEnt];
-  uint64_t v[kFmEnt];
+  uint32_t j[kFmPer];
+  uint64_t v[kFmPer];
 };
 
 __device__ __forceinline__ void fm_load(const SubChunk& s, const uint32_t* __restrict__ Pk,
-                                        const uint64_t* __restrict__ zP, bool valid, FmRegs& g) {
-  const int64_t base = valid ? s.base : 0, len = valid ? s.len : 0;
+                                        const uint64_t* __restrict__ zP, FmRegs& g) {
+  const uint32_t* pk = Pk + s.base;
+  const uint64_t* z = zP + s.base;
+  const uint32_t len = uint32_t(s.len);
 #pragma unroll
-  for (int u = 0; u < kFmEnt; ++u) {
-    const int64_t q = int64_t(u) * kFmThreads + threadIdx.x;
-    g.j[u] = Pk[base + (q < len ? q : 0)];
-    g.v[u] = zP[base + (q < len ? q : 0)];
+  for (int u = 0; u < kFmPer; ++u) {
+    const uint32_t q = uint32_t(u) * kFmThreads + threadIdx.x;
+    g.j[u] = pk[q < len ? q : 0];
+    g.v[u] = z[q < len ? q : 0];
   }
 }
 
@@ -290,149 +347,137 @@ __device__ __forceinline__ void fm_load(const SubChunk& s, const uint32_t* __res
 // with a barrier.
 __device__ __forceinline__ void fm_place(const SubChunk& s, const FmRegs& g, FmLds& L) {
 #pragma unroll
-  for (int u = 0; u < kFmEnt; ++u)
-    if (int64_t(u) * kFmThreads + threadIdx.x < s.len) L.sv[fm_slot(int(g.j[u] & kJMask))] = g.v[u];
+  for (int u = 0; u < kFmPer; ++u)
+    if (uint32_t(u) * kFmThreads + threadIdx.x < uint32_t(s.len)) L.sv[fm_slot(int(g.j[u] & kJMask))] = g.v[u];
   __syncthreads();
 }
 
-// One span in stream order, its entries in L.sv: per position, its code
-// and the scans. kFinal: also the consumption times t and source codes,
-// written out. Ends with a barrier.
-template <bool kFinal>
-__device__ void fm_chunk(const SegParams& p, const SubChunk& s, const Rates& rt, FmLds& L,
-                         Enter in, Enter* sum_out, int16_t* __restrict__ src,
-                         double* __restrict__ tout) {
-  const double inv_p0 = 1.0 / rt.p0;
-  double ca = 0, cu = 0, cm = -INFINITY;  // running over the parts, relative to the chunk
-  const double base_mu = in.a * inv_p0 - in.u;
-  for (int64_t j0 = 0; j0 < s.len; j0 += kFmPart) {
-    const uint32_t hl = uint32_t(s.len - j0 < kFmPart ? s.len - j0 : kFmPart);
-    const int jb = int(j0);
-    double rd[kFmPer], uu[kFmPer];
-    uint32_t cd[kFmPer];
-    double ta = 0, tu = 0;
-#pragma unroll
-    for (int u = 0; u < kFmPer; ++u) {
-      const int x = int(threadIdx.x) * kFmPer + u;
-      rd[u] = 0;
-      uu[u] = 0;
-      cd[u] = 0;
-      if (x < int(hl)) {
-        const uint64_t e = L.sv[fm_slot(jb + x)];
-        const double sz = double(e & kSizeMask);
-        cd[u] = uint32_t(e >> kSizeBits);
-        rd[u] = sz * inv_rate_of(rt, L.sr, cd[u]) + sz * rt.inv_wthr;
-        uu[u] = sz * rt.inv_c;
-      }
-      ta += rd[u];
-      tu += uu[u];
-    }
-    double tota, totu, exa, exu;
-    block_excl_sum2(ta, tu, L.tmp2, &exa, &exu, &tota, &totu);
-    // avail - U at each position, relative to the chunk start
-    double mv[kFmPer];
-    double ra = ca + exa, ru = cu + exu, tm = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < kFmPer; ++u) {
-      const int x = int(threadIdx.x) * kFmPer + u;
-      ra += rd[u];
-      mv[u] = x < int(hl) ? ra * inv_p0 - ru : -INFINITY;
-      ru += uu[u];
-      tm = fmax(tm, mv[u]);
-    }
-    double totm;
-    const double exm = block_excl_max(tm, L.tmpm, &totm);
-    if (kFinal) {
-      // t at each position: U(f) + max(what entered, base + best so far)
-      double tv[kFmPer];
-      double run = fmax(cm, exm);
-      double uf = cu + exu;
-#pragma unroll
-      for (int u = 0; u < kFmPer; ++u) {
-        run = fmax(run, mv[u]);
-        tv[u] = (in.u + uf) + fmax(in.m, base_mu + run);
-        uf += uu[u];
-      }
-      // t into the slots this thread read its entries from, codes into their
-      // own table; one barrier, then both go out in stream order
-#pragma unroll
-      for (int u = 0; u < kFmPer; ++u) {
-        const int x = int(threadIdx.x) * kFmPer + u;
-        L.sv[fm_slot(jb + x)] = __double_as_longlong(tv[u]);
-        const uint32_t c = cd[u];
-        L.code[fm_slot(x)] = uint16_t(c == 0 ? 0u : (c < kOwn0 ? 128u + (c - 1) : 256u + (c - kOwn0)));
-      }
-      __syncthreads();
-      double* td = tout + s.base + j0;
-      int16_t* sd = src + s.base + j0;
-#pragma unroll
-      for (int u = 0; u < kFmPer; ++u) {
-        const int x = u * kFmThreads + int(threadIdx.x);
-        if (x < int(hl)) {
-          stream_store(td + x, __longlong_as_double(L.sv[fm_slot(jb + x)]));
-          stream_store(sd + x, int16_t(L.code[fm_slot(x)]));
-        }
-      }
-    }
-    ca += tota;
-    cu += totu;
-    cm = fmax(cm, totm);
-    __syncthreads();
-  }
-  if (!kFinal && threadIdx.x == 0) *sum_out = Enter{ca, cu, cm};
-}
-
-// One workgroup per span and per CU (the span takes 135 KB of LDS).
-// Walking several spans per workgroup with the next span's entries requested
-// during the scan needs 48 more registers than the scan leaves: the spills
-// made it slower (3.0 and 5.2 ms against 2.8 and 3.7).
-__global__ void __launch_bounds__(kFmThreads)
-fm_sum(SegParams p, const uint32_t* __restrict__ Pk, const uint64_t* __restrict__ zP, Rates rt,
-       uint32_t nch, Enter* __restrict__ sums) {
-  __shared__ FmLds L;
-  load_rates(rt, L.sr);
-  const SubChunk s = sub_chunk(p, nch, blockIdx.x);
-  FmRegs g;
-  fm_load(s, Pk, zP, true, g);
-  fm_place(s, g, L);  // its barrier also publishes the rates
-  fm_chunk<false>(p, s, rt, L, Enter{0, 0, 0}, &sums[s.i * nch + s.c], nullptr, nullptr);
-}
-
-// In place: sums[i][c] becomes what enters sub-chunk c.
-__global__ void __launch_bounds__(256)
-fm_scan(int64_t N, uint32_t nch, double p0, Enter* __restrict__ sums) {
-  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= N) return;
-  Enter* row = sums + i * nch;
-  const double inv_p0 = 1.0 / p0;
-  double a = 0, u = 0, m = -INFINITY;
-  for (uint32_t c = 0; c < nch; ++c) {
-    const Enter x = row[c];
-    row[c] = Enter{a, u, m};
-    m = fmax(m, a * inv_p0 - u + x.m);
-    a += x.a;
-    u += x.u;
-  }
-}
-
+// One workgroup per CU (the span takes 135 KB of LDS) takes spans by ticket, in
+// order of their place in the row (the first of every row, then the second,
+// ...), so that what enters a span is mostly there when it is asked for.
+// Bound by HBM: at ImageNet-22k 6.8 GB of entries in, 5.7 GB of times and codes
+// out in 3.6 ms (3.4 TB/s); the rest is the scan, when nothing is in flight.
+// One kernel for the spans' sums, one that chained them per row and a last one
+// that read the entries again took 2.72 + 0.15 + 3.64 ms. Positions go 16 to a
+// thread, so the span is scanned once (six barriers), and the next span's
+// entries are requested while this one goes out; a thread's times are looked
+// up by each sweep, as holding them (64 registers) spills.
 __global__ void __launch_bounds__(kFmThreads)
 fm_final(SegParams p, const uint32_t* __restrict__ Pk, const uint64_t* __restrict__ zP, Rates rt,
-         uint32_t nch, const Enter* __restrict__ ins, int16_t* __restrict__ src,
-         double* __restrict__ t) {
+         uint32_t nch, uint32_t nblk, FmState* state, uint32_t* ticket,
+         int16_t* __restrict__ src, double* __restrict__ t) {
   __shared__ FmLds L;
+  static_assert(sizeof(FmLds) <= 160 * 1024, "one span fits the LDS");
   load_rates(rt, L.sr);
-  const SubChunk s = sub_chunk(p, nch, blockIdx.x);
+  const double inv_p0 = 1.0 / rt.p0;
+  if (threadIdx.x == 0) L.ticket = atomicAdd(ticket, 1u);
+  __syncthreads();
+  uint32_t b = uint32_t(__builtin_amdgcn_readfirstlane(int(L.ticket)));
+  const uint32_t rows = uint32_t(p.N);
+  SubChunk s;
   FmRegs g;
-  fm_load(s, Pk, zP, true, g);
-  if (s.c == int64_t(nch) - 1) {
-    // the row's padding past its last read
-    for (int64_t f = int64_t(p.E) * s.Li + threadIdx.x; f < p.M_max; f += kFmThreads) {
-      src[s.i * p.M_max + f] = -1;
-      t[s.i * p.M_max + f] = -1.0;
-    }
+  if (b < nblk) {
+    s = sub_chunk(p, nch, b % rows * nch + b / rows);
+    fm_load(s, Pk, zP, g);
   }
-  fm_place(s, g, L);
-  fm_chunk<true>(p, s, rt, L, ins[s.i * nch + s.c], nullptr, src, t);
+  while (b < nblk) {
+    if (s.c == int64_t(nch) - 1) {
+      // the row's padding past its last read
+      for (int64_t f = int64_t(p.E) * s.Li + threadIdx.x; f < p.M_max; f += kFmThreads) {
+        src[s.i * p.M_max + f] = -1;
+        t[s.i * p.M_max + f] = -1.0;
+      }
+    }
+    fm_place(s, g, L);
+    const int x0 = int(threadIdx.x) * kFmPer;
+    const int len = int(s.len);
+    uint64_t* mine = L.sv + fm_slot(x0);  // its slots: consecutive (16 of 32)
+    // read and compute time of a position of this thread (0 past the span's end)
+    auto times = [&](int u, double& rd, double& uu) {
+      const uint64_t e = mine[u];
+      const double sz = x0 + u < len ? double(e & kSizeMask) : 0.0;
+      const uint32_t code = x0 + u < len ? uint32_t(e >> kSizeBits) : 0u;
+      rd = sz * L.sr.inv[code] + sz * rt.inv_wthr;
+      uu = sz * rt.inv_c;
+      return code;
+    };
+    double ta = 0, tu = 0;
+#pragma unroll 1
+    for (int u0 = 0; u0 < kFmPer; u0 += 4) {
+      uint32_t cw = 0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        double rd, uu;
+        cw |= times(u0 + v, rd, uu) << (8 * v);
+        ta += rd;
+        tu += uu;
+      }
+      L.code[(x0 + u0) / 4] = cw;
+    }
+    Enter own;
+    double exa, exu;
+    block_excl_sum2(ta, tu, L.tmp2, &exa, &exu, &own.a, &own.u);
+    // avail - U at each position, relative to the span's start. A position's
+    // sums are the thread's own (small) plus what precedes them: one rounding
+    // at the sums' size per position, not one per read of the thread.
+    double la = 0, lu = 0, tm = -INFINITY;
+#pragma unroll 4
+    for (int u = 0; u < kFmPer; ++u) {
+      double rd, uu;
+      times(u, rd, uu);
+      la += rd;
+      if (x0 + u < len) tm = fmax(tm, (exa + la) * inv_p0 - (exu + lu));
+      lu += uu;
+    }
+    double run = block_excl_max(tm, L.tmpm, &own.m);
+    if (threadIdx.x < 64) {
+      FmState* row = state + s.i * nch;
+      if (threadIdx.x == 0) fm_publish(row[s.c].own, own);
+      const Enter in = fm_enter(row, s.c, inv_p0);
+      if (threadIdx.x == 0) {
+        fm_publish(row[s.c].out, fm_then(in, own, inv_p0));
+        L.in = in;
+        L.ticket = atomicAdd(ticket, 1u);
+      }
+    }
+    __syncthreads();
+    const Enter in = L.in;
+    const double base_mu = in.a * inv_p0 - in.u;
+    // t at each position: U(f) + max(what entered, base + best so far), into
+    // the slots this thread read its entries from
+    la = lu = 0;
+#pragma unroll 4
+    for (int u = 0; u < kFmPer; ++u) {
+      double rd, uu;
+      times(u, rd, uu);
+      la += rd;
+      const double ru = exu + lu;
+      run = fmax(run, (exa + la) * inv_p0 - ru);
+      mine[u] = uint64_t(__double_as_longlong((in.u + ru) + fmax(in.m, base_mu + run)));
+      lu += uu;
+    }
+    const uint32_t b2 = uint32_t(__builtin_amdgcn_readfirstlane(int(L.ticket)));
+    __syncthreads();
+    // the next span's entries are requested before this one goes out
+    const SubChunk d = s;
+    if (b2 < nblk) {
+      s = sub_chunk(p, nch, b2 % rows * nch + b2 / rows);
+      fm_load(s, Pk, zP, g);
+    }
+    const uint8_t* code = reinterpret_cast<const uint8_t*>(L.code);
+#pragma unroll 4
+    for (int u = 0; u < kFmPer; ++u) {
+      const int x = u * kFmThreads + int(threadIdx.x);
+      if (x < len) {
+        const uint32_t c = code[x];
+        stream_store(t + d.base + x, __longlong_as_double(int64_t(L.sv[fm_slot(x)])));
+        stream_store(src + d.base + x,
+                     int16_t(c == 0 ? 0u : (c < kOwn0 ? 128u + (c - 1) : 256u + (c - kOwn0))));
+      }
+    }
+    b = b2;
+    __syncthreads();
+  }
 }
 
 Rates make_rates(const nopfs_model* m) {
@@ -448,10 +493,10 @@ Rates make_rates(const nopfs_model* m) {
   r.c = m->c;
   r.p0 = m->p0;
   for (int32_t j = 0; j < kMaxClasses; ++j) {
-    r.inv_own[j] = j < m->J ? 1.0 / r.own[j] : 0;
-    r.inv_rem[j] = j < m->J ? 1.0 / r.rem[j] : 0;
+    r.inv[1 + j] = j < m->J ? 1.0 / r.rem[j] : 0;
+    r.inv[kOwn0 + j] = j < m->J ? 1.0 / r.own[j] : 0;
   }
-  r.inv_pfs = 1.0 / r.pfs;
+  r.inv[0] = 1.0 / r.pfs;
   r.inv_wthr = 1.0 / r.wthr;
   r.inv_c = 1.0 / r.c;
   // classes ranked by remote rate (higher first), lower tier on ties
@@ -498,26 +543,25 @@ int model_impl(const nopfs_job* job, const int32_t* R, const int8_t* tier, const
   uint64_t *szb, *zP;
   uint32_t* Pk;
   uint16_t* OT;
-  Enter* sums;
+  FmState* state;
+  uint32_t* ticket;
   if ((rc = scr.alloc_n(&szb, size_t(s.F)))) return rc;
   if ((rc = run_partition(p, R, scr, &Pk, &OT, st))) return rc;
   if ((rc = scr.alloc_n(&zP, size_t(s.N * s.M_max)))) return rc;
-  if ((rc = scr.alloc_n(&sums, size_t(nblk)))) return rc;
+  if ((rc = scr.alloc_n(&state, size_t(nblk)))) return rc;
+  if ((rc = scr.alloc_n(&ticket, 1))) return rc;
   if ((rc = launch("fm_holders", fm_holders, dim3(uint32_t(ceil_div(s.F, 256))), dim3(256), 0, st,
-                   s.F, s.N, tier, sizes, rt, szb)))
+                   s.F, s.N, tier, sizes, rt, szb, reinterpret_cast<uint64_t*>(state),
+                   nblk * int64_t(sizeof(FmState) / 8), ticket)))
     return rc;
   if ((rc = launch("fm_gather", fm_gather, dim3(xcd_padded(uint32_t(ntiles))), dim3(kGThreads), 0,
                    st, p, (const uint32_t*)Pk, (const uint16_t*)OT, tier, (const uint64_t*)szb, rt,
                    zP, ngroups, per, uint32_t(ntiles))))
     return rc;
-  if ((rc = launch("fm_sum", fm_sum, dim3(uint32_t(nblk)), dim3(kFmThreads), 0, st, p,
-                   (const uint32_t*)Pk, (const uint64_t*)zP, rt, nch, sums)))
-    return rc;
-  if ((rc = launch("fm_scan", fm_scan, dim3(uint32_t(ceil_div(s.N, 256))), dim3(256), 0, st, s.N,
-                   nch, rt.p0, sums)))
-    return rc;
-  return launch("fm_final", fm_final, dim3(uint32_t(nblk)), dim3(kFmThreads), 0, st, p,
-                (const uint32_t*)Pk, (const uint64_t*)zP, rt, nch, (const Enter*)sums, src, t);
+  const uint32_t blocks = nblk < int64_t(kFmBlocks) ? uint32_t(nblk) : kFmBlocks;
+  return launch("fm_final", fm_final, dim3(blocks), dim3(kFmThreads), 0, st, p,
+                (const uint32_t*)Pk, (const uint64_t*)zP, rt, nch, uint32_t(nblk), state, ticket,
+                src, t);
 }
 
 }  // namespace
