@@ -133,9 +133,9 @@ POLICY_NAMES = ("perfect", "naive", "staging", "nopfs")
 BUFFER_NOTE = ("one workgroup per worker accepts its candidates batch by batch: bound by the "
                "batches' barriers and scans and by latency, not by HBM bandwidth; frac is the HBM "
                "fraction for reference")
-POLICY_NOTE = ("one workgroup per worker scans its chains chunk by chunk: bound by the random "
-               "gathers of the sizes and by instruction issue, not by HBM bandwidth; frac is the "
-               "HBM fraction for reference")
+POLICY_NOTE = ("one workgroup per worker scans its chains chunk by chunk: bound by the "
+               "128-byte lines that the random gathers of the sizes fetch and by instruction "
+               "issue, not by its algorithmic bytes; frac is their fraction for reference")
 
 
 def _kernel_short_name(full):
