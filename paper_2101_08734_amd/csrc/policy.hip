@@ -46,8 +46,10 @@
 //             ahead, sizes and far waits one), the Q scan and the y scan (one
 //             barrier each) and one barrier that finds the first read, if
 //             any, at which the scan stops. The t of this chunk and the one
-//             before stay in LDS for the waits. Where scans would stop early
-//             (windows of less than 512 reads, the first reads of a row), one
+//             before stay in LDS for the waits. The first reads of a row are
+//             stepped, 64 at a time, by three waves (the Q chain, the t chain
+//             one batch behind, the sums). Where scans would stop early
+//             (windows of less than 512 reads), one
 //             wave takes the chunk in scans of 64 reads without barriers, and
 //             steps reads one by one where even those stop within 8. The
 //             fetch-time sums by class are sums of the same kind (no maxima,
@@ -81,6 +83,18 @@ constexpr int64_t kPsUnits = 256;                     // compute units
 constexpr int kPsPer = 4;                             // reads per thread and chunk
 constexpr int kPsMinStep = 512;   // scans shorter than this, twice in a chunk: one wave goes on
 constexpr int kPsMinWave = 8;     // wave scans shorter than this: read by read
+// The first reads of a row are stepped: its values double every few reads, so
+// that scans stop at once (StagingBuffer, windows longer than the row: 656 reads
+// of one worker 72 us with scans from the first read, 31 stepped; 684 reads on
+// 4,096 workers 714 and 338). Up to 1,024 reads (768 of Naive, whose scans are cheaper;
+// none of Perfect, which scans a row of any length as fast as it steps it).
+// Fewer where one wave would go on with short windows anyway: with 256 threads
+// and windows of less than 512 reads 512 (rows of 2,048 to 4,096 reads on 300 to
+// 1,024 workers 5% faster than with 1,024), with windows of less than 128, whose
+// batches wait for each other, 256 (rows of 512 to 1,024 reads 20% faster).
+constexpr int kPsHead = 1024, kPsHeadNaive = 768, kPsHeadShort = 512, kPsHeadPrev = 256;
+// short scans of a row's first chunk before one wave goes on (of others: 2)
+constexpr int kPsShortsFirst = 8, kPsShorts = 2;
 constexpr int kPsMaxJ = 32;
 constexpr int kPsClasses = 1 + 2 * kPsMaxJ;           // PFS, remote j, own j
 constexpr int kPsCopies = 16;                         // partial sums per class in LDS
@@ -331,15 +345,18 @@ ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ siz
   };
 
   // marks the chunk at f0 when one of its reads waits for another (bit 0),
-  // and when one of its first reads does (bit 1)
+  // and when one of its first reads does (bit 1); of the row's first reads,
+  // when one waits for a read of its own 64 (bit 2) or of the 64 before (bit 3)
   auto mark_near = [&](int64_t f0, const int32_t fl[kPsPer]) {
-    bool near = false;
+    uint32_t near = 0;
 #pragma unroll
     for (int j = 0; j < kPsPer; ++j) {
       const int64_t f = f0 + kPsPer * tid + j;
-      near = near || (f < Mi && look(f, fl[j]) >= f0);
+      const int64_t g = f < Mi ? look(f, fl[j]) : -1, b = f & ~int64_t(63);
+      if (g >= f0) near |= kPsPer * tid < kPsMinStep ? 3u : 1u;
+      if (f0 == 0 && f < kPsHead && g >= 0) near |= g >= b ? 4u : (g >= b - 64 ? 8u : 0u);
     }
-    if (near) atomicOr(&s_near[(f0 / kPsChunk) & 1], kPsPer * tid < kPsMinStep ? 3u : 1u);
+    if (near) atomicOr(&s_near[(f0 / kPsChunk) & 1], near);
   };
   // each class's sum after the chunk from the chunk's units, or a mark that
   // the chunk's reads have to be added up in order (one wave)
@@ -360,13 +377,14 @@ ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ siz
     }
     return __ballot(any) != 0u;
   };
-  // the marked classes' fetch times of the chunk (st_f, st_c), in stream
-  // order (one wave): 64 at a time where the sum stays inside its binade
-  auto io_ordered = [&](int n) {
+  // the marked classes' fetch times of the chunk's reads from `from` on (st_f,
+  // st_c), in stream order (one wave): 64 at a time where the sum stays inside
+  // its binade
+  auto io_ordered = [&](int from, int n) {
     for (int c = 0; c < kCls; ++c) {
       if (io_bad[c] == 0u) continue;
       double x = double_of(io_x[c]);
-      for (int b = 0; b < n; b += 64) {
+      for (int b = from; b < n; b += 64) {
         const int at = b + lane;
         const double v = st_f[at];
         const bool on = at < n && (kPolicy != kNoPFS || st_c[at] == c);
@@ -390,6 +408,126 @@ ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ siz
   };
 
   double Q = 0.0, Y = 0.0;  // Q and y = t + u after the last read
+  // The row's first h reads, stepped 64 at a time from the staged terms: one
+  // wave takes the Q chain, a second the t chain of the 64 before, the last
+  // the sums by class. A batch that waits for the 64 before it (`prev`: there
+  // is one) gets its Q chain after they are in; none waits inside itself.
+  auto head = [&](int h, bool prev) {
+    const int nb = (h + 63) / 64;
+    // a batch's terms are requested from LDS before the barrier in front of it
+    int32_t gn = -1;
+    double wn = 0.0, rn = 0.0, un = 0.0, fn = 0.0;
+    int cn = 0;
+    auto request = [&](int b) {
+      const int x = b < h ? b + lane : lane;
+      if (kStaged && wave == 0) {
+        gn = st_g[x];
+        wn = st_w[x];
+        rn = st_rd[x];
+      }
+      if (wave == 1) {
+        un = st_u[x];
+        if (kPolicy == kNaive) rn = st_rd[x];
+      }
+      if (kIo && wave == kPsWaves - 1) {
+        fn = st_f[x];
+        if (kPolicy == kNoPFS) cn = st_c[x];
+      }
+    };
+    request(0);
+    auto q_chain = [&](int b) {
+      const double wl = gn >= 0 ? rt.p0 * ring[gn & (kRing - 1)] : wn;
+      const double rl = rn;
+      request(b + 64);
+      double qb = 0.0;  // lane q: Q after read b + q
+      auto step = [&](int q) {
+        Q = __builtin_fmax(Q, rl_d(wl, q));
+        Q = Q + rl_d(rl, q);
+        qb = lane == q ? Q : qb;
+      };
+      if (h - b >= 64) {  // straight line: later operands are formed while earlier steps finish
+#pragma unroll
+        for (int q = 0; q < 64; ++q) step(q);
+      } else {
+        for (int q = 0; q < h - b; ++q) step(q);
+      }
+      st_w[b + lane] = qb;
+    };
+    auto t_chain = [&](int b) {
+      const double ul = un, rl = rn;
+      request(b + 64);
+      const double al = kStaged ? st_w[b + lane] / rt.p0 : 0.0;
+      double tb = 0.0;  // lane q: t of read b + q
+      auto step = [&](int q) {
+        double tf = Y;
+        if (kPolicy == kNaive) tf = Y + rl_d(rl, q);
+        if (kStaged) {
+          tf = rl_d(al, q);
+          if (b + q > 0) tf = __builtin_fmax(tf, Y);
+        }
+        tb = lane == q ? tf : tb;
+        Y = tf + rl_d(ul, q);
+      };
+      if (h - b >= 64) {
+#pragma unroll
+        for (int q = 0; q < 64; ++q) step(q);
+      } else {
+        for (int q = 0; q < h - b; ++q) step(q);
+      }
+      if (b + lane < h) ring[b + lane] = tb;
+    };
+    double a0 = 0.0, a1 = 0.0;  // the sums of class `lane` and of class 64 + lane
+    auto io_chain = [&](int b) {
+      const double fl = fn;
+      const int cl = cn;
+      request(b + 64);
+      // every step adds the read's fetch time in its class's lane and +0 in
+      // the others (no sum is -0)
+      auto step = [&](int q) {
+        const int c = kPolicy == kNoPFS ? __builtin_amdgcn_readlane(cl, q) : 0;
+        const double f = rl_d(fl, q);
+        a0 = a0 + (c == lane ? f : 0.0);
+        if (K > 64) a1 = a1 + (c == lane + 64 ? f : 0.0);
+      };
+      if (h - b >= 64) {
+#pragma unroll
+        for (int q = 0; q < 64; ++q) step(q);
+      } else {
+        for (int q = 0; q < h - b; ++q) step(q);
+      }
+    };
+    if (kStaged) {
+      for (int k = 0; k <= nb; ++k) {
+        bool late = false;
+        if (wave == 0 && k < nb) {
+          late = prev && __ballot(64 * k + lane < h && gn >= 0 && gn >= 64 * k - 64) != 0u;
+          if (!late) q_chain(64 * k);
+        }
+        if (wave == 1 && k > 0) t_chain(64 * k - 64);
+        if (wave == kPsWaves - 1 && k < nb) io_chain(64 * k);
+        __syncthreads();
+        if (prev) {  // uniform
+          if (late) q_chain(64 * k);
+          __syncthreads();
+        }
+      }
+    } else {
+      for (int k = 0; k < nb; ++k) {
+        if (wave == 1) t_chain(64 * k);
+        if (kIo && wave == kPsWaves - 1) io_chain(64 * k);
+      }
+    }
+    if (wave == 0 && lane == 0) s_Q = Q;
+    if (wave == 1 && lane == 0) s_Y = Y;
+    if (kIo && wave == kPsWaves - 1) {
+      if (lane < kCls) io_x[lane] = bits_of(a0);
+      if (lane + 64 < kCls) io_x[lane + 64] = bits_of(a1);
+    }
+    __syncthreads();
+    Q = s_Q;
+    Y = s_Y;
+  };
+
   int32_t kA[kPsPer], cA[kPsPer] = {}, fA[kPsPer] = {}, cB[kPsPer] = {}, fB[kPsPer] = {};
   int64_t sB[kPsPer];
   double wB[kPsPer] = {};
@@ -450,16 +588,51 @@ ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ siz
     const uint32_t near = kStaged ? uint32_t(__builtin_amdgcn_readfirstlane(int(s_near[(f0 / kPsChunk) & 1]))) : 0u;
     if (kStaged) mark_near(f0 + kPsChunk, fB);
 
+    // the chunk's terms to LDS, for a wave that takes reads of all threads
+    auto stage = [&]() {
+#pragma unroll
+      for (int j = 0; j < kPsPer; ++j) {
+        st_u[i0 + j] = u[j];
+        if (kIo) st_rd[i0 + j] = rd[j];
+        if (kStaged) {
+          st_w[i0 + j] = W[j];
+          st_g[i0 + j] = g[j];
+        }
+      }
+    };
+    auto stage_io = [&]() {
+      if (!kIo) return;
+#pragma unroll
+      for (int j = 0; j < kPsPer; ++j) {
+        st_f[i0 + j] = fetch[j];
+        if (kPolicy == kNoPFS) st_c[i0 + j] = uint8_t(cls[j]);
+      }
+    };
+    int pos = 0;
+    constexpr int kHead = kPolicy == kPerfect ? 0 : (kPolicy == kNaive ? kPsHeadNaive : kPsHead);
+    if (kHead > 0 && f0 == 0 && !(near & 4u)) {
+      stage();
+      stage_io();
+      __syncthreads();
+      if (tid == 0) s_near[0] = 0;
+      const int hmax = (near & 8u) ? kPsHeadPrev
+                                   : (kPsThreads == kPsMany && (near & 2u) ? kPsHeadShort : kHead);
+      pos = n < hmax ? n : hmax;
+      head(pos, (near & 8u) != 0u);
+    }
+    const int pos0 = pos;
+
     // fetch-time sums: this chunk's units by class
-    if (kIo) {
+    if (kIo && pos0 < n) {
       uint64_t sum = 0;
       uint32_t bad = 0;
 #pragma unroll
       for (int j = 0; j < kPsPer; ++j) {
         bool stop = false;
         uint64_t d = units(fetch[j], binade_of(double_of(io_x[cls[j]])), &stop);
-        if (i0 + j >= n) d = 0;
-        bad |= stop && i0 + j < n ? 1u << j : 0u;
+        const bool on = i0 + j >= pos0 && i0 + j < n;
+        if (!on) d = 0;
+        bad |= stop && on ? 1u << j : 0u;
         if (kPolicy == kNoPFS)
           atomicAdd(reinterpret_cast<unsigned long long*>(&io_acc[cls[j] * kPsCopies + (lane & (kPsCopies - 1))]),
                     (unsigned long long)(d));
@@ -477,18 +650,6 @@ ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ siz
       }
     }
 
-    // the chunk's terms to LDS, for a wave that takes reads of all threads
-    auto stage = [&]() {
-#pragma unroll
-      for (int j = 0; j < kPsPer; ++j) {
-        st_u[i0 + j] = u[j];
-        if (kIo) st_rd[i0 + j] = rd[j];
-        if (kStaged) {
-          st_w[i0 + j] = W[j];
-          st_g[i0 + j] = g[j];
-        }
-      }
-    };
     // the chunk's reads from pos on by one wave
     auto wave_chain = [&](int pos) {
       int p = pos;
@@ -584,20 +745,16 @@ ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ siz
       }
     };
 
-    int pos = 0, shorts = 0;
+    int shorts = 0;
     bool first = true, io_slow = false;
-    if (near & 2u) {
+    if ((near & 2u) && pos < n) {
       // short windows: one wave from the start, another for the sums
       stage();
-#pragma unroll
-      for (int j = 0; j < kPsPer; ++j) {
-        st_f[i0 + j] = fetch[j];
-        if (kPolicy == kNoPFS) st_c[i0 + j] = uint8_t(cls[j]);
-      }
+      stage_io();
       __syncthreads();
       if (tid == 0) s_near[(f0 / kPsChunk) & 1] = 0;
-      if (wave == 0) wave_chain(0);
-      if (wave == kPsWaves - 1 && io_check()) io_ordered(n);
+      if (wave == 0) wave_chain(pos);
+      if (wave == kPsWaves - 1 && io_check()) io_ordered(pos0, n);
       __syncthreads();
       Q = s_Q;
       Y = s_Y;
@@ -753,7 +910,7 @@ ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ siz
       const int np = s_pos;
       if (np - pos < kPsMinStep) ++shorts;
       pos = np;
-      if (shorts < 2 || pos >= n) continue;
+      if (shorts < (f0 == 0 ? kPsShortsFirst : kPsShorts) || pos >= n) continue;
 
       // one wave goes on from here
       stage();
@@ -766,13 +923,9 @@ ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ siz
     }
 
     if (kIo && io_slow) {
-#pragma unroll
-      for (int j = 0; j < kPsPer; ++j) {
-        st_f[i0 + j] = fetch[j];
-        if (kPolicy == kNoPFS) st_c[i0 + j] = uint8_t(cls[j]);
-      }
+      stage_io();
       __syncthreads();
-      if (wave == 0) io_ordered(n);
+      if (wave == 0) io_ordered(pos0, n);
       if (tid == 0) s_io_slow = 0;
       __syncthreads();
     }

@@ -116,3 +116,36 @@ def test_sizes_that_stop_scans(oracle, name, model):
                         r=(1e300, 1e300), p=(1, 1))}[model]
     fill = np.maximum(0, np.arange(R.shape[1]) - 900)[None].repeat(2, 0).astype(np.int32)
     _check(oracle, shape, R, sizes, fill, prm, 3)
+
+
+# the stepped first reads of a row: rows that end inside, at and behind them
+# (256, 512, 768 and 1,024 reads), whole and part batches of 64, and windows
+# that reach into the same batch (63), the one before (64 to 127) or none of them
+@pytest.mark.parametrize("N", [2, 257])
+@pytest.mark.parametrize("w", [63, 64, 127, 128, 600, 5000])
+def test_first_reads(oracle, N, w):
+    rows = [1, 64, 65, 255, 256, 257, 511, 513, 767, 769, 1023, 1025, 1087]
+    for M in rows if N == 2 else rows[2::3]:
+        shape = (N * M - 1, 1, N, 1, 0, M + w)  # the last row is one read shorter
+        R = oracle.access_streams(oracle.make_job(*shape))
+        sizes = wl.random_sizes(shape[0], M, 1_000, 2_000_000)
+        fill = np.maximum(0, np.arange(R.shape[1]) - w + 1)[None].repeat(N, 0).astype(np.int32)
+        _check(oracle, shape, R, sizes, fill, dict(wl.LASSEN_MODEL, c=1e9), M)
+
+
+def test_first_reads_of_all_classes(oracle):
+    """32 tiers: 65 source classes, one more than a wave has lanes."""
+    shape = (3_001, 1, 2, 1, 0, 7)
+    rjob, job = oracle.make_job(*shape), nopfs.Job(*shape)
+    R = oracle.access_streams(rjob)
+    sizes = wl.random_sizes(shape[0], 8, 1_000, 2_000_000)
+    prm = dict(wl.LASSEN_MODEL, r=[1e9 + 1e7 * j for j in range(32)], p=[1 + j % 3 for j in range(32)])
+    codes = np.array([0] + [128 + j for j in range(32)] + [256 + j for j in range(32)] + [127, 160, 288], np.int16)
+    src = np.random.default_rng(9).choice(codes, size=R.shape)
+    fill = np.maximum(0, np.arange(R.shape[1]) - 300)[None].repeat(2, 0).astype(np.int32)
+    want = oracle.policy_sim(rjob, R, sizes, oracle.make_model(**prm), nopfs.POLICY_NOPFS, src=src, fill=fill)
+    got = nopfs.policy_sim(job, _dev(R), _dev(sizes), nopfs.make_model(**prm), nopfs.POLICY_NOPFS,
+                           src=_dev(src), fill=_dev(fill))
+    torch.cuda.synchronize()
+    for what, g, e in zip(("t", "finish", "io"), got, want):
+        assert np.array_equal(g.cpu().numpy(), e), what
