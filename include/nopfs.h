@@ -302,8 +302,9 @@ int nopfs_fetch_model(const nopfs_job* job, const int32_t* R, const int8_t* tier
  *   hit:     int8 [N][M_max], output: 1 hit, 0 miss, -1 padding.
  *   hits:    int64 [N][2], output: hits and hit bytes per worker.
  * M_max < 2^24. Scratch: one bit per stream position, and 4 bytes more where
- * the replay goes in the order of next uses (if they can be had). Errors:
- * EINVAL (also d0 < 0),
+ * the replay may go in the order of next uses (jobs that read again about 300
+ * samples per worker and epoch or more); without memory for those it goes in
+ * stream order, with the same results. Errors: EINVAL (also d0 < 0),
  * ERANGE (M_max >= 2^24), ENOMEM, EDEVICE. */
 int nopfs_buffer_sim(const nopfs_job* job, const int32_t* R, const int32_t* next,
                      const int64_t* sizes, int64_t d0, int8_t* hit, int64_t* hits,
@@ -399,7 +400,8 @@ int nopfs_scratch_release(void* hip_stream);
  *   which=1  largest bucket the stream sort keeps in LDS (elements)
  *   which=2  candidate records per worker in the tier plan's fast path, and
  *            reads per window in the next-use fast path
- *   which=3  fail the next internal scratch allocation (value 1)
+ *   which=3  fail the value-th internal scratch allocation from now (1: the
+ *            next one)
  *   which=4  longest range of buffer starts the staging schedule keeps in
  *            LDS per chunk (wider ranges take the global-memory search)
  *   which=5  doublings (at most 4) of the sample windows of the staging

@@ -56,13 +56,7 @@ static thread_local int64_t g_debug[6] = {0, 0, 0, 0, 0, 0};
 
 int64_t debug_value(int which) { return (which >= 0 && which < 6) ? g_debug[which] : 0; }
 
-bool take_alloc_failure() {
-  if (g_debug[3]) {
-    g_debug[3] = 0;
-    return true;
-  }
-  return false;
-}
+bool take_alloc_failure() { return g_debug[3] > 0 && --g_debug[3] == 0; }
 
 // Scratch of one (device, stream): one block of device memory reused by
 // every call on that stream, handed out as a stack (the Scratch objects of a
@@ -219,8 +213,11 @@ Scratch::~Scratch() {
 int Scratch::alloc(void** p, size_t bytes) {
   *p = nullptr;
   if (n_ >= 32) return fail(NOPFS_ENOMEM, "too many scratch buffers");
-  if (take_alloc_failure()) return fail(NOPFS_ENOMEM, "scratch allocation failed (test hook)");
   Arena* a = arena_;
+  if (take_alloc_failure()) {
+    if (a) a->failed = true;
+    return fail(NOPFS_ENOMEM, "scratch allocation failed (test hook)");
+  }
   if (!a) return fail(NOPFS_ENOMEM, "no device memory for scratch (no current device)");
   bytes = (bytes + 255) & ~size_t(255);
   if (bytes == 0) bytes = 256;
@@ -250,6 +247,23 @@ int Scratch::alloc(void** p, size_t bytes) {
   recs_[n_++] = a->stack.size();
   a->stack.push_back(r);
   return NOPFS_OK;
+}
+
+bool Scratch::try_alloc(void** p, size_t bytes) {
+  *p = nullptr;
+  Arena* a = arena_;
+  if (!a) return false;
+  if (a->top + ((bytes + 255) & ~size_t(255)) > a->cap) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream_, &capture) != hipSuccess) (void)hipGetLastError();
+    if (capture != hipStreamCaptureStatusNone) return false;
+  }
+  const bool failed = a->failed;
+  const std::string detail = g_last_error;
+  if (alloc(p, bytes) == NOPFS_OK) return true;
+  a->failed = failed;
+  g_last_error = detail;
+  return false;
 }
 
 // -------------------------------------------------------------- profiling --

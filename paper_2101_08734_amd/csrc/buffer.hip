@@ -44,8 +44,9 @@
 // per batch two block-wide scans and five barriers, per change of T several
 // looks into blocks (about 50 us).
 //
-// In stream order (bs_sim), where an epoch brings too few candidates for that
-// (the rule in buffer_impl), or memory for the previous uses is missing:
+// In stream order (bs_sim), where an epoch brings too few candidates for that or
+// the buffer holds too few samples (the rule in buffer_impl), or memory for the
+// previous uses is missing:
 //
 //   bs_sim   -- one wave per worker. Held keys in a three-level bitmap: a
 //               bit per position in 64-bit words in global memory, one word
@@ -131,10 +132,11 @@ __device__ __forceinline__ uint64_t l0_load(const uint64_t* p) {
 
 __global__ void __launch_bounds__(64)
 bs_sim(BsShape r, const int32_t* __restrict__ R, const int32_t* __restrict__ next,
-       const int64_t* __restrict__ sizes, int64_t d0,
+       const int64_t* __restrict__ sizes, int64_t d0, const uint32_t* __restrict__ in_order,
        uint64_t* __restrict__ L0, int8_t* __restrict__ hit, int64_t* __restrict__ hits) {
   __shared__ uint32_t l1[kBsW1];
   __shared__ uint32_t l2[kBsW2];
+  if (in_order && *in_order == 0u) return;  // the other replay takes this call
   const int64_t i = blockIdx.x;
   const int lane = threadIdx.x;
   const int64_t Mi = bs_row_len(r, i);
@@ -404,6 +406,7 @@ constexpr uint32_t kKbMany = 32;   // as is one that puts more blocks than this 
 constexpr int kKbMinSpan = 256;    // but not below this many positions
 constexpr double kKbMinCands = 300;  // candidates per worker and epoch
 constexpr int64_t kKbMaxD0 = int64_t(1) << 50;       // sums over a block and a batch stay below 2^63
+constexpr int kKbSample = 16;                        // sizes per thread whose mean is taken
 
 // padded index: a thread's 16 consecutive blocks start on different banks
 __device__ __forceinline__ int kb_slot(int b) { return b + (b >> 4); }
@@ -425,9 +428,31 @@ struct KbSmem {
   int64_t hc, hb;
 };
 
-// hit: 0 up to the row's length, -1 behind it; prev: -1
+// hit: 0 up to the row's length, -1 behind it; prev: -1. The first workgroup
+// also chooses the replay: in stream order (*in_order = 1) when d0 is less than
+// `least` sizes' worth, by the mean of up to 4,096 sizes, and one of them fits.
 __global__ void __launch_bounds__(256)
-kb_init(BsShape r, int32_t* __restrict__ prev, int8_t* __restrict__ hit) {
+kb_init(BsShape r, const int64_t* __restrict__ sizes, int64_t d0, double least,
+        uint32_t* __restrict__ in_order, int32_t* __restrict__ prev, int8_t* __restrict__ hit) {
+  if (in_order && blockIdx.x == 0 && blockIdx.y == 0) {
+    __shared__ double part[4];
+    const int64_t n = r.F < 256 * kKbSample ? r.F : 256 * kKbSample;
+    double sum = 0;
+    bool fits = false;
+#pragma unroll
+    for (int u = 0; u < kKbSample; ++u) {
+      const int64_t x = u * 256 + int64_t(threadIdx.x);
+      const int64_t s = sizes[x < n ? x * r.F / n : 0];  // unconditional
+      sum += x < n ? double(s) : 0.0;
+      fits = fits || s <= d0;
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+    fits = __syncthreads_or(fits);
+    if (threadIdx.x == 0)
+      *in_order = fits && double(d0) * double(n) < least * (part[0] + part[1] + part[2] + part[3]) ? 1u : 0u;
+  }
   const int64_t i = blockIdx.y;
   const int64_t Mi = bs_row_len(r, i);
   const int64_t f0 = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 16;
@@ -450,7 +475,9 @@ kb_init(BsShape r, int32_t* __restrict__ prev, int8_t* __restrict__ hit) {
 
 // prev[next[f]] = f
 __global__ void __launch_bounds__(256)
-kb_prev(BsShape r, const int32_t* __restrict__ next, int32_t* __restrict__ prev) {
+kb_prev(BsShape r, const int32_t* __restrict__ next, const uint32_t* __restrict__ in_order,
+        int32_t* __restrict__ prev) {
+  if (in_order && *in_order != 0u) return;
   const int64_t i = blockIdx.y;
   const int64_t Mi = bs_row_len(r, i);
   const int64_t f0 = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 4;
@@ -471,13 +498,14 @@ kb_prev(BsShape r, const int32_t* __restrict__ next, int32_t* __restrict__ prev)
 
 __global__ void __launch_bounds__(kKbThreads)
 kb_sim(BsShape r, const int32_t* __restrict__ R, const int32_t* __restrict__ next,
-       const int64_t* __restrict__ sizes, int64_t d0, int ash, int sh,
-       const int32_t* __restrict__ prev, int8_t* __restrict__ hit, int64_t* __restrict__ hits) {
+       const int64_t* __restrict__ sizes, int64_t d0, const uint32_t* __restrict__ in_order, int ash,
+       int sh, const int32_t* __restrict__ prev, int8_t* __restrict__ hit, int64_t* __restrict__ hits) {
   __shared__ KbSmem m;
   const int64_t i = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int32_t Mi = int32_t(bs_row_len(r, i));  // < 2^24
+  const bool here = !in_order || *in_order == 0u;  // else the other replay takes the call
+  const int32_t Mi = here ? int32_t(bs_row_len(r, i)) : 0;  // < 2^24
   const int32_t* Rr = R + i * r.M_max;
   const int32_t* Xr = next + i * r.M_max;
   const int32_t* Pr = prev + i * r.M_max;
@@ -857,7 +885,7 @@ kb_sim(BsShape r, const int32_t* __restrict__ R, const int32_t* __restrict__ nex
   atomicAdd(reinterpret_cast<unsigned long long*>(&m.hc), (unsigned long long)(hc));
   atomicAdd(reinterpret_cast<unsigned long long*>(&m.hb), (unsigned long long)(hb));
   __syncthreads();
-  if (tid == 0) {
+  if (tid == 0 && here) {
     hits[i * 2] = m.hc;
     hits[i * 2 + 1] = m.hb;
   }
@@ -874,10 +902,7 @@ int buffer_impl(const nopfs_job* job, const int32_t* R, const int32_t* next, con
   if (s.M_max >= (int64_t(1) << kBsMaxLog)) return fail(NOPFS_ERANGE, "M_max must be < 2^24");
   if (s.N >= (int64_t(1) << 31)) return fail(NOPFS_ERANGE, "N too large for one launch");
   BsShape r{s.F, s.N, s.B, s.M_max, s.E, s.drop_last};
-  const int64_t W0 = (s.M_max + 63) >> 6;
   Scratch scr(st);
-  uint64_t* L0;
-  if ((rc = scr.alloc_n(&L0, size_t(s.N * W0)))) return rc;
   // Candidates per worker and epoch of a uniform shuffle (a read has an
   // earlier one with probability 1 - (1 - p)^e in epoch e, p = L / F). The order
   // of next uses pays per change of T, a few per epoch, the stream order per
@@ -886,29 +911,47 @@ int buffer_impl(const nopfs_job* job, const int32_t* R, const int32_t* next, con
   // 520 1.0x (3.0x), 780 1.3x (4.3x), 1,030 1.05x (4.6x).
   const double p = double(s.L) / double(s.F), pe = p * double(s.E);
   const double cands = s.M_max > 0 ? double(s.L) * (1.0 - (1.0 - pow(1.0 - p, double(s.E))) / pe) : 0.0;
-  if (cands >= kKbMinCands && d0 < kKbMaxD0 && s.N < 65536) {
-    // without memory for the previous uses (4 bytes per position) the replay
-    // in stream order takes the job
-    const std::string detail = nopfs_last_error();
-    int32_t* prev;
-    if (scr.alloc_n(&prev, size_t(s.N * s.M_max)) == NOPFS_OK) {
-      int ash = 0;  // units of adj: 2^ash bytes, at most 2^26 of them in d0
-      while ((d0 >> ash) >= (int64_t(1) << 26)) ++ash;
-      int sh = kKbMinShift;  // time blocks of 2^sh positions
-      while (((s.M_max - 1) >> sh) >= kKbBlocks) ++sh;
-      if ((rc = launch("kb_init", kb_init, dim3(uint32_t(ceil_div(s.M_max, 4096)), uint32_t(s.N)),
-                       dim3(256), 0, st, r, prev, hit)))
-        return rc;
-      if ((rc = launch("kb_prev", kb_prev, dim3(uint32_t(ceil_div(s.M_max, 1024)), uint32_t(s.N)),
-                       dim3(256), 0, st, r, next, prev)))
-        return rc;
-      return launch("bs_sim", kb_sim, dim3(uint32_t(s.N)), dim3(kKbThreads), 0, st, r, R, next, sizes,
-                    d0, ash, sh, (const int32_t*)prev, hit, hits);
-    }
-    set_last_error(detail);
+  const bool many = cands >= kKbMinCands && d0 < kKbMaxD0 && s.N < 65536;
+  // A buffer of few samples: T changes again after few candidates, and the
+  // stream order has little to discard. The line lies at a capacity in samples
+  // that falls with the candidates and rises with the reads between them: a
+  // fit over 110 shapes of 300 to 6,000 candidates at capacities of 1 to 1,000
+  // samples, where beyond it the order of next uses took at most 1.4 times the
+  // other's time in all but one (355 reads, 338 candidates an epoch, 2 workers,
+  // line at 17 samples: 3 samples 2.3x, 20 1.15x, 80 0.6x; 27,365 reads, 1,047
+  // candidates, 64 workers, line at 30: 10 1.2x, 40 0.75x; ImageNet-22k, line at 4).
+  // Only the device knows the sizes, so both replays are launched and one leaves.
+  const double least = many ? 2.2e4 * pow(double(s.L), 0.6) / pow(cands, 1.83) : 0.0;
+  const int64_t W0 = (s.M_max + 63) >> 6;
+  uint64_t* L0 = nullptr;
+  uint32_t* in_order = nullptr;
+  int32_t* prev = nullptr;
+  const bool either = many && least > 1.0;
+  if (!many || either) {
+    if ((rc = scr.alloc_n(&L0, size_t(s.N * W0) + 1))) return rc;  // and the choice
+    if (either) in_order = reinterpret_cast<uint32_t*>(L0 + s.N * W0);
   }
-  return launch("bs_sim", bs_sim, dim3(uint32_t(s.N)), dim3(64), 0, st, r, R, next, sizes, d0, L0, hit,
-                hits);
+  if (many && scr.try_alloc_n(&prev, size_t(s.N * s.M_max))) {
+    int ash = 0;  // units of adj: 2^ash bytes, at most 2^26 of them in d0
+    while ((d0 >> ash) >= (int64_t(1) << 26)) ++ash;
+    int sh = kKbMinShift;  // time blocks of 2^sh positions
+    while (((s.M_max - 1) >> sh) >= kKbBlocks) ++sh;
+    if ((rc = launch("kb_init", kb_init, dim3(uint32_t(ceil_div(s.M_max, 4096)), uint32_t(s.N)),
+                     dim3(256), 0, st, r, sizes, d0, least, in_order, prev, hit)))
+      return rc;
+    if ((rc = launch("kb_prev", kb_prev, dim3(uint32_t(ceil_div(s.M_max, 1024)), uint32_t(s.N)),
+                     dim3(256), 0, st, r, next, (const uint32_t*)in_order, prev)))
+      return rc;
+    if ((rc = launch("kb_sim", kb_sim, dim3(uint32_t(s.N)), dim3(kKbThreads), 0, st, r, R, next, sizes,
+                     d0, (const uint32_t*)in_order, ash, sh, (const int32_t*)prev, hit, hits)))
+      return rc;
+    if (!either) return NOPFS_OK;
+  } else {
+    in_order = nullptr;  // without memory for the previous uses: stream order
+    if (!L0 && (rc = scr.alloc_n(&L0, size_t(s.N * W0)))) return rc;
+  }
+  return launch("bs_sim", bs_sim, dim3(uint32_t(s.N)), dim3(64), 0, st, r, R, next, sizes, d0,
+                (const uint32_t*)in_order, L0, hit, hits);
 }
 
 }  // namespace

@@ -67,8 +67,15 @@ class Scratch {
   int alloc(void** p, size_t bytes);
   template <typename T>
   int alloc_n(T** p, size_t n) { return alloc(reinterpret_cast<void**>(p), n * sizeof(T)); }
+  // The same for a buffer that the call can do without: false, with no error
+  // recorded, where there is no memory for it (or the stream is being captured
+  // and its block has no room: nothing may be allocated then). The block still
+  // grows to what the call did get.
+  template <typename T>
+  bool try_alloc_n(T** p, size_t n) { return try_alloc(reinterpret_cast<void**>(p), n * sizeof(T)); }
 
  private:
+  bool try_alloc(void** p, size_t bytes);
   hipStream_t stream_;
   struct Arena* arena_ = nullptr;
   size_t recs_[32] = {};  // this object's entries on the arena's stack
@@ -107,7 +114,7 @@ int launch(const char* name, Kernel k, dim3 grid, dim3 block, size_t shmem,
 
 // Debug overrides (nopfs_debug_set).
 int64_t debug_value(int which);
-bool take_alloc_failure();
+bool take_alloc_failure();  // this allocation is the one that is to fail
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
