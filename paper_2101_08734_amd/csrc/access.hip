@@ -531,17 +531,19 @@ __device__ void next_tile_slow(const SegParams& p, int64_t i, uint32_t kb, const
     const int64_t epoch = seg_len(p, i) / p.emul;
     for (int64_t e = int64_t(p.E) * p.emul - 1; e >= 0; --e) {
       // reads of one epoch are distinct samples: no two threads share a slot
-      // (with the epochs folded, those of the epoch among all the row's)
-      const int64_t seg = p.emul == 1 ? e : 0;
-      for_each_read(p, i, kb, O, prow, rt, seg, seg + 1,
-                    [&](int64_t pos, int64_t fbase, uint32_t v, uint32_t) {
-                      const uint32_t x = (v >> kScShift) - xoff;
-                      const int64_t f = fbase + (v & kJMask);
-                      if (x < wlen && f >= e * epoch && f < (e + 1) * epoch) {
-                        nrow[pos] = last[x];
-                        last[x] = int32_t(f);
-                      }
-                    });
+      // (with the epochs folded, those of the epoch among the reads of the
+      // sub-chunks it reaches into: one or two)
+      const int64_t r0 = p.emul == 1 ? e * p.nsc : e * epoch / kSC;
+      const int64_t r1 = p.emul == 1 ? (e + 1) * p.nsc : ((e + 1) * epoch + kSC - 1) / kSC;
+      for_runs(p, i, kb, O, prow, rt, r0, r1,
+               [&](int64_t pos, int64_t fbase, uint32_t v, uint32_t) {
+                 const uint32_t x = (v >> kScShift) - xoff;
+                 const int64_t f = fbase + (v & kJMask);
+                 if (x < wlen && f >= e * epoch && f < (e + 1) * epoch) {
+                   nrow[pos] = last[x];
+                   last[x] = int32_t(f);
+                 }
+               });
       __syncthreads();
     }
   }
@@ -565,7 +567,7 @@ next_tile(SegParams p, const uint32_t* __restrict__ Pk, const uint16_t* __restri
   // table loaded here is reused for the gather below
   uint32_t total;
   if (runs <= kNextThreads) {
-    total = load_runs(p, i, kb, OT, rt, 0, runs, 0);
+    total = load_runs(p, i, kb, OT, rt, runs, 0);
   } else {
     if (threadIdx.x == 0) s_total = 0;
     __syncthreads();
@@ -622,7 +624,7 @@ next_tile(SegParams p, const uint32_t* __restrict__ Pk, const uint16_t* __restri
   } else {
     for (int d = threadIdx.x; d < kNextSlots; d += kNextThreads) s.head[d] = kNoLink;
     __syncthreads();
-    for_each_read(p, i, kb, OT, prow, rt, 0, p.E, gather);
+    for_runs(p, i, kb, OT, prow, rt, 0, runs, gather);
   }
   __syncthreads();
   // each read: smallest later position of the same sample on its chain
@@ -654,8 +656,8 @@ next_tile(SegParams p, const uint32_t* __restrict__ Pk, const uint16_t* __restri
       if (idx < total) s.f[idx] = res[q];
     }
     __syncthreads();
-    for_each_read(p, i, kb, OT, prow, rt, 0, p.E,
-                  [&](int64_t pos, int64_t, uint32_t, uint32_t idx) { nrow[pos] = s.f[idx]; });
+    for_runs(p, i, kb, OT, prow, rt, 0, runs,
+             [&](int64_t pos, int64_t, uint32_t, uint32_t idx) { nrow[pos] = s.f[idx]; });
   }
 }
 

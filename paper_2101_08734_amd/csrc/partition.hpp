@@ -77,12 +77,12 @@ struct RunTable {
   uint16_t run_of[kRunMap];  // run index of each read (when total <= kRunMap)
 };
 
-// Loads the run table of runs [r0, r0 + NT) of epochs [e_lo, e_hi)
-// and returns the number of reads they hold. Leaves rt ready for lookups.
+// Loads the run table of runs [r0, r0 + NT), none past `runs`, and returns the
+// number of reads they hold. Leaves rt ready for lookups.
 template <int NT>
 __device__ __forceinline__ uint32_t load_runs(const SegParams& p, int64_t i, uint32_t kb,
                                               const uint16_t* __restrict__ OT, RunTable<NT>& rt,
-                                              int64_t e_lo, int64_t runs, int64_t r0) {
+                                              int64_t runs, int64_t r0) {
   const int64_t Li = seg_len(p, i);
   const int64_t R = int64_t(p.E) * p.nsc;
   const uint16_t* oa = OT + (i * (p.nbk + 1) + kb) * R;  // window kb: run starts
@@ -90,9 +90,8 @@ __device__ __forceinline__ uint32_t load_runs(const SegParams& p, int64_t i, uin
   const int64_t r = r0 + threadIdx.x;
   uint32_t len = 0;
   if (r < runs) {
-    const int64_t run = e_lo * p.nsc + r;
-    const uint32_t e = uint32_t(run) / uint32_t(p.nsc), sc = uint32_t(run) - e * uint32_t(p.nsc);
-    const uint32_t a = oa[run], b = ob[run];
+    const uint32_t e = uint32_t(r) / uint32_t(p.nsc), sc = uint32_t(r) - e * uint32_t(p.nsc);
+    const uint32_t a = oa[r], b = ob[r];
     len = b - a;
     rt.fbase[threadIdx.x] = int32_t(e * Li + sc * kSC);
     rt.start[threadIdx.x] = int32_t(e * Li + sc * kSC + a);
@@ -159,16 +158,16 @@ __device__ __forceinline__ void consume_runs(const RunTable<NT>& rt, int nr, uin
   }
 }
 
+// Calls fn as consume_runs does for every read of runs [lo, hi) of window kb.
 template <int NT, typename Fn>
-__device__ __forceinline__ void for_each_read(const SegParams& p, int64_t i, uint32_t kb,
-                                              const uint16_t* __restrict__ O,
-                                              const uint32_t* __restrict__ prow, RunTable<NT>& rt,
-                                              int64_t e_lo, int64_t e_hi, Fn fn) {
-  const int64_t runs = (e_hi - e_lo) * p.nsc;
+__device__ __forceinline__ void for_runs(const SegParams& p, int64_t i, uint32_t kb,
+                                         const uint16_t* __restrict__ O,
+                                         const uint32_t* __restrict__ prow, RunTable<NT>& rt,
+                                         int64_t lo, int64_t hi, Fn fn) {
   uint32_t done = 0;
-  for (int64_t r0 = 0; r0 < runs; r0 += NT) {
-    const uint32_t total = load_runs(p, i, kb, O, rt, e_lo, runs, r0);
-    const int nr = int(runs - r0 < NT ? runs - r0 : NT);
+  for (int64_t r0 = lo; r0 < hi; r0 += NT) {
+    const uint32_t total = load_runs(p, i, kb, O, rt, hi, r0);
+    const int nr = int(hi - r0 < NT ? hi - r0 : NT);
     consume_runs(rt, nr, total, prow, done, fn);
     done += total;
     __syncthreads();

@@ -136,7 +136,7 @@ pf_tile(SegParams p, const uint32_t* __restrict__ Pk, const uint16_t* __restrict
     }
     const uint32_t tshl = words ? tsh : 0u;
     // run table
-    const uint32_t total = load_runs(p, i, kb, OT, rt, 0, runs, 0);
+    const uint32_t total = load_runs(p, i, kb, OT, rt, runs, 0);
     if (total <= uint32_t(kPfKeep * kTileThreads)) {
       uint32_t v[kPfKeep];
       int32_t pos[kPfKeep], fb[kPfKeep];

@@ -235,3 +235,22 @@ def test_output_tensors_checked():
         nopfs.access_streams(job, R=torch.empty((2, 3), dtype=torch.int32, device="cuda"))
     with pytest.raises(TypeError):
         nopfs.access_streams(job, R=torch.empty((2, 48), dtype=torch.int32))
+
+
+# rows of one and of three sub-chunks of 16,384 reads, their short epochs folded
+# into one segment (64 sub-chunks and more), by chains in both paths
+@pytest.mark.parametrize("path", PATHS)
+@pytest.mark.parametrize("F,E,N", [(70 * 300 + 17, 40, 70), (70 * 1_000 + 3, 40, 70)])
+def test_slow_paths_folded(oracle, path, F, E, N):
+    """The epoch-serial next-use path where a row's epochs are folded: each
+    epoch is picked out of the sub-chunks it reaches into."""
+    sizes = wl.random_sizes(F, 42, 1_000, 2_000_000)
+    caps = _caps(sizes, (0.03, 0.2))
+    job = nopfs.Job(F, E, N, 1, 0, 43)
+    exp = oracle.full_pipeline(oracle.make_job(F, E, N, 1, 0, 43), sizes, caps)
+    try:
+        nopfs.debug_set(2, 8)
+        got = gpu_pipeline(job, sizes, caps, path)
+    finally:
+        nopfs.debug_set(2, 0)
+    compare(got, exp)
