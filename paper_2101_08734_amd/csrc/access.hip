@@ -880,15 +880,26 @@ int launch_stats(const SegParams& p, const uint32_t* Pk, const uint16_t* OT, uin
 // windows are not the counting pass's (plan, ImageNet-1k on 64 workers: 3.41 ->
 // 3.26 ms, on 128 3.40 -> 3.92). With fewer tiles than compute units a tile's chain of
 // epochs is all there is to wait for (2,000 samples, 200 epochs, 8 workers:
-// 0.05 -> 0.11 ms), so those jobs walk up to 64 epochs only.
+// 0.05 -> 0.11 ms), so those jobs walk up to 64 epochs only, and the next-use
+// call, which saves no partition by it, only from 128 tiles on, or from 96 (64)
+// where more than 8 (32) epochs have 700 (2,000) reads per window, or from 80 with
+// 3,000. Next-use
+// call, chains against walk over 1,021 jobs of 1 to 40 workers: below 64 tiles the
+// walk takes up to 5.9 times as long (7,627 samples, 52 epochs, one worker: 24
+// and 141 us); with 64 to 96 tiles 0.9 to 1.5 of it, 0.8 to 0.96 where the rule
+// takes it (391,731 samples, 36 epochs, 2 workers: 272 and 168); with 96 to 128
+// 0.85 to 1.35, 0.74 to 0.97 where taken; from 128 to 256 0.5 to 1.08.
 constexpr int kWalkWs = NOPFS_STATS_WS;
 static_assert((1 << kWalkWs) <= kWalkWin, "a window's samples fit the walk's table");
 constexpr double kWalkReads = 384, kWalkReadsFused = 128;
 
-bool walks(const SegParams& p, double reads) {
+bool walks(const SegParams& p, double least, bool fused) {
   const double win = p.F < (int64_t(1) << p.ws) ? double(p.F) : double(int64_t(1) << p.ws);
-  return p.ws == kWalkWs && double(p.L) * win / double(p.F) >= reads &&
-         (p.N * p.nbk >= 256 || p.E <= 64);
+  const double reads = double(p.L) * win / double(p.F);
+  const int64_t tiles = p.N * int64_t(p.nbk);
+  if (p.ws != kWalkWs || reads < least || (tiles < 256 && p.E > 64)) return false;
+  return fused || tiles >= 128 || (tiles >= 96 && p.E > 8 && reads >= 700) ||
+         (tiles >= 80 && reads >= 3000) || (tiles >= 64 && p.E > 32 && reads >= 2000);
 }
 
 // Window width of the next-use pass by chains: the widest whose expected reads stay
@@ -1014,7 +1025,7 @@ int next_impl(const nopfs_job* job, const int32_t* R, int32_t* next, hipStream_t
   if (s.M_max == 0) return NOPFS_OK;  // R and next have no elements and may be NULL
   if (!R || !next) return fail(NOPFS_EINVAL, "R and next must be non-NULL");
   SegParams p = seg_params(s, kWalkWs);
-  const bool walk = walks(p, kWalkReads);
+  const bool walk = walks(p, kWalkReads, false);
   if (!walk) p = chain_params(s);
   Scratch scr(st);
   uint32_t* Pk;
@@ -1032,7 +1043,7 @@ int access_fused(const Shape& s, const int32_t* R, const ClassTable* classes, ui
   int rc;
   SegParams ps = seg_params(s, NOPFS_STATS_WS);
   SegParams pn = chain_params(s);
-  const bool walk = walks(ps, pn.ws == ps.ws ? kWalkReads : kWalkReadsFused);
+  const bool walk = walks(ps, pn.ws == ps.ws ? kWalkReads : kWalkReadsFused, true);
   if (walk) pn = ps;  // epoch by epoch
   else fold_epochs(ps);
   uint32_t *Pk, *Pn;

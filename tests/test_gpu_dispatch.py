@@ -1,0 +1,63 @@
+"""Rules that choose a kernel, a layout or a split by the job's sizes: jobs on
+both sides of each line, against the oracle. Integer results must be equal.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_2101_08734_amd import nopfs  # noqa: E402
+from paper_2101_08734_amd import workloads as wl  # noqa: E402
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    nopfs.lib()
+    yield
+    for which in (1, 2, 3):
+        nopfs.debug_set(which, 0)
+    torch.cuda.empty_cache()
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _same(name, got, want):
+    g = got.cpu().numpy()
+    bad = np.argwhere(g != want)
+    assert len(bad) == 0, (name, len(bad), bad[:3].tolist(), g[tuple(bad[0])], want[tuple(bad[0])])
+
+
+def _launched(call):
+    """The call's result and the kernels it launched."""
+    nopfs.profile_enable(True)
+    try:
+        out = call()
+        torch.cuda.synchronize()
+        return out, set(nopfs.profile_results())
+    finally:
+        nopfs.profile_enable(False)
+
+
+# next uses of jobs with few workers: the epochs are walked where enough tiles
+# (worker, window of 8,192 samples) fill the chip, chained elsewhere
+@pytest.mark.parametrize("F,E,N,walk", [
+    (7_627, 52, 1, False),          # one tile
+    (8 * 8192, 4, 16, True),        # 128 tiles
+    (15 * 8192, 4, 8, False),       # 120, few epochs
+    (15 * 8192, 9, 8, True),        # 120, more epochs, 1,024 reads per window
+    (39 * 8192, 3, 2, False),       # 78
+    (39 * 8192 + 1, 3, 2, True),    # 80, 4,096 reads per window
+    (33 * 8192, 32, 2, False),      # 66
+    (33 * 8192, 33, 2, True),
+])
+def test_next_walk_or_chains(oracle, F, E, N, walk):
+    shape = (F, E, N, 1, 0, F + E)
+    R = oracle.access_streams(oracle.make_job(*shape))
+    got, names = _launched(lambda: nopfs.reuse_next(nopfs.Job(*shape), _dev(R)))
+    _same("next", got, oracle.reuse_next(oracle.make_job(*shape), R))
+    assert ("next_walk" in names, "next_tile" in names) == (walk, not walk), names
