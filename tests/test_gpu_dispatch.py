@@ -61,3 +61,18 @@ def test_next_walk_or_chains(oracle, F, E, N, walk):
     got, names = _launched(lambda: nopfs.reuse_next(nopfs.Job(*shape), _dev(R)))
     _same("next", got, oracle.reuse_next(oracle.make_job(*shape), R))
     assert ("next_walk" in names, "next_tile" in names) == (walk, not walk), names
+
+
+# counting tiles: few and many threads to a run, runs of a few reads and of
+# thousands, with few and with many tiles
+@pytest.mark.parametrize("shape", [
+    (10_000, 5, 4, 1, 0, 1), (900_001, 9, 12, 1, 0, 2), (1_300_003, 8, 64, 1, 0, 3), (2_000_005, 11, 100, 1, 1, 4),
+], ids=lambda s: f"F{s[0]}E{s[1]}N{s[2]}")
+def test_threads_per_run(oracle, shape):
+    rjob = oracle.make_job(*shape)
+    R = oracle.access_streams(rjob)
+    count, first = nopfs.access_stats(nopfs.Job(*shape), _dev(R))
+    torch.cuda.synchronize()
+    want = oracle.access_stats(rjob, R)
+    _same("count", count, want[0])
+    _same("first", first, want[1])
