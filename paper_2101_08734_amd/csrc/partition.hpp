@@ -45,9 +45,11 @@ __device__ __forceinline__ int64_t seg_len(const SegParams& p, int64_t i) {
 // sub-chunks) the partition took 0.93 ms against 0.87 and the unpartition 1.36
 // against 1.25. So do those of jobs that would be left with fewer than 64
 // sub-chunks (10,000 samples on 4 workers, 5 epochs: prefetch tiles 16 -> 40 us).
-inline void fold_epochs(SegParams& p) {
+// `fewest` unfolded sub-chunks at least, for passes that take longer over a
+// long sub-chunk than over many short ones.
+inline void fold_epochs(SegParams& p, int64_t fewest = 0) {
   const int64_t nsc = ceil_div(p.M_max, kSC);
-  if (p.L > kSC / 2 || p.N * nsc < 64) return;
+  if (p.L > kSC / 2 || p.N * nsc < 64 || p.N * p.E * int64_t(p.nsc) < fewest) return;
   p.nsc = int32_t(nsc);
   p.emul = p.E;
   p.E = 1;

@@ -56,6 +56,7 @@
 //                padding.
 #include <limits.h>
 
+#include <algorithm>
 #include <new>
 
 #include "gather.hpp"
@@ -879,6 +880,24 @@ st_fill(SegParams p, int64_t d0, uint32_t nch, int64_t nparts, SpanSums S,
   }
 }
 
+// The queues' passes take one workgroup per sub-chunk, whose waves step through
+// its positions, so folded epochs pay once there are more short sub-chunks than
+// a folded one has steps for: 400 and a fifth of its reads, at most 1,900. Measured over 515
+// jobs of 4 to 600 workers with epochs of 64 to 9,000 reads (call with folded
+// epochs over call without): 671 reads, 6 epochs, 70 workers 54 against 39 us;
+// 1,449 reads, 5 epochs, 64 workers 55 and 45; 226 reads, 5 epochs, 203 workers 37
+// and 40; 393 reads, 39 epochs, 99 workers 74 and 97; 83 reads, 38 epochs, 426
+// workers 67 and 282. With 256 folded sub-chunks and more the steps of one no
+// longer show (5,939 reads, 3 epochs, 203 workers 178 and 177), with 512 where the
+// codes are counted one by one (more than 8 tiers; 3,355 reads, 5 epochs, 170
+// workers, 9 tiers 117 and 101) and a sub-chunk's steps take half as long again.
+int64_t prefetch_fold(const SegParams& p, int32_t J) {
+  const int64_t nsc = ceil_div(p.M_max, kSC);
+  if (nsc < 1 || p.N * nsc >= (J > 8 ? 512 : 256)) return 0;
+  const int64_t fewest = std::min<int64_t>(400 + p.M_max / nsc / 5, 1900);
+  return J > 8 ? fewest * 3 / 2 : fewest;
+}
+
 int prefetch_impl(const nopfs_job* job, const int32_t* R, const int8_t* tier, int32_t J,
                   int32_t* order, int64_t* qlen, hipStream_t st) {
   Shape s;
@@ -892,7 +911,7 @@ int prefetch_impl(const nopfs_job* job, const int32_t* R, const int8_t* tier, in
   const int64_t ntiles = s.N * int64_t(p.nbk);
   if (s.N * s.E * int64_t(p.nsc) >= (int64_t(1) << 31) || ntiles >= (int64_t(1) << 31))
     return fail(NOPFS_ERANGE, "job too large for one launch");
-  fold_epochs(p);
+  fold_epochs(p, prefetch_fold(p, J));
   const uint32_t nch = uint32_t(p.E) * uint32_t(p.nsc);  // sub-chunks per worker
   const int64_t nblk = s.N * int64_t(nch);
   Scratch scr(st);

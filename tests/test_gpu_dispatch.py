@@ -76,3 +76,25 @@ def test_threads_per_run(oracle, shape):
     want = oracle.access_stats(rjob, R)
     _same("count", count, want[0])
     _same("first", first, want[1])
+
+
+# prefetch queues: epochs folded or not, with up to 8 tiers and more
+@pytest.mark.parametrize("J", [2, 8, 9])
+@pytest.mark.parametrize("shape", [
+    (70 * 671, 6, 70, 1, 0, 1),      # 420 short sub-chunks, 70 folded ones
+    (64 * 150 + 3, 9, 64, 1, 0, 2),  # 576 and 64 of 1,350 reads
+    (99 * 393, 39, 99, 1, 1, 3),     # 3,861 and 99
+    (258 * 90, 2, 258, 1, 0, 4),     # 516 and 258
+    (33 * 2_000, 18, 33, 1, 0, 5),   # 594 and 99, three to a row
+], ids=lambda s: f"F{s[0]}E{s[1]}N{s[2]}" if isinstance(s, tuple) else None)
+def test_prefetch_fold(oracle, shape, J):
+    F, E, N = shape[:3]
+    rjob = oracle.make_job(*shape)
+    R = oracle.access_streams(rjob)
+    _, first = oracle.access_stats(rjob, R)
+    tier = np.random.default_rng(J).integers(-1, J, (N, F)).astype(np.int8)
+    order, qlen = nopfs.prefetch_order(nopfs.Job(*shape), _dev(R), _dev(tier), J)
+    torch.cuda.synchronize()
+    eo, eq = oracle.prefetch_order(rjob, R, first, tier, J)
+    _same("order", order, eo)
+    _same("qlen", qlen, eq)
