@@ -98,3 +98,20 @@ def test_prefetch_fold(oracle, shape, J):
     eo, eq = oracle.prefetch_order(rjob, R, first, tier, J)
     _same("order", order, eo)
     _same("qlen", qlen, eq)
+
+
+# the tier plan's slices: one per row, several, and cut where that evens the load
+@pytest.mark.parametrize("F,N", [(40_000, 399), (600_000, 3), (70_001, 130), (524_289, 2), (9_000, 1)])
+def test_plan_slices(oracle, F, N):
+    shape = (F, 2, N, 1, 0, F)
+    sizes = wl.random_sizes(F, N, 1_000, 2_000_000)
+    tot = int(sizes.sum())
+    caps = [tot // 40, tot // 5]
+    rjob, job, sd = oracle.make_job(*shape), nopfs.Job(*shape), _dev(sizes)
+    want = oracle.full_pipeline(rjob, sizes, np.array(caps, np.int64))
+    got = nopfs.plan_job(job, sd, caps)
+    tier, used = nopfs.tier_plan(job, _dev(want["count"]), _dev(want["first"]), sd, caps)
+    torch.cuda.synchronize()
+    for what, t, u in (("fused", got["tier"], got["used"]), ("stage", tier, used)):
+        _same(what + " tier", t, want["tier"])
+        _same(what + " used", u, want["used"])
