@@ -33,7 +33,8 @@
 //                   per tier. A worker whose candidate list overflowed takes
 //                   an exact weighted radix select over its full row for
 //                   every cut instead, then a full rewrite of the row (slow,
-//                   rarely taken).
+//                   rarely taken with few tiers; plan_exact, a launch of its
+//                   own, for many tiers and workers).
 #include <limits.h>
 #include <math.h>
 
@@ -119,12 +120,14 @@ __device__ __forceinline__ uint64_t rank_key(const PlanArgs& a, uint32_t c, int3
 constexpr int kInitThreads = 256;
 __global__ void __launch_bounds__(kInitThreads)
 plan_init(PlanArgs a, int64_t hn, uint32_t zb, uint64_t* __restrict__ H, int32_t* __restrict__ ccount,
-          const int64_t* __restrict__ sizes, uint64_t* __restrict__ binsum, ClassTable* __restrict__ gct) {
+          int32_t* __restrict__ rows, const int64_t* __restrict__ sizes, uint64_t* __restrict__ binsum,
+          ClassTable* __restrict__ gct) {
   if (blockIdx.x < zb) {
     const int64_t stride = int64_t(zb) * kInitThreads;
     const int64_t t0 = int64_t(blockIdx.x) * kInitThreads + threadIdx.x;
     for (int64_t t = t0; t < hn; t += stride) H[t] = 0;
     for (int64_t t = t0; t < a.N; t += stride) ccount[t] = 0;
+    if (rows && t0 == 0) rows[0] = 0;
     return;
   }
   const uint32_t blk = blockIdx.x - zb;
@@ -587,6 +590,15 @@ __device__ void plan_exact(const PlanArgs& a, int64_t i, const uint8_t* __restri
   }
 }
 
+__global__ void __launch_bounds__(1024)
+plan_exact_rows(PlanArgs a, const int32_t* __restrict__ rows, const uint8_t* __restrict__ count,
+                const int32_t* __restrict__ first, const int64_t* __restrict__ sizes,
+                int8_t* __restrict__ tier, int64_t* __restrict__ used) {
+  __shared__ ExactSmem sh;
+  if (int32_t(blockIdx.x) >= rows[0]) return;
+  plan_exact(a, rows[1 + blockIdx.x], count, first, sizes, tier, used, sh);
+}
+
 // -- exact resolution of the candidates --------------------------------------------------
 struct ResolveSmem {
   uint64_t key[kCandMax];  // rank keys; after the sort, bytes up to and with each candidate
@@ -596,11 +608,13 @@ struct ResolveSmem {
   uint64_t tmp[65];
 };
 
+// A worker whose list overflowed takes its full row here, or, where there is a
+// list of `rows` ([0] their number), is left to plan_exact_rows.
 __global__ void __launch_bounds__(kResolveThreads)
 plan_resolve(PlanArgs a, const uint64_t* __restrict__ H, const CandRec* __restrict__ cand,
              const int32_t* __restrict__ ccount, const uint8_t* __restrict__ count,
              const int32_t* __restrict__ first, const int64_t* __restrict__ sizes,
-             int8_t* __restrict__ tier, int64_t* __restrict__ used) {
+             int8_t* __restrict__ tier, int64_t* __restrict__ used, int32_t* __restrict__ rows) {
   __shared__ union {
     ResolveSmem r;
     ExactSmem x;
@@ -609,7 +623,8 @@ plan_resolve(PlanArgs a, const uint64_t* __restrict__ H, const CandRec* __restri
   const int64_t i = blockIdx.x;
   const int32_t n = ccount[i];
   if (n > a.cmax) {  // uniform
-    plan_exact(a, i, count, first, sizes, tier, used, sh.x);
+    if (!rows) plan_exact(a, i, count, first, sizes, tier, used, sh.x);
+    else if (threadIdx.x == 0) rows[1 + atomicAdd(&rows[0], 1)] = int32_t(i);
     return;
   }
   const uint64_t* Hi = H + i * int64_t(a.nbin + 1);
@@ -1104,6 +1119,7 @@ void class_bins(int64_t F, int64_t E, int64_t L, uint16_t* nbc, uint32_t* nbin1)
 struct PlanBufs {
   uint64_t *H, *binsum, *Z;
   int32_t *ranges, *ccount;
+  int32_t* rows;  // the workers whose list overflowed, NULL where they are not listed
   CandRec* cand;
 };
 
@@ -1146,12 +1162,22 @@ int plan_begin(const Shape& s, const PlanArgs& a, const int64_t* sizes, ClassTab
   if ((rc = scr.alloc_n(&b->binsum, size_t(a.nb0)))) return rc;
   if ((rc = scr.alloc_n(&b->Z, size_t(s.N) * a.nb0))) return rc;
   if ((rc = scr.alloc_n(&b->ranges, size_t(s.N * 2 * a.J)))) return rc;
-  if ((rc = scr.alloc_n(&b->ccount, size_t(s.N)))) return rc;
+  // The candidates of a call are about 256 cells (a class-0 bin) for every bin
+  // between a tier's earliest and latest cut, 1 + 2 + ... + J bins in all: with
+  // more than four tiers the list of 4,096 may overflow on every worker. A full
+  // row in the resolution's own workgroup (83 KB of LDS) leaves a compute unit
+  // one row at a time, which costs where there are more workers than units (9
+  // tiers: 281 workers, 1,851,087 samples 133 ms, listed 103; 403 workers,
+  // 1,170,715 samples 88 and 70); fewer workers, or tiers that hardly overflow,
+  // save the second launch (5 us).
+  const bool list = s.N > 256 && a.J > 4;
+  if ((rc = scr.alloc_n(&b->ccount, size_t(s.N) + (list ? size_t(s.N) + 1 : 0)))) return rc;
+  b->rows = list ? b->ccount + s.N : nullptr;
   if ((rc = scr.alloc_n(&b->cand, size_t(s.N * a.cmax)))) return rc;
   const uint32_t zb = uint32_t(std::min(ceil_div(hn, 1024), int64_t(65536)));
   const uint32_t blocks = zb + uint32_t(ceil_div(a.nb0, 4)) + (gct ? 1u : 0u);
   return launch("plan_init", plan_init, dim3(blocks), dim3(kInitThreads), 0, st, a, hn, zb, b->H,
-                b->ccount, sizes, b->binsum, gct);
+                b->ccount, b->rows, sizes, b->binsum, gct);
 }
 
 // Exact resolution of the candidates, or of the whole row for workers whose
@@ -1159,9 +1185,14 @@ int plan_begin(const Shape& s, const PlanArgs& a, const int64_t* sizes, ClassTab
 int plan_end(const Shape& s, const PlanArgs& a, const PlanBufs& b, const uint8_t* count,
              const int32_t* first, const int64_t* sizes, int8_t* tier, int64_t* used,
              hipStream_t st) {
-  return launch("plan_resolve", plan_resolve, dim3(uint32_t(s.N)), dim3(kResolveThreads), 0, st, a,
-                (const uint64_t*)b.H, (const CandRec*)b.cand, (const int32_t*)b.ccount, count, first,
-                sizes, tier, used);
+  int rc;
+  if ((rc = launch("plan_resolve", plan_resolve, dim3(uint32_t(s.N)), dim3(kResolveThreads), 0, st, a,
+                   (const uint64_t*)b.H, (const CandRec*)b.cand, (const int32_t*)b.ccount, count, first,
+                   sizes, tier, used, b.rows)))
+    return rc;
+  if (!b.rows) return NOPFS_OK;
+  return launch("plan_exact", plan_exact_rows, dim3(uint32_t(s.N)), dim3(1024), 0, st, a,
+                (const int32_t*)b.rows, count, first, sizes, tier, used);
 }
 
 }  // namespace

@@ -115,3 +115,28 @@ def test_plan_slices(oracle, F, N):
     for what, t, u in (("fused", got["tier"], got["used"]), ("stage", tier, used)):
         _same(what + " tier", t, want["tier"])
         _same(what + " used", u, want["used"])
+
+
+# workers whose candidates overflow: resolved in place, or listed and taken by a
+# launch of their own (more than 256 workers and 4 tiers); every worker or none
+@pytest.mark.parametrize("N,J,listed", [(256, 5, False), (257, 4, False), (257, 5, True), (300, 9, True)])
+@pytest.mark.parametrize("cap", [0, 8], ids=["default", "overflow"])
+def test_plan_overflow(oracle, N, J, listed, cap):
+    shape = (9_001, 3, N, 1, 0, N + J)
+    sizes = wl.random_sizes(shape[0], J, 1_000, 2_000_000)
+    tot = int(sizes.sum())
+    caps = [tot // (3 * J) + 1_000 * j for j in range(J)]
+    rjob, job, sd = oracle.make_job(*shape), nopfs.Job(*shape), _dev(sizes)
+    want = oracle.full_pipeline(rjob, sizes, np.array(caps, np.int64))
+    c, f = _dev(want["count"]), _dev(want["first"])
+    nopfs.debug_set(2, cap)
+    try:
+        (tier, used), names = _launched(lambda: nopfs.tier_plan(job, c, f, sd, caps))
+        got = nopfs.plan_job(job, sd, caps)
+        torch.cuda.synchronize()
+    finally:
+        nopfs.debug_set(2, 0)
+    for what, t, u in (("stage", tier, used), ("fused", got["tier"], got["used"])):
+        _same(what + " tier", t, want["tier"])
+        _same(what + " used", u, want["used"])
+    assert ("plan_exact" in names) == listed, names
