@@ -22,11 +22,13 @@ constexpr int kGatherWs = 14;                 // window: 2^14 samples of 8-byte 
 constexpr int kGatherWin = 1 << kGatherWs;    // 8-byte values held in LDS (128 KB)
 constexpr int kGThreads = 1024;
 // A tile holds about kGReads reads: its window's values (128 KB of LDS) are
-// loaded once for all of them. With fewer than kGTiles such tiles (four per
-// compute unit, one at a time on each) they are made smaller, down to kGMin
-// reads.
-constexpr double kGReads = 163840, kGMin = 4096;
-constexpr int64_t kGTiles = 1024;
+// loaded once for all of them, which takes as long as kGLoad reads do (10.5 us
+// and 0.65 ns a read: 166 tiles of 65,000 reads 53 us, 1,162 of 9,300 83 us).
+// Where that makes fewer than kGRounds rounds of tiles (one at a time per compute
+// unit), their number follows the last round: the cheapest of the splits that
+// fill 1 to kGRounds rounds.
+constexpr double kGReads = 163840, kGLoad = 16384;
+constexpr int64_t kGRounds = 8, kGUnits = 256;
 constexpr int kGRuns = 1024;                  // runs per pass of a tile
 constexpr uint32_t kGLongRun = 96;            // mean reads per run from which waves take whole runs
 static_assert(kGRuns % kGThreads == 0, "gather tile shape");
@@ -46,19 +48,26 @@ struct GatherLds {
   uint32_t tmp[65];
 };
 
-// Runs per tile of a gather pass, and from it the groups per window. At
-// ImageNet-22k a window has 4,300 runs of 38 reads per 32 rows, one tile; at
-// ImageNet-1k on 16 workers 7,040 runs of 420 reads, which took one tile per
-// window (40 workgroups on 256 compute units: 3.3 ms for the staging
-// schedule's pass, 0.20 ms now).
+// Runs per tile of a gather pass, and from it the groups per window.
 inline int64_t gather_runs(const SegParams& p) {
   const int64_t runs = p.N * p.nsc;
   const double run = run_mean(p);  // reads
   int64_t per = int64_t(kGReads / run) + 1;
-  const int64_t split = ceil_div(runs * p.nbk, kGTiles);  // gives kGTiles tiles
-  const int64_t least = int64_t(kGMin / run) + 1;
-  if (per > split) per = split > least ? split : least;
-  return per < runs ? per : runs;
+  per = per < runs ? per : runs;
+  if (runs < 1 || ceil_div(runs, per) * p.nbk >= kGRounds * kGUnits) return per;
+  const double win = double(int64_t(1) << p.ws);
+  const double load = kGLoad * (double(p.F) < win ? double(p.F) / win : 1.0);
+  double best = 0;
+  for (int64_t r = 1; r <= kGRounds; ++r) {
+    int64_t g = r * kGUnits / p.nbk;  // groups per window that fill r rounds
+    g = g < 1 ? 1 : (g < runs ? g : runs);
+    const double cost = double(ceil_div(g * p.nbk, kGUnits)) * (load + run * double(runs) / double(g));
+    if (best == 0 || cost < best) {
+      best = cost;
+      per = ceil_div(runs, g);
+    }
+  }
+  return per;
 }
 
 // Window width (log2) of a gather pass: kGatherWs, or wider by the test

@@ -140,3 +140,28 @@ def test_plan_overflow(oracle, N, J, listed, cap):
         _same(what + " tier", t, want["tier"])
         _same(what + " used", u, want["used"])
     assert ("plan_exact" in names) == listed, names
+
+
+# the gather passes' splits: one window and many, tiles of one run, of all runs
+# of a window and of part of them, fewer runs than compute units and more
+@pytest.mark.parametrize("shape", [
+    (100, 3, 1, 1, 0, 1), (3_000, 2, 1000, 1, 0, 2), (20_000, 3, 300, 1, 0, 3), (40_000, 30, 3, 1, 0, 4),
+    (1_100_003, 2, 5, 1, 0, 5), (5_000_001, 1, 2, 1, 0, 6), (600_011, 6, 40, 1, 1, 7),
+], ids=lambda s: f"F{s[0]}E{s[1]}N{s[2]}")
+@pytest.mark.parametrize("wide", [False, True], ids=["sizes32", "sizes64"])
+def test_gather_splits(oracle, shape, wide):
+    F, _, N = shape[:3]
+    rjob, job = oracle.make_job(*shape), nopfs.Job(*shape)
+    R = oracle.access_streams(rjob)
+    sizes = wl.random_sizes(F, shape[-1], 1, 1 << (36 if wide else 20))
+    tier = np.random.default_rng(F).integers(-1, 2, (N, F)).astype(np.int8)
+    d0 = int(sizes.sum()) // (5 * N)
+    Rd, sd, td = _dev(R), _dev(sizes), _dev(tier)
+    fill = nopfs.staging_schedule(job, Rd, sd, d0)
+    src, t = nopfs.fetch_model(job, Rd, td, sd, nopfs.make_model(**wl.LASSEN_MODEL))
+    torch.cuda.synchronize()
+    _same("fill", fill, oracle.staging_schedule(rjob, R, sizes, d0))
+    es, et = oracle.fetch_model(rjob, R, tier, sizes, oracle.make_model(**wl.LASSEN_MODEL))
+    _same("src", src, es)
+    # the same positive terms summed in another order: 8 (n + 2) 2^-53 of t on rows of n reads
+    assert np.allclose(t.cpu().numpy(), et, rtol=8 * (R.shape[1] + 2) * 2.0 ** -53, atol=0)
