@@ -335,8 +335,11 @@ __device__ __forceinline__ void fm_load(const SubChunk& s, const uint32_t* __res
   const uint32_t* pk = Pk + s.base;
   const uint64_t* z = zP + s.base;
   const uint32_t len = uint32_t(s.len);
+  g.j[0] = pk[threadIdx.x < len ? threadIdx.x : 0];
+  g.v[0] = z[threadIdx.x < len ? threadIdx.x : 0];
+  if (len <= uint32_t(kFmThreads)) return;  // uniform: a short row's span
 #pragma unroll
-  for (int u = 0; u < kFmPer; ++u) {
+  for (int u = 1; u < kFmPer; ++u) {
     const uint32_t q = uint32_t(u) * kFmThreads + threadIdx.x;
     g.j[u] = pk[q < len ? q : 0];
     g.v[u] = z[q < len ? q : 0];
@@ -346,9 +349,13 @@ __device__ __forceinline__ void fm_load(const SubChunk& s, const uint32_t* __res
 // Every entry of the span into the LDS slot of its stream position. Ends
 // with a barrier.
 __device__ __forceinline__ void fm_place(const SubChunk& s, const FmRegs& g, FmLds& L) {
+  const uint32_t len = uint32_t(s.len);
+  if (threadIdx.x < len) L.sv[fm_slot(int(g.j[0] & kJMask))] = g.v[0];
+  if (len > uint32_t(kFmThreads)) {  // uniform
 #pragma unroll
-  for (int u = 0; u < kFmPer; ++u)
-    if (uint32_t(u) * kFmThreads + threadIdx.x < uint32_t(s.len)) L.sv[fm_slot(int(g.j[u] & kJMask))] = g.v[u];
+    for (int u = 1; u < kFmPer; ++u)
+      if (uint32_t(u) * kFmThreads + threadIdx.x < len) L.sv[fm_slot(int(g.j[u] & kJMask))] = g.v[u];
+  }
   __syncthreads();
 }
 
@@ -402,8 +409,9 @@ fm_final(SegParams p, const uint32_t* __restrict__ Pk, const uint64_t* __restric
       return code;
     };
     double ta = 0, tu = 0;
+    const int mine_n = x0 < len ? kFmPer : 0;  // threads behind the span's end take no sweep
 #pragma unroll 1
-    for (int u0 = 0; u0 < kFmPer; u0 += 4) {
+    for (int u0 = 0; u0 < mine_n; u0 += 4) {
       uint32_t cw = 0;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
@@ -422,7 +430,7 @@ fm_final(SegParams p, const uint32_t* __restrict__ Pk, const uint64_t* __restric
     // at the sums' size per position, not one per read of the thread.
     double la = 0, lu = 0, tm = -INFINITY;
 #pragma unroll 4
-    for (int u = 0; u < kFmPer; ++u) {
+    for (int u = 0; u < mine_n; ++u) {
       double rd, uu;
       times(u, rd, uu);
       la += rd;
@@ -447,7 +455,7 @@ fm_final(SegParams p, const uint32_t* __restrict__ Pk, const uint64_t* __restric
     // the slots this thread read its entries from
     la = lu = 0;
 #pragma unroll 4
-    for (int u = 0; u < kFmPer; ++u) {
+    for (int u = 0; u < mine_n; ++u) {
       double rd, uu;
       times(u, rd, uu);
       la += rd;
@@ -467,6 +475,7 @@ fm_final(SegParams p, const uint32_t* __restrict__ Pk, const uint64_t* __restric
     const uint8_t* code = reinterpret_cast<const uint8_t*>(L.code);
 #pragma unroll 4
     for (int u = 0; u < kFmPer; ++u) {
+      if (u * kFmThreads >= len) break;  // uniform
       const int x = u * kFmThreads + int(threadIdx.x);
       if (x < len) {
         const uint32_t c = code[x];

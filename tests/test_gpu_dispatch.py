@@ -165,3 +165,19 @@ def test_gather_splits(oracle, shape, wide):
     _same("src", src, es)
     # the same positive terms summed in another order: 8 (n + 2) 2^-53 of t on rows of n reads
     assert np.allclose(t.cpu().numpy(), et, rtol=8 * (R.shape[1] + 2) * 2.0 ** -53, atol=0)
+
+
+# spans of the fetch model that do not fill their workgroup: rows around 16 reads
+# (a thread's), 1,024 (one load per thread) and their multiples
+@pytest.mark.parametrize("M", [1, 15, 16, 17, 1023, 1024, 1025, 2049, 16_383, 16_385, 17_408, 17_409])
+def test_short_spans(oracle, M):
+    shape = (3 * M - 1, 1, 3, 1, 0, M)  # the last row is one read shorter
+    rjob, job = oracle.make_job(*shape), nopfs.Job(*shape)
+    R = oracle.access_streams(rjob)
+    sizes = wl.random_sizes(shape[0], M, 1, 1 << 20)
+    tier = np.random.default_rng(M).integers(-1, 2, (3, shape[0])).astype(np.int8)
+    src, t = nopfs.fetch_model(job, _dev(R), _dev(tier), _dev(sizes), nopfs.make_model(**wl.LASSEN_MODEL))
+    torch.cuda.synchronize()
+    es, et = oracle.fetch_model(rjob, R, tier, sizes, oracle.make_model(**wl.LASSEN_MODEL))
+    _same("src", src, es)
+    assert np.allclose(t.cpu().numpy(), et, rtol=8 * (R.shape[1] + 2) * 2.0 ** -53, atol=0)
