@@ -714,9 +714,14 @@ int streams_impl(const nopfs_job* job, int32_t* R, hipStream_t st, int32_t e_beg
   // 2^m buckets per epoch, the fewest with a mean of at most kMeanBucket
   uint32_t m = 0;
   while (m < 31 && (s.F >> m) > kMeanBucket) ++m;
-  // a job of few buckets: smaller ones (of more than 512 keys), until there are
-  // two per compute unit to sort
-  while ((s.F >> m) > 2 * kSmallBucket && (s.E << m) < kFewBuckets) ++m;
+  // a job of few buckets: smaller ones (of more than 512 keys), up to two per
+  // compute unit to sort, or past that where an epoch has at most 8, on whose
+  // counts the scatter's atomics would meet (stream call: 437,946 ids x 7, 64
+  // buckets an epoch 66 us, 128 70; 58,212 x 13, 32 and 64: 47 and 57; but 24,388
+  // x 97, 4 and 8: 182 and 129)
+  while ((s.F >> m) > 2 * kSmallBucket &&
+         (s.E << m) < kFewBuckets && ((s.E << (m + 1)) <= kFewBuckets || m < 4))
+    ++m;
   const uint32_t nb = 1u << m;
   const uint32_t nbw = nb < kMaxWin ? nb : kMaxWin;
   // chunks: multiples of a scatter round, at most kMaxChunks per epoch

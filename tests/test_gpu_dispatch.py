@@ -181,3 +181,12 @@ def test_short_spans(oracle, M):
     es, et = oracle.fetch_model(rjob, R, tier, sizes, oracle.make_model(**wl.LASSEN_MODEL))
     _same("src", src, es)
     assert np.allclose(t.cpu().numpy(), et, rtol=8 * (R.shape[1] + 2) * 2.0 ** -53, atol=0)
+
+
+# buckets of small jobs: up to 512, past that with at most 8 an epoch, and not
+@pytest.mark.parametrize("F,E", [(58_212, 13), (437_946, 7), (24_388, 97), (61_000, 16), (61_000, 17), (15_000, 40)])
+def test_stream_buckets(oracle, F, E):
+    shape = (F, E, 3, 1, 0, F + E)
+    got = nopfs.access_streams(nopfs.Job(*shape))
+    torch.cuda.synchronize()
+    _same("R", got, oracle.access_streams(oracle.make_job(*shape)))
