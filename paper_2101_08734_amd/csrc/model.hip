@@ -335,11 +335,8 @@ __device__ __forceinline__ void fm_load(const SubChunk& s, const uint32_t* __res
   const uint32_t* pk = Pk + s.base;
   const uint64_t* z = zP + s.base;
   const uint32_t len = uint32_t(s.len);
-  g.j[0] = pk[threadIdx.x < len ? threadIdx.x : 0];
-  g.v[0] = z[threadIdx.x < len ? threadIdx.x : 0];
-  if (len <= uint32_t(kFmThreads)) return;  // uniform: a short row's span
 #pragma unroll
-  for (int u = 1; u < kFmPer; ++u) {
+  for (int u = 0; u < kFmPer; ++u) {
     const uint32_t q = uint32_t(u) * kFmThreads + threadIdx.x;
     g.j[u] = pk[q < len ? q : 0];
     g.v[u] = z[q < len ? q : 0];
@@ -349,13 +346,9 @@ __device__ __forceinline__ void fm_load(const SubChunk& s, const uint32_t* __res
 // Every entry of the span into the LDS slot of its stream position. Ends
 // with a barrier.
 __device__ __forceinline__ void fm_place(const SubChunk& s, const FmRegs& g, FmLds& L) {
-  const uint32_t len = uint32_t(s.len);
-  if (threadIdx.x < len) L.sv[fm_slot(int(g.j[0] & kJMask))] = g.v[0];
-  if (len > uint32_t(kFmThreads)) {  // uniform
 #pragma unroll
-    for (int u = 1; u < kFmPer; ++u)
-      if (uint32_t(u) * kFmThreads + threadIdx.x < len) L.sv[fm_slot(int(g.j[u] & kJMask))] = g.v[u];
-  }
+  for (int u = 0; u < kFmPer; ++u)
+    if (uint32_t(u) * kFmThreads + threadIdx.x < uint32_t(s.len)) L.sv[fm_slot(int(g.j[u] & kJMask))] = g.v[u];
   __syncthreads();
 }
 
