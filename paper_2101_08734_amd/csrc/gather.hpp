@@ -9,8 +9,9 @@
 // order, a row's spans in order); tiles are window-major, so the groups of
 // one window and the tiles of neighbouring windows (whose runs adjoin in
 // memory) run together on one XCD. Consecutive threads take consecutive reads
-// of the tile's runs, so loads and stores go out in run-long pieces (19 reads
-// on average at ImageNet-22k) instead of one store per lane into 64
+// of the tile's runs, so loads and stores go out in run-long pieces (at
+// ImageNet-22k 19 reads on average in the fetch model's windows of 2^14 samples,
+// 38 in the staging schedule's of 2^15) instead of one store per lane into 64
 // different runs.
 #pragma once
 
@@ -30,7 +31,14 @@ constexpr int kGThreads = 1024;
 constexpr double kGReads = 163840, kGLoad = 16384;
 constexpr int64_t kGRounds = 8, kGUnits = 256;
 constexpr int kGRuns = 1024;                  // runs per pass of a tile
-constexpr uint32_t kGLongRun = 96;            // mean reads per run from which waves take whole runs
+// Mean reads per run from which waves take whole runs. With eight reads per
+// thread (staging) a wave takes 512 of a run at a time: runs of 107 reads 206 us
+// so and 149 by search, of 153 123 and 112, of 199 137 and 145, of 268 93 and 111,
+// of 1,342 37 and 53. With four (fetch model; each read also waits for its own
+// tier, which the search's shorter steps hide): 99 reads 366 and 279 us, 210 715
+// and 583, 383 137 and 120, 5,370 38 and 35, 8,950 36 and 38, 10,000 21 and 25.
+template <int kPer>
+constexpr uint32_t kGLongRun = kPer >= 8 ? 192 : 8192;
 static_assert(kGRuns % kGThreads == 0, "gather tile shape");
 
 // kChunk: reads per inner pass of the workgroup; each thread requests
@@ -145,7 +153,7 @@ __device__ __forceinline__ void gather_tile(const SegParams& p, const uint32_t* 
       }
       if (threadIdx.x == 0) L.pref[nr] = total;
       __syncthreads();
-      if (total >= kGLongRun * nr) {  // uniform
+      if (total >= kGLongRun<kPer> * nr) {  // uniform
         // long runs: kG waves to a run (one where there are as many runs as
         // waves), each lane's loads of a step together, no lookup per read.
         constexpr uint32_t kWaves = kGThreads / 64, kStep = 64 * kPer;
@@ -180,8 +188,7 @@ __device__ __forceinline__ void gather_tile(const SegParams& p, const uint32_t* 
       // hold the total): ten steps in LDS, and no barrier, so that the waves'
       // loads overlap. A map of 4,096 reads at a time, written by the runs'
       // owners between barriers, took 4.40 ms in the fetch model's pass at
-      // ImageNet-22k (38 reads a run), this 3.88; 0.237 and 0.231 ms in the
-      // staging schedule's at ImageNet-1k, 16 workers.
+      // ImageNet-22k (19 reads a run), this 3.88.
       constexpr uint32_t kSpan = 64 * kPer;
       const uint32_t lane = threadIdx.x & 63;
       for (uint32_t x0 = (threadIdx.x >> 6) * kSpan; x0 < total; x0 += kChunk) {
