@@ -982,17 +982,17 @@ static size_t partition_smem(const SegParams& p) {
 int run_partition(const SegParams& p, const int32_t* R, Scratch& scr, uint32_t** Pk,
                   uint16_t** OT, hipStream_t st) {
   int rc;
-  uint16_t* O;
+  uint16_t* O = nullptr;
   const size_t on = size_t(p.N * p.E * p.nsc) * (p.nbk + 1);
-  if ((rc = scr.alloc_n(Pk, size_t(p.N * p.M_max)))) return rc;
-  if ((rc = scr.alloc_n(&O, on))) return rc;
-  if ((rc = scr.alloc_n(OT, on))) return rc;
   // few offsets go straight to their window-major places (a launch less, 5 us);
   // many would scatter 2-byte stores over the table
   const bool direct = on <= kDirectOffsets;
+  if ((rc = scr.alloc_n(Pk, size_t(p.N * p.M_max)))) return rc;
+  if (!direct && (rc = scr.alloc_n(&O, on))) return rc;
+  if ((rc = scr.alloc_n(OT, on))) return rc;
   const int64_t wgs = p.N * p.E * p.nsc;
   if ((rc = launch("seg_partition", seg_partition, dim3(uint32_t(wgs)), dim3(kPartThreads),
-                   partition_smem(p), st, p, R, *Pk, direct ? (uint16_t*)nullptr : O, *OT)))
+                   partition_smem(p), st, p, R, *Pk, O, *OT)))
     return rc;
   if (direct) return NOPFS_OK;
   const int64_t runs = int64_t(p.E) * p.nsc;

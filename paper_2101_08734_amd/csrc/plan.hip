@@ -1161,7 +1161,8 @@ int plan_begin(const Shape& s, const PlanArgs& a, const int64_t* sizes, ClassTab
   if ((rc = scr.alloc_n(&b->H, size_t(hn)))) return rc;
   if ((rc = scr.alloc_n(&b->binsum, size_t(a.nb0)))) return rc;
   if ((rc = scr.alloc_n(&b->Z, size_t(s.N) * a.nb0))) return rc;
-  if ((rc = scr.alloc_n(&b->ranges, size_t(s.N * 2 * a.J)))) return rc;
+  b->ranges = nullptr;  // in memory only for the dense passes; the fused call's cuts stay in plan_cut
+  if (!gct && (rc = scr.alloc_n(&b->ranges, size_t(s.N * 2 * a.J)))) return rc;
   // The candidates of a call are about 256 cells (a class-0 bin) for every bin
   // between a tier's earliest and latest cut, 1 + 2 + ... + J bins in all: with
   // more than four tiers the list of 4,096 may overflow on every worker. A full
