@@ -131,11 +131,26 @@ def committed_traffic(workload, kernel):
 
 POLICY_NAMES = ("perfect", "naive", "staging", "nopfs")
 BUFFER_NOTE = ("one workgroup per worker accepts its candidates batch by batch: bound by the "
-               "batches' barriers and scans and by latency, not by HBM bandwidth; frac is the HBM "
-               "fraction for reference")
-POLICY_NOTE = ("one workgroup per worker scans its chains chunk by chunk: bound by the "
-               "128-byte lines that the random gathers of the sizes fetch and by instruction "
-               "issue, not by its algorithmic bytes; frac is their fraction for reference")
+               "batches' barriers and scans and by the latency of their look-ups, not by HBM "
+               "bandwidth; frac is the HBM fraction for reference")
+BUFFER_NOTE_STREAM = ("one wave per worker steps through its reads in stream order: bound by that "
+                      "chain's latency, not by HBM bandwidth; frac is the HBM fraction for "
+                      "reference")
+
+
+def policy_note(name, N, F, reads):
+    """What bounds a policy call, as the counters have it for the workloads here: latency
+    with fewer workers than half of the 256 compute units or rows of few chunks; else
+    the size gathers' lines, for the staging policies (more work per read) only with a
+    size table beyond the XCDs' 32 MB of L2."""
+    if N < 128 or reads < 16384:
+        s = "the latency and barriers of the chunks"
+    elif name in ("perfect", "naive") or 8 * F > 32 << 20:
+        s = "the 128-byte lines that the random gathers of the sizes fetch"
+    else:
+        s = "the chunks' barriers and latency"
+    return ("one workgroup per worker scans its chains chunk by chunk: bound by " + s +
+            ", not by its algorithmic bytes; frac is their fraction for reference")
 
 
 def _kernel_short_name(full):
@@ -460,7 +475,7 @@ def time_buffer(nopfs, torch, w, job, M, M_w, R, nxt, sizes, steps, warmup, stre
     out["hit_rate"] = round(int(h[:, 0].sum()) / A, 4)
     out["hit_bytes"] = int(h[:, 1].sum())
     out["reads_per_s_per_worker"] = round(A / job.N / (out["buffer_sim"]["ms_per_call"] * 1e-3), 1)
-    out["buffer_sim"]["roofline"]["note"] = BUFFER_NOTE
+    out["buffer_sim"]["roofline"]["note"] = BUFFER_NOTE if replay == "kb_sim" else BUFFER_NOTE_STREAM
     return out
 
 
@@ -491,7 +506,7 @@ def time_policies(nopfs, torch, wl, w, job, M, M_w, R, tier, sizes, steps, warmu
         J = model.J
         out[name]["slowest_worker_s"] = round(float(f.max()), 3)
         out[name]["mean_worker_s"] = round(float(f.mean()), 3)
-        out[name]["roofline"]["note"] = POLICY_NOTE
+        out[name]["roofline"]["note"] = policy_note(name, job.N, job.F, max(M_w))
         out[name]["fetch_s"] = {"pfs": round(float(tot[0]), 1),
                                 "remote": round(float(tot[1:1 + J].sum()), 1),
                                 "own": round(float(tot[1 + J:].sum()), 1)}

@@ -38,11 +38,15 @@
 //               narrowed to a batch of few candidates, then found by taking
 //               candidates back from the load, last to first, at every
 //               position in question.
-// ImageNet-22k, 5 GB: 102 ms in stream order, 9.1 in the order of next uses
-// (kb_sim 6.8, kb_prev 1.5, kb_init 0.7); 300,000 samples, 10 epochs, 2 workers
-// 620 -> 4.4; 10,000 samples, 5 epochs, 4 workers 2.6 -> 0.7. What bounds kb_sim:
-// per batch two block-wide scans and five barriers, per change of T several
-// looks into blocks (about 50 us).
+// ImageNet-22k, 5 GB: 102 ms in stream order, 9.0 in the order of next uses
+// (kb_sim 6.5, kb_prev 1.5, kb_init 0.7; the rest is the gaps between them); 300,000
+// samples, 10 epochs, 2 workers 620 -> 4.4; 10,000 samples, 5 epochs, 4 workers
+// 2.6 -> 0.7. What bounds kb_sim: barriers and latency, not its vector units (23%
+// busy). Per batch two block-wide scans and five barriers, per change of T several
+// looks into blocks (about 50 us). The looks also are most of what it reads: 21.9 GB
+// at ImageNet-22k with 5 GB, 9.7 with a buffer of four epochs, where nothing is
+// discarded (the rows' next and previous uses 4.5, the rest the candidates' ids and
+// sizes, a 128-byte line each).
 //
 // In stream order (bs_sim), where an epoch brings too few candidates for that or
 // the buffer holds too few samples (the rule in buffer_impl), or memory for the
@@ -401,9 +405,21 @@ constexpr int kKbList = 2048;                        // candidates per batch
 constexpr int kKbBlocks = 8192;                      // time blocks
 constexpr int kKbMinShift = 6;                       // of at least 64 positions
 constexpr int kKbSeg = kKbBlocks / kKbThreads;       // blocks per thread in the scan
-constexpr uint32_t kKbFew = 128;   // a batch of more candidates is cut before its record is searched
-constexpr uint32_t kKbMany = 32;   // as is one that puts more blocks than this over
-constexpr int kKbMinSpan = 256;    // but not below this many positions
+// A batch of more than kKbFew candidates is cut before its record is searched, as
+// is one that puts more than kKbMany blocks over, but not below kKbMinSpan
+// positions. Kernel times, us, of (a) 10,000 samples x 5 epochs x 4 workers with a
+// buffer of 180 samples, (b) 300,000 x 10 x 2, (c) 32,000 x 40 x 16, (d) ImageNet-22k:
+//                     (a)     (b)      (c)      (d)
+//   as here           449   3,026    5,068    8,751
+//   kKbFew 64         448   3,023    4,654    8,768
+//   kKbFew 512      1,379   6,821   10,958   14,787
+//   kKbMany 8         440   2,988    5,033    8,799
+//   kKbMany 128       494   3,556    5,504    8,896
+//   kKbMinSpan 128    450   2,865    5,065    8,762
+//   kKbMinSpan 1024   705   7,953    6,299    9,084
+constexpr uint32_t kKbFew = 128;
+constexpr uint32_t kKbMany = 32;
+constexpr int kKbMinSpan = 256;
 constexpr double kKbMinCands = 300;  // candidates per worker and epoch
 constexpr int64_t kKbMaxD0 = int64_t(1) << 50;       // sums over a block and a batch stay below 2^63
 constexpr int kKbSample = 16;                        // sizes per thread whose mean is taken

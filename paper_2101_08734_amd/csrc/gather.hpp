@@ -22,12 +22,14 @@ namespace nopfs {
 constexpr int kGatherWs = 14;                 // window: 2^14 samples of 8-byte values
 constexpr int kGatherWin = 1 << kGatherWs;    // 8-byte values held in LDS (128 KB)
 constexpr int kGThreads = 1024;
-// A tile holds about kGReads reads: its window's values (128 KB of LDS) are
-// loaded once for all of them, which takes as long as kGLoad reads do (10.5 us
-// and 0.65 ns a read: 166 tiles of 65,000 reads 53 us, 1,162 of 9,300 83 us).
-// Where that makes fewer than kGRounds rounds of tiles (one at a time per compute
-// unit), their number follows the last round: the cheapest of the splits that
-// fill 1 to kGRounds rounds.
+// A tile holds about kGReads reads (ImageNet-22k, 20 epochs, with 81,920, 163,840 and
+// 327,680: the staging schedule's pass 957, 888 and 832 us, the fetch model's 2,384,
+// 2,407 and 2,142; the largest was not measured on other jobs): its window's values
+// (128 KB of LDS) are loaded once for all of them, which takes as long as kGLoad
+// reads do (10.5 us and 0.65 ns a read: 166 tiles of 65,000 reads 53 us, 1,162 of
+// 9,300 83 us). Where that makes fewer than kGRounds rounds of tiles (one at a time
+// per compute unit), their number follows the last round: the cheapest of the splits
+// that fill 1 to kGRounds rounds.
 constexpr double kGReads = 163840, kGLoad = 16384;
 constexpr int64_t kGRounds = 8, kGUnits = 256;
 constexpr int kGRuns = 1024;                  // runs per pass of a tile

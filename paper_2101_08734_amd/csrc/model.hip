@@ -355,9 +355,13 @@ __device__ __forceinline__ void fm_place(const SubChunk& s, const FmRegs& g, FmL
 // One workgroup per CU (the span takes 135 KB of LDS) takes spans by ticket, in
 // order of their place in the row (the first of every row, then the second,
 // ...), so that what enters a span is mostly there when it is asked for.
-// Bound by HBM: at ImageNet-22k 6.8 GB of entries in, 5.7 GB of times and codes
-// out in 3.6 ms (3.4 TB/s); the rest is the scan, when nothing is in flight.
-// One kernel for the spans' sums, one that chained them per row and a last one
+// The row's times are chained by a scan with decoupled look-back (Merrill and
+// Garland, Single-pass Parallel Prefix Scan with Decoupled Look-back, 2016): a span
+// publishes its own sums, then its row's up to its end.
+// Bound by HBM traffic (ImageNet-22k: 6.8 GB of entries in, 5.7 GB of times and
+// codes out, 3.49 ms, 3.6 TB/s of a copy's 4.9) and, for what is missing to the
+// copy, by the scan, when the workgroup, alone on its compute unit, has nothing in
+// flight. One kernel for the spans' sums, one that chained them per row and a last one
 // that read the entries again took 2.72 + 0.15 + 3.64 ms. Positions go 16 to a
 // thread, so the span is scanned once (six barriers), and the next span's
 // entries are requested while this one goes out; a thread's times are looked

@@ -60,11 +60,18 @@
 // Stepping read by read took 37 ns a read (NoPFS, a chain of dependent
 // additions per worker); ImageNet-22k (2.2M reads per worker): Perfect 36,
 // Naive 56, StagingBuffer 63, NoPFS 82 ms, now NoPFS 13.0. ImageNet-1k on 256
-// workers: 7.4 / 11.3 / 12.8 / 16.7 ms, now 1.4 / 1.7 / 2.4 / 2.8. Bounds: the
-// random 8-byte gathers of the sizes (NoPFS at ImageNet-22k without them:
-// 8.1 ms) and, below that, instruction issue (1,250 vector instructions per
-// wave and chunk on two waves per SIMD). 1,024 threads of two reads each:
-// 15.3 ms (the scans' cross-lane steps double).
+// workers: 7.4 / 11.3 / 12.8 / 16.7 ms, now 1.4 / 1.7 / 2.4 / 2.8. Bounds:
+//   many workers, a size table larger than an L2 (ImageNet-22k, 114 MB): the
+//     128-byte lines that the random 8-byte gathers fetch, 73 to 81 GB a call at
+//     6.6 to 6.9 TB/s at the L2s' outer side, which counts what the last-level
+//     cache serves too (NoPFS without the gathers: 8.1 ms);
+//   many workers, a smaller table (ImageNet-1k, 10 MB, 256 workers): Perfect and
+//     Naive those lines again (7.7 and 6.3 TB/s), the staging policies the chunk's
+//     barriers and latency (4.6 TB/s, vector units 32% busy, occupancy 24%: one
+//     workgroup per compute unit);
+//   few workers (ImageNet-1k on 16): the latency of one workgroup's chunks, on 16
+//     of 256 compute units (0.4 TB/s, vector units 2.5% busy).
+// 1,024 threads of two reads each: 15.3 ms (the scans' cross-lane steps double).
 
 #include <cmath>
 #include <new>
@@ -81,8 +88,14 @@ namespace {
 constexpr int kPsFew = 512, kPsMany = 256;
 constexpr int64_t kPsUnits = 256;                     // compute units
 constexpr int kPsPer = 4;                             // reads per thread and chunk
-constexpr int kPsMinStep = 512;   // scans shorter than this, twice in a chunk: one wave goes on
-constexpr int kPsMinWave = 8;     // wave scans shorter than this: read by read
+// Scans shorter than kPsMinStep, twice in a chunk: one wave goes on. (With 256 the
+// same times; with 1,024 windows of 700 reads 7,588 us instead of 4,243, 300
+// workers 584 instead of 476.)
+constexpr int kPsMinStep = 512;
+// Wave scans shorter than kPsMinWave: read by read. (With 4 windows of 12 reads
+// 37.2 ms instead of 43.3, but of 4 reads 72.4 instead of 69.9; with 16 windows of
+// 12 62.3.)
+constexpr int kPsMinWave = 8;
 // The first reads of a row are stepped: its values double every few reads, so
 // that scans stop at once (StagingBuffer, windows longer than the row: 656 reads
 // of one worker 72 us with scans from the first read, 31 stepped; 684 reads on
