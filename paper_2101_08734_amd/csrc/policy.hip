@@ -104,8 +104,12 @@ constexpr int kPsMinWave = 8;
 // Fewer where one wave would go on with short windows anyway: with 256 threads
 // and windows of less than 512 reads 512 (rows of 2,048 to 4,096 reads on 300 to
 // 1,024 workers 5% faster than with 1,024), with windows of less than 128, whose
-// batches wait for each other, 256 (rows of 512 to 1,024 reads 20% faster).
+// batches wait for each other, 256 (rows of 512 to 1,024 reads 20% faster). Naive
+// with more than two workgroups per compute unit, which hide each other's scans
+// but not the steps, 384 (1,024 workers, 2,048 and 10,240 reads: 90 and 168 us with
+// 768, 79 and 155 with 384; 4,096 workers, 1,024 reads 212 and 172).
 constexpr int kPsHead = 1024, kPsHeadNaive = 768, kPsHeadShort = 512, kPsHeadPrev = 256;
+constexpr int kPsHeadNaiveMany = 384;
 // short scans of a row's first chunk before one wave goes on (of others: 2)
 constexpr int kPsShortsFirst = 8, kPsShorts = 2;
 constexpr int kPsMaxJ = 32;
@@ -629,7 +633,10 @@ ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ siz
       __syncthreads();
       if (tid == 0) s_near[0] = 0;
       const int hmax = (near & 8u) ? kPsHeadPrev
-                                   : (kPsThreads == kPsMany && (near & 2u) ? kPsHeadShort : kHead);
+                       : kPsThreads == kPsMany && (near & 2u) ? kPsHeadShort
+                       : kPsThreads == kPsMany && kPolicy == kNaive && gridDim.x > 2 * kPsUnits
+                           ? kPsHeadNaiveMany
+                           : kHead;
       pos = n < hmax ? n : hmax;
       head(pos, (near & 8u) != 0u);
     }

@@ -149,3 +149,13 @@ def test_first_reads_of_all_classes(oracle):
     torch.cuda.synchronize()
     for what, g, e in zip(("t", "finish", "io"), got, want):
         assert np.array_equal(g.cpu().numpy(), e), what
+
+
+@pytest.mark.parametrize("M", [383, 384, 385, 767, 769, 1025])
+def test_first_reads_of_many_workers(oracle, M):
+    """More than two workgroups per compute unit: Naive steps 384 reads instead of 768."""
+    shape = (513 * M - 1, 1, 513, 1, 0, M)
+    R = oracle.access_streams(oracle.make_job(*shape))
+    sizes = wl.random_sizes(shape[0], M, 1_000, 2_000_000)
+    fill = np.maximum(0, np.arange(R.shape[1]) - 700)[None].repeat(513, 0).astype(np.int32)
+    _check(oracle, shape, R, sizes, fill, dict(wl.LASSEN_MODEL, c=1e9), M)
