@@ -856,10 +856,11 @@ int launch_stats(const SegParams& p, const uint32_t* Pk, const uint16_t* OT, uin
                    (reinterpret_cast<uintptr_t>(first) & 15) == 0;
   const dim3 grid(xcd_padded(ntiles)), block(kStatsThreads);
   const int64_t runs = int64_t(p.E) * p.nsc;
-  // (many tiles of 16 short runs and more: a few rounds of loads cost less than
-  // the threads; 118 workers, 22 runs of 35 reads a tile: 12 threads 313 us, 4 284)
+  // (without the list and with many tiles of 16 short runs and more a few rounds
+  // of loads cost less than the threads; 118 workers, 22 runs of 35 reads a tile:
+  // 12 threads 316 us, 4 290. The list's waits hide the threads: 316 and 366.)
   const double mean = run_mean(p);
-  const int64_t split = mean <= 64 && ntiles > 1024 && runs >= 16
+  const int64_t split = !cc && mean <= 64 && ntiles > 1024 && runs >= 16
                             ? int64_t(kStatsSplit)
                             : std::max(int64_t(kStatsSplit), int64_t((mean * 1.25 + 24) / kRunLoads));
   const uint32_t ns = uint32_t(std::max(int64_t(1), std::min(kStatsThreads / runs, split)));
