@@ -627,7 +627,9 @@ ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ siz
     };
     int pos = 0;
     constexpr int kHead = kPolicy == kPerfect ? 0 : (kPolicy == kNaive ? kPsHeadNaive : kPsHead);
-    if (kHead > 0 && f0 == 0 && !(near & 4u)) {
+    // (said to be unlikely, the steps' uniform values spill, not the chunk loop's:
+    // rows of 7.2M reads, 16 workers, Naive 20,059 -> 19,813 us)
+    if (__builtin_expect(kHead > 0 && f0 == 0 && !(near & 4u), 0)) {
       stage();
       stage_io();
       __syncthreads();
