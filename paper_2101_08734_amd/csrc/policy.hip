@@ -99,8 +99,9 @@ constexpr int kPsMinWave = 8;
 // The first reads of a row are stepped: its values double every few reads, so
 // that scans stop at once (StagingBuffer, windows longer than the row: 656 reads
 // of one worker 72 us with scans from the first read, 31 stepped; 684 reads on
-// 4,096 workers 714 and 338). Up to 1,024 reads (768 of Naive, whose scans are cheaper;
-// none of Perfect, which scans a row of any length as fast as it steps it).
+// 4,096 workers 714 and 338). Up to 1,024 reads (768 of Naive, whose scans are cheaper,
+// 256 of Perfect: 16 workers, rows of 100, 332 and 2,600 reads 12.4, 17.8 and 28.2 us
+// with none, 10.8, 15.3 and 26.7 with 256, 9.5, 13.5 and 34.2 with 768).
 // Fewer where one wave would go on with short windows anyway: with 256 threads
 // and windows of less than 512 reads 512 (rows of 2,048 to 4,096 reads on 300 to
 // 1,024 workers 5% faster than with 1,024), with windows of less than 128, whose
@@ -108,9 +109,11 @@ constexpr int kPsMinWave = 8;
 // with more than two workgroups per compute unit, which hide each other's scans
 // but not the steps, 384 (1,024 workers, 2,048 and 10,240 reads: 90 and 168 us with
 // 768, 79 and 155 with 384; 4,096 workers, 1,024 reads 212 and 172).
-constexpr int kPsHead = 1024, kPsHeadNaive = 768, kPsHeadShort = 512, kPsHeadPrev = 256;
+constexpr int kPsHead = 1024, kPsHeadNaive = 768, kPsHeadPerfect = 256, kPsHeadShort = 512, kPsHeadPrev = 256;
 constexpr int kPsHeadNaiveMany = 384;
-// short scans of a row's first chunk before one wave goes on (of others: 2)
+// Short scans of a row's first chunk before one wave goes on (of others, and of
+// Perfect: 2. Rows of 332 reads on 16 workers 21.6 us with 8 for Perfect too, 17.6
+// with 2; StagingBuffer's rows of 2,600 reads 90 and 110).
 constexpr int kPsShortsFirst = 8, kPsShorts = 2;
 constexpr int kPsMaxJ = 32;
 constexpr int kPsClasses = 1 + 2 * kPsMaxJ;           // PFS, remote j, own j
@@ -626,10 +629,10 @@ ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ siz
       }
     };
     int pos = 0;
-    constexpr int kHead = kPolicy == kPerfect ? 0 : (kPolicy == kNaive ? kPsHeadNaive : kPsHead);
+    constexpr int kHead = kPolicy == kPerfect ? kPsHeadPerfect : (kPolicy == kNaive ? kPsHeadNaive : kPsHead);
     // (said to be unlikely, the steps' uniform values spill, not the chunk loop's:
     // rows of 7.2M reads, 16 workers, Naive 20,059 -> 19,813 us)
-    if (__builtin_expect(kHead > 0 && f0 == 0 && !(near & 4u), 0)) {
+    if (__builtin_expect(f0 == 0 && !(near & 4u), 0)) {
       stage();
       stage_io();
       __syncthreads();
@@ -932,7 +935,7 @@ ps_sim(PsShape r, const int32_t* __restrict__ R, const int64_t* __restrict__ siz
       const int np = s_pos;
       if (np - pos < kPsMinStep) ++shorts;
       pos = np;
-      if (shorts < (f0 == 0 ? kPsShortsFirst : kPsShorts) || pos >= n) continue;
+      if (shorts < (f0 == 0 && kPolicy != kPerfect ? kPsShortsFirst : kPsShorts) || pos >= n) continue;
 
       // one wave goes on from here
       stage();
